@@ -133,7 +133,7 @@ int time_candidate(std::vector<Prepared>& P, int prec, int mid_every, const Cand
     if (rc) break;
   }
   int64_t nwt = 0, nwa = 0;
-  if (!rc) rc = write_tables(ws + off, lpd, preps, cand.workgroups, grp.stream, staging, &grp.cfg,
+  if (!rc) rc = write_tables(ws + off, lpd, preps, prec, cand.workgroups, grp.stream, staging, &grp.cfg,
                             &nwt, &nwa);
   if (!rc && grp.launch_init()) rc = fail(OPDHG_ERR_DEVICE, device_error_string());
   if (!rc && hipStreamSynchronize(grp.stream) != hipSuccess) rc = fail(OPDHG_ERR_DEVICE, "init");

@@ -2023,7 +2023,8 @@ static std::vector<int64_t> spread_long_tiles(const std::vector<Tile>& tiles) {
 // Items of one side for all LPs, chunked: fills slot / first and each LP's
 // slot count.
 void side_items(std::vector<LpDev>& lps, const std::vector<const Prepared*>& preps, bool tside,
-                int64_t cap, int* grid, int* chunk, std::vector<WorkItem>& out, bool step) {
+                int64_t cap, int* grid, int* chunk, std::vector<WorkItem>& out, bool step,
+                bool chunk_slots) {
   out.clear();
   std::vector<std::pair<int64_t, int64_t>> range(lps.size());
   for (size_t i = 0; i < lps.size(); ++i) {
@@ -2041,24 +2042,24 @@ void side_items(std::vector<LpDev>& lps, const std::vector<const Prepared*>& pre
   const int64_t n = (int64_t)out.size();
   chunking(n, cap, grid, chunk);
   const int64_t C = *chunk;
-  // The step kernels store every tile's partial sums in the slot of its
+  // The FP32 step kernels store every tile's partial sums in the slot of its
   // index within the LP's list: an LP's step partials, and the order the
   // decision adds them in, do not depend on how the set's items are chunked
   // over workgroups, so a packed or served LP adds exactly what its solo
-  // solve adds. The evaluation kernels, whose double-double sums do not
-  // depend on the order, store one partial per chunk touching the LP, in
-  // the slot of the chunk's ordinal among those chunks.
+  // solve adds. The evaluation kernels and the FP64 step kernels, whose
+  // double-double sums do not depend on the order, store one partial per
+  // chunk touching the LP, in the slot of the chunk's ordinal among those
+  // chunks.
   for (size_t i = 0; i < lps.size(); ++i) {
     const int64_t s = range[i].first, e = range[i].second;
     for (int64_t q = s; q < e; ++q) {
-      out[q].slot = out[q].tile;
+      out[q].slot = chunk_slots ? (int32_t)(q / C - s / C) : out[q].tile;
       out[q].first = q == s ? 1 : 0;
     }
-    if (step) {
-      (tside ? lps[i].nslot_st : lps[i].nslot_sa) = (int32_t)(e - s);
-    } else {
-      (tside ? lps[i].nslot_t : lps[i].nslot_a) =
-          e > s ? (int32_t)((e - 1) / C - s / C + 1) : 0;
+    const int32_t nch = e > s ? (int32_t)((e - 1) / C - s / C + 1) : 0;
+    (tside ? lps[i].nslot_st : lps[i].nslot_sa) = chunk_slots ? nch : (int32_t)(e - s);
+    if (!step) {
+      (tside ? lps[i].nslot_t : lps[i].nslot_a) = nch;
       (tside ? lps[i].item0_t : lps[i].item0_a) = (int32_t)s;
     }
   }
@@ -2069,30 +2070,29 @@ void side_items(std::vector<LpDev>& lps, const std::vector<const Prepared*>& pre
 // Write the tables for a list of LPs into device memory at `dst` and point
 // cfg at them.
 int write_tables(uint8_t* dst, const std::vector<LpDev>& lps_in,
-                 const std::vector<const Prepared*>& preps, int64_t cap, hipStream_t stream,
+                 const std::vector<const Prepared*>& preps, int prec, int64_t cap,
+                 hipStream_t stream,
                  std::vector<uint8_t>& staging, LaunchCfg* cfg, int64_t* nwt, int64_t* nwa,
                  size_t capacity, bool fixed_launch) {
   std::vector<LpDev> lps(lps_in);
   std::vector<WorkItem> wt, wa, st, sa;
   std::vector<WinItem> vt, va;
   std::vector<SegItem> gt, ga;
-  side_items(lps, preps, true, cap, &cfg->grid_t, &cfg->chunk_t, wt);
-  side_items(lps, preps, false, cap, &cfg->grid_a, &cfg->chunk_a, wa);
+  const bool chunk_slots = prec == OPDHG_FP64;
+  side_items(lps, preps, true, cap, &cfg->grid_t, &cfg->chunk_t, wt, false, chunk_slots);
+  side_items(lps, preps, false, cap, &cfg->grid_a, &cfg->chunk_a, wa, false, chunk_slots);
   if (fixed_launch) {
     // the server's changing set: its step kernels run the evaluation lists
     // with the device-side chunking (no LP there has windowed chunks)
-    for (size_t i = 0; i < lps.size(); ++i) {
+    for (size_t i = 0; i < lps.size(); ++i)
       if (preps[i]->win_t.chunks() || preps[i]->win_a.chunks())
         return fail(OPDHG_ERR_INVALID_ARGUMENT, "windowed chunks in a shared launch set");
-      lps[i].nslot_st = (int32_t)preps[i]->tiles_t.size();
-      lps[i].nslot_sa = (int32_t)preps[i]->tiles_a.size();
-    }
     cfg->sgrid_t = cfg->schunk_t = cfg->sgrid_a = cfg->schunk_a = 0;
     cfg->step_fixed = 0;
     cfg->evprod = 0;
   } else {
-    side_items(lps, preps, true, cap, &cfg->sgrid_t, &cfg->schunk_t, st, true);
-    side_items(lps, preps, false, cap, &cfg->sgrid_a, &cfg->schunk_a, sa, true);
+    side_items(lps, preps, true, cap, &cfg->sgrid_t, &cfg->schunk_t, st, true, chunk_slots);
+    side_items(lps, preps, false, cap, &cfg->sgrid_a, &cfg->schunk_a, sa, true, chunk_slots);
     cfg->step_fixed = 1;
     int64_t nst = 0, nsa = 0;
     for (const Prepared* P : preps) {
@@ -2627,7 +2627,7 @@ static int session_from_prepared(opdhg_prepared& pr, void* d_workspace, size_t w
   S.d_tables = S.ws + S.L.total;
   std::vector<uint8_t> staging;
   int64_t nwt = 0, nwa = 0;
-  if ((rc = write_tables(S.d_tables, {S.lpd}, {&S.P}, grid_cap(p), S.grp.stream, staging,
+  if ((rc = write_tables(S.d_tables, {S.lpd}, {&S.P}, p->precision, grid_cap(p), S.grp.stream, staging,
                          &S.grp.cfg, &nwt, &nwa)))
     return rc;
   if ((rc = S.grp.launch_init())) return fail(OPDHG_ERR_DEVICE, device_error_string());
@@ -3017,7 +3017,7 @@ static int batch_solve(opdhg_batch& B, void* d_workspace, size_t workspace_bytes
   int64_t wt = 0, wa = 0;
   std::vector<const Prepared*> preps(count);
   for (int i = 0; i < count; ++i) preps[i] = &P[i];
-  if ((rc = write_tables(ws + off, lpd, preps, grid_cap(p), grp.stream, staging, &grp.cfg, &wt,
+  if ((rc = write_tables(ws + off, lpd, preps, p->precision, grid_cap(p), grp.stream, staging, &grp.cfg, &wt,
                          &wa))) {
     grp.release();
     return rc;

@@ -14,9 +14,10 @@
 // kTileCap is a tile of its own, reduced by the whole workgroup.
 //
 // The epilogues fuse the method's vector work into the sparse products and
-// accumulate FP64 partial sums per thread. The step kernels store one
+// accumulate FP64 partial sums per thread. The FP32 step kernels store one
 // partial per tile (a DPP scan per wave, then the waves' totals added once
-// per window of work items); the evaluation kernels store one per chunk and
+// per window of work items); the FP64 ones and the evaluation kernels, whose
+// double-double sums do not depend on the order, store one per chunk and
 // LP. A one-workgroup-per-LP decision kernel sums an LP's partials in a
 // fixed order and takes its scalar decision. Workgroups never wait for or
 // signal each other inside a launch; kernel boundaries carry every result
@@ -184,6 +185,14 @@ __device__ __forceinline__ DD dd_shfl_xor(const DD& a, int off) {
   return DD{__shfl_xor(a.hi, off, 64), __shfl_xor(a.lo, off, 64)};
 }
 
+// Lane l's value of v (l uniform over the wave).
+__device__ __forceinline__ double lane_value(double v, int l) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, l);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
 // The value of another lane moved by DPP (a VALU operand modifier, no LDS
 // traffic): CTRL selects the pattern, ROWS the rows of 16 lanes written;
 // lanes without a source, and rows not written, get 0.
@@ -204,118 +213,212 @@ __device__ __forceinline__ void dd_dpp_step(DD (&v)[NV]) {
   }
 }
 
-// Merge NV double-doubles over the workgroup (NW waves) in a fixed order;
-// thread 0 gets the totals. s_red holds NW * NV DD. Within a wave a scan of
-// DPP moves brings the wave's total to lane 63: row_shr by 1, 2, 4 and 8
-// (lane 15 of each row of 16 holds the row's sum), row_bcast:15 into rows
-// 1 and 3, then row_bcast:31 into rows 2 and 3. Every level runs in the
+// Plain FP64 sums (see acc_prod) of NV quantities over a wave, in a fixed
+// order: a scan of DPP moves brings the totals to lane 63: row_shr by 1, 2,
+// 4 and 8 (lane 15 of each row of 16 holds the row's sum), row_bcast:15 into
+// rows 1 and 3, then row_bcast:31 into rows 2 and 3. Every level runs in the
 // VALU, so the reductions of all workgroups on a CU do not queue on LDS.
-// PLAIN: FP64 sums of the high parts only (see acc_prod).
-template <int NV, bool PLAIN>
+template <int NV>
 __device__ __forceinline__ void wave_scan(DD (&v)[NV]) {
-  dd_dpp_step<0x111, 0xF, PLAIN>(v);  // row_shr:1
-  dd_dpp_step<0x112, 0xF, PLAIN>(v);  // row_shr:2
-  dd_dpp_step<0x114, 0xF, PLAIN>(v);  // row_shr:4
-  dd_dpp_step<0x118, 0xF, PLAIN>(v);  // row_shr:8
-  dd_dpp_step<0x142, 0xA, PLAIN>(v);  // row_bcast:15
-  dd_dpp_step<0x143, 0xC, PLAIN>(v);  // row_bcast:31
+  dd_dpp_step<0x111, 0xF, true>(v);  // row_shr:1
+  dd_dpp_step<0x112, 0xF, true>(v);  // row_shr:2
+  dd_dpp_step<0x114, 0xF, true>(v);  // row_shr:4
+  dd_dpp_step<0x118, 0xF, true>(v);  // row_shr:8
+  dd_dpp_step<0x142, 0xA, true>(v);  // row_bcast:15
+  dd_dpp_step<0x143, 0xC, true>(v);  // row_bcast:31
 }
 
-template <int NV, int NW = kBlock / 64, bool PLAIN = false>
-__device__ __forceinline__ void block_sum(DD (&v)[NV], DD* s_red) {
+// Exchange between a wave's halves (ROW false) or between its rows of 16,
+// 0 with 1 and 2 with 3 (ROW true): the lanes of the second half (odd rows)
+// of a and of the first half (even rows) of b change places, so that
+// afterwards a holds a's lower and b's lower lanes, b their upper ones.
+template <bool ROW>
+__device__ __forceinline__ void lane_swap(double& a, double& b) {
+  const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);
+  uint32_t w[2][2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint32_t x = (uint32_t)(ua >> (32 * h)), y = (uint32_t)(ub >> (32 * h));
+    if constexpr (ROW) {
+      const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+      w[h][0] = r[0], w[h][1] = r[1];
+    } else {
+      const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+      w[h][0] = r[0], w[h][1] = r[1];
+    }
+  }
+  a = __builtin_bit_cast(double, (uint64_t)w[1][0] << 32 | w[0][0]);
+  b = __builtin_bit_cast(double, (uint64_t)w[1][1] << 32 | w[0][1]);
+}
+
+// The merge of a's two halves (rows) in the lower lanes and of b's in the
+// upper ones: two quantities become one per lane.
+template <bool ROW>
+__device__ __forceinline__ DD dd_halve(DD a, DD b) {
+  lane_swap<ROW>(a.hi, b.hi);
+  lane_swap<ROW>(a.lo, b.lo);
+  return dd_merge(a, b);
+}
+
+template <int CTRL>
+__device__ __forceinline__ DD dd_dpp(const DD& v) {
+  return DD{dpp_f64<CTRL, 0xF>(v.hi), dpp_f64<CTRL, 0xF>(v.lo)};
+}
+
+constexpr int pow2_above(int v) { return v <= 1 ? 1 : 2 * pow2_above((v + 1) / 2); }
+
+// Double-double totals of NV <= 16 quantities over a wave. With P the power
+// of two above NV, the lanes [q * 64 / P, (q + 1) * 64 / P) get quantity
+// q's total (lanes of q >= NV: zero). Each level halves the quantities a
+// lane works on (between the wave's halves, its rows, the halves of a row,
+// the halves of those) until one is left, and the rest of the levels merge
+// that one: 7 merges of about 14 instructions for 4 quantities and 17 for
+// 12, where a scan of all of them takes 24 and 72. The sums do not depend
+// on the order (see the head of this file). FP64 runs, 50k x 100k with
+// 700k entries: an attempt took 32.3 us with scans, 29.7 with this and the
+// decision below; 15k x 10k with 54k entries 20.1 and 17.5.
+template <int NV>
+__device__ __forceinline__ DD wave_totals(const DD (&v)[NV]) {
+  constexpr int P = pow2_above(NV);
+  static_assert(P <= 16, "at most 16 quantities");
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  wave_scan<NV, PLAIN>(v);
-  if (lane == 63) {
+  auto at = [&](int q) { return q < NV ? v[q < NV ? q : 0] : dd_zero(); };
+  DD a[P >= 2 ? P / 2 : 1];
+  if constexpr (P >= 2) {
 #pragma unroll
-    for (int q = 0; q < NV; ++q) s_red[wave * NV + q] = v[q];
+    for (int q = 0; q < P / 2; ++q) a[q] = dd_halve<false>(at(q), at(q + P / 2));
+  } else {
+    a[0] = dd_halve<false>(v[0], v[0]);
   }
-  lds_barrier();
-  if (threadIdx.x == 0) {
+  DD b[P >= 4 ? P / 4 : 1];
+  if constexpr (P >= 4) {
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      DD t = s_red[q];
+    for (int q = 0; q < P / 4; ++q) b[q] = dd_halve<true>(a[q], a[q + P / 4]);
+  } else {
+    b[0] = dd_halve<true>(a[0], a[0]);
+  }
+  // inside a row of 16: lane l with l + 8 (row_ror:8), then with its mirror
+  // in 8 lanes (row_half_mirror), then quads
+  DD c[P >= 8 ? P / 8 : 1];
+  if constexpr (P >= 8) {
+    const bool up = (lane & 8) != 0;
 #pragma unroll
-      for (int w = 1; w < NW; ++w) {
-        if constexpr (PLAIN) t.hi += s_red[w * NV + q].hi;
-        else t = dd_merge(t, s_red[w * NV + q]);
-      }
-      v[q] = t;
+    for (int q = 0; q < P / 8; ++q) {
+      const DD& x = b[q];
+      const DD& y = b[q + P / 8];
+      c[q] = dd_merge(up ? y : x, dd_dpp<0x128>(up ? x : y));
     }
+  } else {
+    c[0] = dd_merge(b[0], dd_dpp<0x128>(b[0]));
   }
-  lds_barrier();
+  DD d;
+  if constexpr (P >= 16) {
+    const bool up = (lane & 4) != 0;
+    d = dd_merge(up ? c[1] : c[0], dd_dpp<0x141>(up ? c[0] : c[1]));
+  } else {
+    d = dd_merge(c[0], dd_dpp<0x141>(c[0]));
+  }
+  d = dd_merge(d, dd_dpp<0x4E>(d));  // quad_perm:[2,3,0,1]
+  d = dd_merge(d, dd_dpp<0xB1>(d));  // quad_perm:[1,0,3,2]
+  return d;
 }
 
-// Store workgroup totals in partial slot `slot` (thread 0). Partials are
-// laid out quantity-major (hi and lo of quantity q at 2q * stride + slot and
-// (2q + 1) * stride + slot) so the decision kernel reads them coalesced.
-template <int NV>
-__device__ __forceinline__ void store_partials(double* part, int stride, int slot,
-                                               const DD (&v)[NV]) {
-  if (threadIdx.x == 0) {
-    gptr<double> g = gp(part);
+// The waves' totals of NV quantities into s_red (wave-major).
+template <int NV, bool PLAIN>
+__device__ __forceinline__ void store_wave_totals(DD (&v)[NV], DD* s_red) {
+  const int lane = threadIdx.x & 63;
+  DD* const dst = s_red + (threadIdx.x >> 6) * NV;
+  if constexpr (PLAIN) {
+    wave_scan<NV>(v);
+    if (lane == 63) {
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      g[(size_t)(2 * q) * stride + slot] = v[q].hi;
-      g[(size_t)(2 * q + 1) * stride + slot] = v[q].lo;
+      for (int q = 0; q < NV; ++q) dst[q] = v[q];
     }
+  } else {
+    constexpr int kLanes = 64 / pow2_above(NV);  // lanes holding a quantity's total
+    const DD t = wave_totals<NV>(v);
+    const int q = lane / kLanes;
+    if (lane % kLanes == 0 && q < NV) dst[q] = t;
   }
 }
 
-// Fixed-order merge of NV double-double partials over `count` slots (whole
-// workgroup; quantity-major with the given stride); thread 0 gets the
-// rounded totals. Partials were written by
-// earlier launches. Each thread loads B tiles' partials before merging
-// them, so the loads of a batch are in flight together.
-template <int NV>
-__device__ __forceinline__ void sum_partials(const double* __restrict__ part, int stride,
-                                             int count, double (&out)[NV], DD* s_red) {
-  constexpr int B = NV <= 4 ? 8 : 2;
-  DD v[NV];
+// Merge NV double-doubles over the workgroup (NW waves) in a fixed order;
+// thread q < NV gets quantity q's total. s_red holds NW * NV DD.
+template <int NV, int NW, bool PLAIN>
+__device__ __forceinline__ DD block_total(DD (&v)[NV], DD* s_red) {
+  store_wave_totals<NV, PLAIN>(v, s_red);
+  lds_barrier();
+  DD t = dd_zero();
+  if (threadIdx.x < NV) {
+    t = s_red[threadIdx.x];
 #pragma unroll
-  for (int q = 0; q < NV; ++q) v[q] = dd_zero();
-  const gptr<const double> g = gp(part);
-  for (int base = threadIdx.x; base < count; base += kBlock * B) {
-    double h[B][NV], l[B][NV];
+    for (int w = 1; w < NW; ++w) {
+      if constexpr (PLAIN) t.hi += s_red[w * NV + threadIdx.x].hi;
+      else t = dd_merge(t, s_red[w * NV + threadIdx.x]);
+    }
+  }
+  return t;
+}
+
+// Store workgroup totals (thread q holds quantity q's) in partial slot
+// `slot`. Partials are laid out quantity-major (hi and lo of quantity q at
+// 2q * stride + slot and (2q + 1) * stride + slot) so the decision kernel
+// reads them coalesced.
+template <int NV>
+__device__ __forceinline__ void store_partials(double* part, int stride, int slot, const DD& t) {
+  if (threadIdx.x < NV) {
+    const gptr<double> g = gp(part);
+    const size_t q = threadIdx.x;
+    g[2 * q * stride + slot] = t.hi;
+    g[(2 * q + 1) * stride + slot] = t.lo;
+  }
+}
+
+// Double-double total of one quantity over `count` partial slots, by one
+// wave: hi and lo words at h and h + stride, B slots per lane in flight;
+// every lane gets it. Partials were written by earlier launches. A wave per
+// quantity needs one reduction of one quantity, where a workgroup that
+// shares out the slots reduces all of them over its waves.
+__device__ __forceinline__ DD wave_partials(gptr<const double> h, int stride, int count) {
+  constexpr int B = 16;
+  const int lane = threadIdx.x & 63;
+  DD v[1] = {dd_zero()};
+  for (int base = lane; base < count; base += 64 * B) {
+    double hv[B], lv[B];
 #pragma unroll
     for (int k = 0; k < B; ++k) {
-      // out-of-range slots re-read slot `base` (valid) and are zeroed
-      const int t = base + k * kBlock;
-      const bool ok = t < count;
-      const int tc = ok ? t : base;
-#pragma unroll
-      for (int q = 0; q < NV; ++q) {
-        const double hv = g[(size_t)(2 * q) * stride + tc];
-        const double lv = g[(size_t)(2 * q + 1) * stride + tc];
-        h[k][q] = ok ? hv : 0.0;
-        l[k][q] = ok ? lv : 0.0;
+      // only loads behind the uniform test; slots past the count re-read
+      // slot `base` (valid) and add zero
+      const int t = base + k * 64;
+      hv[k] = lv[k] = 0.0;
+      if (base - lane + k * 64 < count) {
+        const int tc = t < count ? t : base;
+        hv[k] = h[tc];
+        lv[k] = h[(size_t)stride + tc];
       }
     }
 #pragma unroll
     for (int k = 0; k < B; ++k) {
-#pragma unroll
-      for (int q = 0; q < NV; ++q) v[q] = dd_merge(v[q], DD{h[k][q], l[k][q]});
+      if (base - lane + k * 64 < count) {
+        const bool ok = base + k * 64 < count;
+        v[0] = dd_merge(v[0], DD{ok ? hv[k] : 0.0, ok ? lv[k] : 0.0});
+      }
     }
   }
-  block_sum<NV>(v, s_red);
-#pragma unroll
-  for (int q = 0; q < NV; ++q) out[q] = dd_value(v[q]);
+  return wave_totals<1>(v);
 }
 
-// The same for two partial arrays at once (NA quantities over ca slots of
-// pa, then NB over cb slots of pb): one pass, so the loads of both arrays
-// are in flight together. PLAIN: the partials are plain FP64 sums (their
-// low words are zero), read and added as plain doubles.
-template <int NA, int NB, bool PLAIN, typename Mid>
+// Plain FP64 sums (FP32 runs' partials, whose low words are zero) of two
+// partial arrays at once, NA quantities over ca slots of pa and NB over cb
+// slots of pb, in a fixed order: the loads of both arrays are in flight
+// together. Thread 0 gets the totals.
+template <int NA, int NB, typename Mid>
 __device__ __forceinline__ void sum_partials2(const double* pa, int sa, int ca, const double* pb,
                                               int sb, int cb, double (&out)[NA + NB],
                                               DD* s_red, Mid&& mid) {
+  constexpr bool PLAIN = true;
   constexpr int B = 8;  // 2048 slots per round: one round of loads for most launch sets
   DD v[NA + NB];
-  if constexpr (!PLAIN) {  // plain sums are set to zero by the first round
-#pragma unroll
-    for (int q = 0; q < NA + NB; ++q) v[q] = dd_zero();
-  }
   const gptr<const double> ga = gp(pa), gb = gp(pb);
   const int count = ca > cb ? ca : cb;
   // Every thread runs the first round; mid() runs between its loads and
@@ -324,27 +427,21 @@ __device__ __forceinline__ void sum_partials2(const double* pa, int sa, int ca, 
   // test); inside a group, slots past the count read slot 0 and add zero.
   auto round = [&](int r0, bool first) {
     const int t0 = r0 + (int)threadIdx.x;
-    double h[B][NA + NB], l[B][NA + NB];
+    double h[B][NA + NB];
 #pragma unroll
     for (int k = 0; k < B; ++k) {
       const int t = t0 + k * kBlock;
       const int ta = t < ca ? t : 0, tb = t < cb ? t : 0;
       // only loads behind the uniform tests: the masks apply at the merge
 #pragma unroll
-      for (int q = 0; q < NA + NB; ++q) h[k][q] = l[k][q] = 0.0;
+      for (int q = 0; q < NA + NB; ++q) h[k][q] = 0.0;
       if (r0 + k * kBlock < ca) {
 #pragma unroll
-        for (int q = 0; q < NA; ++q) {
-          h[k][q] = ga[(size_t)(2 * q) * sa + ta];
-          if constexpr (!PLAIN) l[k][q] = ga[(size_t)(2 * q + 1) * sa + ta];
-        }
+        for (int q = 0; q < NA; ++q) h[k][q] = ga[(size_t)(2 * q) * sa + ta];
       }
       if (r0 + k * kBlock < cb) {
 #pragma unroll
-        for (int q = 0; q < NB; ++q) {
-          h[k][NA + q] = gb[(size_t)(2 * q) * sb + tb];
-          if constexpr (!PLAIN) l[k][NA + q] = gb[(size_t)(2 * q + 1) * sb + tb];
-        }
+        for (int q = 0; q < NB; ++q) h[k][NA + q] = gb[(size_t)(2 * q) * sb + tb];
       }
     }
     if (first) {
@@ -352,12 +449,10 @@ __device__ __forceinline__ void sum_partials2(const double* pa, int sa, int ca, 
       // plain sums start from a zero the compiler cannot see: with a known
       // zero it moves the first additions into the load branches above,
       // each then waiting there for its loads
-      if constexpr (PLAIN) {
-        double z = 0.0;
-        asm volatile("" : "+v"(z));
+      double z = 0.0;
+      asm volatile("" : "+v"(z));
 #pragma unroll
-        for (int q = 0; q < NA + NB; ++q) v[q] = DD{z, 0.0};
-      }
+      for (int q = 0; q < NA + NB; ++q) v[q] = DD{z, 0.0};
     }
 #pragma unroll
     for (int k = 0; k < B; ++k) {
@@ -367,17 +462,16 @@ __device__ __forceinline__ void sum_partials2(const double* pa, int sa, int ca, 
 #pragma unroll
         for (int q = 0; q < NA + NB; ++q) {
           const bool ok = q < NA ? oka : okb;
-          if constexpr (PLAIN) v[q].hi += ok ? h[k][q] : 0.0;
-          else v[q] = dd_merge(v[q], DD{ok ? h[k][q] : 0.0, ok ? l[k][q] : 0.0});
+          v[q].hi += ok ? h[k][q] : 0.0;
         }
       }
     }
   };
   round(0, true);
   for (int r0 = kBlock * B; r0 < count; r0 += kBlock * B) round(r0, false);
-  block_sum<NA + NB, kBlock / 64, PLAIN>(v, s_red);
+  const double t = block_total<NA + NB, kBlock / 64, PLAIN>(v, s_red).hi;
 #pragma unroll
-  for (int q = 0; q < NA + NB; ++q) out[q] = dd_value(v[q]);
+  for (int q = 0; q < NA + NB; ++q) out[q] = lane_value(t, q);  // wave 0 holds them
 }
 
 // ---- numbers of the sparse products: exact products and double-double
@@ -733,8 +827,8 @@ __device__ __forceinline__ void dd_reset(DD (&v)[NV]) {
 template <int NV, bool PLAIN = false>
 __device__ __forceinline__ void flush_partials(DD (&p)[NV], DD* s_red, double* part, int stride,
                                                int slot) {
-  block_sum<NV, kBlock / 64, PLAIN>(p, s_red);
-  store_partials<NV>(part, stride, slot, p);
+  store_partials<NV>(part, stride, slot, block_total<NV, kBlock / 64, PLAIN>(p, s_red));
+  lds_barrier();  // s_red is written again by the next LP's part
   dd_reset(p);
 }
 
@@ -1035,8 +1129,8 @@ __device__ __forceinline__ SideChunks side_chunks(const Counts* counts, bool tsi
 }
 
 // Partial sums of the tiles of one window of work items: the four waves'
-// totals of each tile (lane 63 after wave_scan) and where the tile's sums
-// go (null: the tile's LP did not run).
+// totals of each tile, and in FP32 runs where the tile's sums go (null: the
+// tile's LP did not run).
 template <int NV>
 struct TilePartials {
   DD w[kItemWin][kBlock / 64][NV];
@@ -1052,11 +1146,18 @@ struct TilePartials {
 // to variables it sets) and returns whether the LP takes part; dest()
 // gives the LP's partial array and stride; commit() issues the row stores
 // the epilogues held back, after the tile's wave totals are in LDS and
-// before the next item can change the LP. Every tile stores its own
-// partial sums in its item's slot: each wave's totals go to LDS after the
-// tile (no barrier), and once per window of items the four waves' totals
-// of each tile are added in a fixed order and stored, after the barrier
-// the window needs anyway.
+// before the next item can change the LP. Each wave's totals of a tile go to
+// LDS after the tile (no barrier). In FP32 (PLAIN) every tile stores its own
+// partial sums in its item's slot: once per window of items the four waves'
+// totals of each tile are added in a fixed order and stored, after the
+// barrier the window needs anyway. FP64's double-double sums are the same in
+// any order, so the totals of an LP's tiles in the chunk are merged, wave q
+// taking quantity q, and stored once in the chunk's slot: the step decision
+// then reads at most 2048 slots a side instead of one per tile (34k on
+// 1.92M x 5.12M with 35M entries: k_decide 88 us
+// with one per tile, 8.8 now). The totals pass through
+// LDS, not through the threads' sums: kept in registers over the tiles they
+// cost a workgroup per CU.
 template <typename V, int NA, int NV, bool PLAIN, typename Begin, typename Load, typename Finish,
           typename Dest, typename Commit, typename Piece>
 __device__ __forceinline__ void run_chunk_spmv(const WorkItem* __restrict__ work, SideChunks sc,
@@ -1065,16 +1166,47 @@ __device__ __forceinline__ void run_chunk_spmv(const WorkItem* __restrict__ work
                                                const gptr<const V>& va, const gptr<const V>* vec,
                                                const double* div, Begin&& begin, Load&& load,
                                                Finish&& finish, Dest&& dest, Commit&& commit,
-                                               Piece&& piece, DD (&p)[NV], TilePartials<NV>& tp,
-                                               SpmvShared<V, NA>& sh) {
+                                               Piece&& piece, DD (&p)[NV],
+                                               TilePartials<NV>& tp, SpmvShared<V, NA>& sh) {
   const int chi = chunk_index(sc.grid);
   if (chi < 0) return;
   const int chunk = sc.chunk;
   const int w0 = chi * chunk;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  int lp = -1;
+  int lp = -1, slot = 0;
   bool run = false;
+  // FP64: merges the totals of the window's tiles [ka, kb), all of the
+  // current LP, into the chunk's (wave q: quantity q)
+  DD sum = dd_zero();
+  auto collect = [&](int ka, int kb) {
+    if constexpr (!PLAIN) {
+      if (wave >= NV) return;
+      if (kb - ka == 1) {
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) sum = dd_merge(sum, tp.w[ka][w][wave]);
+        return;
+      }
+      DD v[1] = {dd_zero()};
+      for (int x = ka * (kBlock / 64) + lane; x < kb * (kBlock / 64); x += 64)
+        v[0] = dd_merge(v[0], tp.w[x / (kBlock / 64)][x % (kBlock / 64)][wave]);
+      sum = dd_merge(sum, wave_totals<1>(v));
+    }
+  };
+  // and stores them in the LP's slot
+  auto store_sum = [&]() {
+    if constexpr (!PLAIN) {
+      double* d;
+      int sd;
+      dest(d, sd);
+      if (wave < NV && lane == 0 && d) {
+        const gptr<double> g = gp(d);
+        g[(size_t)(2 * wave) * sd + slot] = sum.hi;
+        g[(size_t)(2 * wave + 1) * sd + slot] = sum.lo;
+      }
+      sum = dd_zero();
+    }
+  };
   for (int k0 = 0; k0 < chunk; k0 += kItemWin) {
     const int cnt = min(kItemWin, chunk - k0);
     {
@@ -1083,12 +1215,20 @@ __device__ __forceinline__ void run_chunk_spmv(const WorkItem* __restrict__ work
       for (int q = threadIdx.x; q < cnt * kItemWords; q += kBlock) dst[q] = src[q];
     }
     lds_barrier();
+    int kb = 0, last = 0;  // the current LP's items in the window
     for (int k = 0; k < cnt; ++k) {
       const WorkItem it = uniform_item(s_items[k]);
       bool on = false;
       if (it.lp >= 0) {
         if (it.lp != lp) {
+          if (!PLAIN && run) {
+            lds_barrier();
+            collect(kb, k);
+            store_sum();
+          }
+          kb = k;
           lp = it.lp;
+          slot = it.slot;
           run = begin(it);
         }
         if (run) {
@@ -1097,43 +1237,46 @@ __device__ __forceinline__ void run_chunk_spmv(const WorkItem* __restrict__ work
             piece_tile<V, NA>(it, ci, va, vec, div, piece, sh);
           else
             spmv_tile<V, NA>(it, rp, ci, va, vec, div, load, finish, sh);
-          wave_scan<NV, PLAIN>(p);
-          if (lane == 63) {
-#pragma unroll
-            for (int q = 0; q < NV; ++q) tp.w[k][wave][q] = p[q];
-          }
+          last = k + 1;
+          store_wave_totals<NV, PLAIN>(p, tp.w[k][0]);
           dd_reset(p);
           commit();
           on = true;
         }
       }
-      if (threadIdx.x == 0) {
-        double* d;
-        int sd;
-        dest(d, sd);
-        tp.dst[k] = on ? d : nullptr;
-        tp.stride[k] = sd;
-        tp.slot[k] = it.slot;
+      if constexpr (PLAIN) {
+        if (threadIdx.x == 0) {
+          double* d;
+          int sd;
+          dest(d, sd);
+          tp.dst[k] = on ? d : nullptr;
+          tp.stride[k] = sd;
+          tp.slot[k] = it.slot;
+        }
       }
     }
     lds_barrier();  // the window's partials are in LDS; its items are rewritten next
-    for (int x = threadIdx.x; x < cnt * NV; x += kBlock) {
-      const int k = x / NV, q = x - k * NV;
-      double* d = tp.dst[k];
-      if (d) {
-        DD t = tp.w[k][0][q];
+    if constexpr (PLAIN) {
+      for (int x = threadIdx.x; x < cnt * NV; x += kBlock) {
+        const int k = x / NV, q = x - k * NV;
+        double* d = tp.dst[k];
+        if (d) {
+          DD t = tp.w[k][0][q];
 #pragma unroll
-        for (int w = 1; w < kBlock / 64; ++w) {
-          if constexpr (PLAIN) t.hi += tp.w[k][w][q].hi;
-          else t = dd_merge(t, tp.w[k][w][q]);
+          for (int w = 1; w < kBlock / 64; ++w) t.hi += tp.w[k][w][q].hi;
+          const gptr<double> g = gp(d);
+          const size_t sd = (size_t)tp.stride[k], sl = (size_t)tp.slot[k];
+          g[(2 * q) * sd + sl] = t.hi;
+          g[(2 * q + 1) * sd + sl] = t.lo;
         }
-        const gptr<double> g = gp(d);
-        const size_t sd = (size_t)tp.stride[k], sl = (size_t)tp.slot[k];
-        g[(2 * q) * sd + sl] = t.hi;
-        g[(2 * q + 1) * sd + sl] = t.lo;
       }
+    } else if (run) {
+      // padding items (of no LP) end a list: they add the tiles before them
+      collect(kb, last);
+      if (k0 + kItemWin < chunk) lds_barrier();  // the next window's tiles write there
     }
   }
+  if (!PLAIN && run) store_sum();
 }
 
 // ---------------------------------------------------------------------------
@@ -1823,8 +1966,8 @@ __device__ __forceinline__ void win_chunk(const LaunchCfg& cfg, const WinItem* l
     if (two) st.finish(r0 + r2, part[r2], q1, p);
   }
   if (st.part() != nullptr) {  // (a product run stores rows only)
-    block_sum<NV, kWinWaves, true>(p, s_red);
-    store_partials<NV>(st.part(), st.stride(), it.slot, p);
+    store_partials<NV>(st.part(), st.stride(), it.slot,
+                       block_total<NV, kWinWaves, true>(p, s_red));
   }
   st.commit();
 }
@@ -1882,8 +2025,8 @@ __device__ __forceinline__ void seg_rows(const LaunchCfg& cfg, const SegItem* li
   for (int off = kSegLanes / 2; off > 0; off >>= 1) acc.merge_xor(off);
   if (on && lane == 0) st.finish(row, (V)acc.value(), pre, p);
   if (st.part() != nullptr) {
-    block_sum<NV, kBlock / 64, Step::kPlain>(p, s_red);
-    store_partials<NV>(st.part(), st.stride(), it.slot, p);
+    store_partials<NV>(st.part(), st.stride(), it.slot,
+                       block_total<NV, kBlock / 64, Step::kPlain>(p, s_red));
   }
   st.commit();
 }
@@ -2003,14 +2146,6 @@ __global__ __launch_bounds__(kWinBlock) void k_dual_win(LaunchCfg cfg, int force
 // pointers, partial-slot counts and the copies of the parameters it reads.
 using DecideLp = DecideRec;
 
-// Lane l's value of v (l uniform over the wave).
-__device__ __forceinline__ double lane_value(double v, int l) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, l);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
 __device__ __forceinline__ DecideLp decide_lp(const LpDev* rec) {
   const gptr<const LpDev> L = gp(rec);
   DecideLp d;
@@ -2042,13 +2177,17 @@ __device__ __forceinline__ DecideLp decide_lp(const LpDev* rec) {
 // arguments and skips this round); then the factor ring, the partial sums
 // and the control block together. The factor of the attempt is read from
 // the lane that holds it once the attempt count is known.
-// One wave per SIMD: a single workgroup per LP runs this kernel, so the
-// registers go to keeping the partial loads in flight at once.
-// PLAIN: the step kernels' partials are plain FP64 sums (FP32 runs).
+// PLAIN: the step kernels' partials are plain FP64 sums (FP32 runs), added
+// by four waves in a fixed order, one wave per SIMD: a single workgroup per
+// LP runs this kernel, so the registers go to keeping the partial loads in
+// flight at once. FP64 runs give each of the seven sums a wave (wave_partials):
+// 5.2 us at 700 slots a side against 6.9 with four waves that share out the
+// slots and reduce all seven.
+constexpr int kDecBlock = 512;
 static_assert(kPowRing == 64, "lane l of a wave holds ring entries l and kPowRing + l");
 template <bool PLAIN>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_decide(
-    LaunchCfg cfg) {
+__global__ __launch_bounds__(PLAIN ? kBlock : kDecBlock)
+    __attribute__((amdgpu_waves_per_eu(PLAIN ? 1 : 2, PLAIN ? 1 : 2))) void k_decide(LaunchCfg cfg) {
   __shared__ DD s_red[4 * 7];
   // all launch arguments in one round, the solo record's fields included
   const DecideRec& sr = cfg.solo_rec;
@@ -2086,30 +2225,49 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     double sv[7];
     // the control block is read after the first round of partial loads is
     // issued, in the same round trip
-    sum_partials2<3, 4, PLAIN>(d.part_t, d.ntiles_t, d.ns_t, d.part_a, d.ntiles_a, d.ns_a, sv, s_red,
-                        [&]() {
-                          // every load first, then the moves to scalar
-                          // registers (each of which waits for its load)
-                          const int st0 = g->status, ne0 = g->need_eval, cu0 = g->cur;
-                          const int64_t kl0 = g->k_limit, rb0 = g->ring_base, k0 = g->k;
-                          const int64_t t0 = g->t, at0 = g->attempts, re0 = g->retries;
-                          const double et0 = g->eta, om0 = g->omega, w0 = g->w;
-                          const double hp0 = g->hp_norm, hd0 = g->hd_norm;
-                          status = uni(st0);
-                          need = uni(ne0);
-                          k_limit = uni(kl0);
-                          ring_base = uni(rb0);
-                          in.eta = uni(et0);
-                          in.omega = uni(om0);
-                          in.w = uni(w0);
-                          in.hp_norm = uni(hp0);
-                          in.hd_norm = uni(hd0);
-                          in.k = uni(k0);
-                          in.t = uni(t0);
-                          in.attempts = uni(at0);
-                          in.retries = uni(re0);
-                          in.cur = uni(cu0);
-                        });
+    auto control = [&]() {
+      // every load first, then the moves to scalar registers (each of
+      // which waits for its load)
+      const int st0 = g->status, ne0 = g->need_eval, cu0 = g->cur;
+      const int64_t kl0 = g->k_limit, rb0 = g->ring_base, k0 = g->k;
+      const int64_t t0 = g->t, at0 = g->attempts, re0 = g->retries;
+      const double et0 = g->eta, om0 = g->omega, w0 = g->w;
+      const double hp0 = g->hp_norm, hd0 = g->hd_norm;
+      status = uni(st0);
+      need = uni(ne0);
+      k_limit = uni(kl0);
+      ring_base = uni(rb0);
+      in.eta = uni(et0);
+      in.omega = uni(om0);
+      in.w = uni(w0);
+      in.hp_norm = uni(hp0);
+      in.hd_norm = uni(hd0);
+      in.k = uni(k0);
+      in.t = uni(t0);
+      in.attempts = uni(at0);
+      in.retries = uni(re0);
+      in.cur = uni(cu0);
+    };
+    if constexpr (PLAIN) {
+      sum_partials2<3, 4>(d.part_t, d.ntiles_t, d.ns_t, d.part_a, d.ntiles_a, d.ns_a, sv, s_red,
+                          control);
+    } else {
+      // wave q sums quantity q; the last wave, whose first thread decides,
+      // reads the control block meanwhile
+      const int q = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+      if (q < 7) {
+        const bool ts = q < 3;
+        const int stride = ts ? d.ntiles_t : d.ntiles_a;
+        const DD t = wave_partials(gp(ts ? d.part_t : d.part_a) + (size_t)(2 * (ts ? q : q - 3)) * stride,
+                                   stride, ts ? d.ns_t : d.ns_a);
+        if (lane == 0) s_red[q] = t;
+      } else {
+        control();
+      }
+      lds_barrier();
+#pragma unroll
+      for (int k = 0; k < 7; ++k) sv[k] = dd_value(s_red[k]);
+    }
     // the attempt decided here is j = attempts + 1, in the ring at
     // j - ring_base - 1 (the ring covers every attempt of the sequence);
     // the index is uniform, so its lane's values are read across the wave
@@ -2117,7 +2275,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     r = r < 0 ? 0 : (r >= kPowRing ? kPowRing - 1 : r);
     in.f_red = lane_value(rv_red, (int)r);
     in.f_gro = lane_value(rv_gro, (int)r);
-    if (status == kRunning && need == 0 && in.k < k_limit && threadIdx.x == 0) {
+    if (status == kRunning && need == 0 && in.k < k_limit &&
+        threadIdx.x == (PLAIN ? 0 : kDecBlock - 64)) {
       if (decide_step(*d.ctl, in, sv)) {
         // the guarded evaluation steps ahead look for due LPs again
         const gptr<Counts> cn = gp(const_cast<Counts*>(cfg.counts));
@@ -2411,21 +2570,32 @@ __global__ __launch_bounds__(kBlock) void k_eval_pre(LaunchCfg cfg) {
 // step-rule factor ring for the sequence; the guarded ones inside it
 // (mid = 1, 2, ...) leave the ring alone (it already covers every attempt
 // of the sequence).
-__global__ __launch_bounds__(kBlock) void k_eval_decide(LaunchCfg cfg, int mid) {
-  __shared__ DD s_red[4 * 2 * kEvT];
+// Each of the evaluation's sums gets a wave of the workgroup (wave_partials).
+__global__ __launch_bounds__(kDecBlock) void k_eval_decide(LaunchCfg cfg, int mid) {
+  __shared__ double s_sum[2 * kEvT + 2 * kEvA];
   if (eval_step_skips(cfg, mid, false)) return;
+  auto decide = [&](const LpDev& lp, Ctl* c) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    for (int q = wave; q < 2 * kEvT + 2 * kEvA; q += kDecBlock / 64) {
+      const bool ts = q < 2 * kEvT;
+      const int stride = ts ? lp.ntiles_t : lp.ntiles_a;
+      const DD t = wave_partials(
+          gp((const double*)(ts ? lp.part_t : lp.part_a)) +
+              (size_t)(2 * (ts ? q : q - 2 * kEvT)) * stride,
+          stride, ts ? lp.nslot_t : lp.nslot_a);
+      if ((threadIdx.x & 63) == 0) s_sum[q] = dd_value(t);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) decide_eval(c, lp.prm, s_sum, s_sum + 2 * kEvT);
+    __syncthreads();
+  };
   const int nlps = cfg.counts->nlps;
   for (int li = blockIdx.x; li < nlps; li += gridDim.x) {
     const LpDev& lp = cfg.lps[li];
     Ctl* c = lp.ctl;
     if (c->status != kRunning) continue;
     if (mid) {
-      if (!eval_guard(c, 1)) continue;
-      double st[2 * kEvT], sa[2 * kEvA];
-      sum_partials<2 * kEvT>(lp.part_t, lp.ntiles_t, lp.nslot_t, st, s_red);
-      sum_partials<2 * kEvA>(lp.part_a, lp.ntiles_a, lp.nslot_a, sa, s_red);
-      if (threadIdx.x == 0) decide_eval(c, lp.prm, st, sa);
-      __syncthreads();
+      if (eval_guard(c, 1)) decide(lp, c);
       continue;
     }
     // step-rule factors for the attempts j = a0 + 1 .. a0 + kPowRing of this
@@ -2435,7 +2605,7 @@ __global__ __launch_bounds__(kBlock) void k_eval_decide(LaunchCfg cfg, int mid) 
     // its partial sums.
     const int64_t a0 = c->attempts;
     const DevParams* p = lp.prm;
-    for (int t = threadIdx.x; t < kPowRing; t += kBlock) {
+    for (int t = threadIdx.x; t < kPowRing; t += kDecBlock) {
       const int64_t j = a0 + 1 + t;
       if (j <= kPowTab) {
         lp.pow_ring[t] = lp.pow_tab[j - 1];
@@ -2447,12 +2617,7 @@ __global__ __launch_bounds__(kBlock) void k_eval_decide(LaunchCfg cfg, int mid) 
       }
     }
     if (threadIdx.x == 0) c->ring_base = a0;
-    if (!eval_guard(c, 0)) continue;
-    double st[2 * kEvT], sa[2 * kEvA];
-    sum_partials<2 * kEvT>(lp.part_t, lp.ntiles_t, lp.nslot_t, st, s_red);
-    sum_partials<2 * kEvA>(lp.part_a, lp.ntiles_a, lp.nslot_a, sa, s_red);
-    if (threadIdx.x == 0) decide_eval(c, lp.prm, st, sa);
-    __syncthreads();
+    if (eval_guard(c, 0)) decide(lp, c);
   }
 }
 
@@ -2686,10 +2851,10 @@ __global__ __launch_bounds__(kBlock) void k_power_w(PrepCfg a, int round) {
     a.sc[j] = w;
     dd_add_prod(p[0], w, w);
   }
-  block_sum<1>(p, s_red);
+  const DD t = block_total<1, kBlock / 64, false>(p, s_red);
   if (threadIdx.x == 0) {
-    a.scr[2 * blockIdx.x + 0] = p[0].hi;
-    a.scr[2 * blockIdx.x + 1] = p[0].lo;
+    a.scr[2 * blockIdx.x + 0] = t.hi;
+    a.scr[2 * blockIdx.x + 1] = t.lo;
   }
 }
 
@@ -2872,12 +3037,10 @@ __global__ __launch_bounds__(kBlock) void k_prep_vectors(PrepCfg a) {
     static_cast<V*>(a.xa)[j] = (V)x0;
     dd_add_prod(p[1], cj, cj);
   }
-  block_sum<2>(p, s_red);
-  if (threadIdx.x == 0) {
-    a.scr[4 * blockIdx.x + 0] = p[0].hi;
-    a.scr[4 * blockIdx.x + 1] = p[0].lo;
-    a.scr[4 * blockIdx.x + 2] = p[1].hi;
-    a.scr[4 * blockIdx.x + 3] = p[1].lo;
+  const DD t = block_total<2, kBlock / 64, false>(p, s_red);
+  if (threadIdx.x < 2) {
+    a.scr[4 * blockIdx.x + 2 * threadIdx.x + 0] = t.hi;
+    a.scr[4 * blockIdx.x + 2 * threadIdx.x + 1] = t.lo;
   }
 }
 
@@ -2978,7 +3141,9 @@ int Kernels<V>::dual_seg(const LaunchCfg& c, void* stream, int force) {
 template <typename V>
 int Kernels<V>::decide(const LaunchCfg& c, void* stream) {
   constexpr bool kPlainSums = sizeof(V) == 4;  // FP32 step kernels store plain sums
-  OPDHG_LAUNCH(k_decide<kPlainSums>, c.launch_lp, c);
+  hipLaunchKernelGGL(k_decide<kPlainSums>, dim3(c.launch_lp), dim3(kPlainSums ? kBlock : kDecBlock),
+                     0, (hipStream_t)stream, c);
+  return launched();
 }
 template <typename V>
 int Kernels<V>::learn_flush(const LaunchCfg& c, void* stream) {
@@ -3050,7 +3215,9 @@ int Kernels<V>::eval_a(const LaunchCfg& c, void* stream, int mid) {
 }
 template <typename V>
 int Kernels<V>::eval_decide(const LaunchCfg& c, void* stream, int mid) {
-  OPDHG_LAUNCH(k_eval_decide, c.launch_lp, c, mid);
+  hipLaunchKernelGGL(k_eval_decide, dim3(c.launch_lp), dim3(kDecBlock), 0, (hipStream_t)stream, c,
+                     mid);
+  return launched();
 }
 template <typename V>
 int Kernels<V>::apply(const LaunchCfg& c, void* stream, int mid) {

@@ -181,7 +181,8 @@ int upload_slot(uint8_t* base, const SlotLayout& L, Prepared& P, int prec, hipSt
 // OPDHG_ERR_OVER_BUDGET when they need more bytes. With fixed_launch the
 // launch grids in cfg are kept (they must cover the new grids).
 int write_tables(uint8_t* dst, const std::vector<LpDev>& lps,
-                 const std::vector<const Prepared*>& preps, int64_t cap, hipStream_t stream,
+                 const std::vector<const Prepared*>& preps, int prec, int64_t cap,
+                 hipStream_t stream,
                  std::vector<uint8_t>& staging, LaunchCfg* cfg, int64_t* nwt, int64_t* nwa,
                  size_t capacity = 0, bool fixed_launch = false);
 // Bytes of the launch tables of a fixed set (evaluation and step lists,
@@ -195,8 +196,11 @@ void step_tiles(Prepared& P, int64_t cap, int lanes);
 // chunked over at most cap workgroups and padded to grid * chunk items;
 // fills each item's slot / last flags and each LP's slot count.
 // step: the step kernels' tiles (stiles) and slot counts (nslot_st / nslot_sa).
+// chunk_slots: the step kernels store one partial per chunk and LP (FP64)
+// instead of one per tile.
 void side_items(std::vector<LpDev>& lps, const std::vector<const Prepared*>& preps, bool tside,
-                int64_t cap, int* grid, int* chunk, std::vector<WorkItem>& out, bool step = false);
+                int64_t cap, int* grid, int* chunk, std::vector<WorkItem>& out, bool step,
+                bool chunk_slots);
 // Workgroup cap of the sparse-product launches under these parameters.
 int64_t grid_cap(const opdhg_params* p);
 void chunking(int64_t n, int64_t cap, int* grid, int* chunk);

@@ -355,7 +355,7 @@ int ServerImpl::admit(Job& j) {
   LaunchCfg own{};
   std::vector<uint8_t> staging;
   int64_t nwt = 0, nwa = 0;
-  if ((rc = write_tables(base + align256(j.L.total), {j.lpd}, {&j.P}, wg_cap, s_h2d, staging,
+  if ((rc = write_tables(base + align256(j.L.total), {j.lpd}, {&j.P}, cfg.precision, wg_cap, s_h2d, staging,
                          &own, &nwt, &nwa)))
     return rc;
   rc = cfg.precision == OPDHG_FP32 ? Kernels<float>::init_products(own, s_h2d)
@@ -379,13 +379,11 @@ int ServerImpl::write_shared() {
   }
   std::vector<WorkItem> wt, wa;
   int gt = 1, ct = 1, ga = 1, ca = 1;
-  side_items(lps, preps, true, wg_cap, &gt, &ct, wt);
-  side_items(lps, preps, false, wg_cap, &ga, &ca, wa);
-  // the step kernels run the evaluation lists, one partial slot per tile
-  for (size_t i = 0; i < lps.size(); ++i) {
-    lps[i].nslot_st = (int32_t)preps[i]->tiles_t.size();
-    lps[i].nslot_sa = (int32_t)preps[i]->tiles_a.size();
-  }
+  // the step kernels run the evaluation lists: one partial slot per tile
+  // (FP32) or per chunk touching the LP (FP64)
+  const bool chunk_slots = cfg.precision == OPDHG_FP64;
+  side_items(lps, preps, true, wg_cap, &gt, &ct, wt, false, chunk_slots);
+  side_items(lps, preps, false, wg_cap, &ga, &ca, wa, false, chunk_slots);
   if ((int64_t)wt.size() > tab.cap_wt || (int64_t)wa.size() > tab.cap_wa ||
       (int64_t)lps.size() > tab.cap_lps)
     return fail(OPDHG_ERR_OVER_BUDGET, "launch tables overflow");
