@@ -90,7 +90,10 @@ extern "C" {
 
 /* ---- windowed sparse products (FP32) ---- */
 #define OPDHG_WINDOWS_AUTO 0   /* a side whose rows give at least 128 windowed chunks uses them */
-#define OPDHG_WINDOWS_OFF 1    /* every row in tiles that gather from global memory */
+#define OPDHG_WINDOWS_OFF 1    /* every row in tiles that gather from global memory; a small FP64
+                                  LP too, whose attempts otherwise run in one workgroup (same
+                                  results; without room for its packed entries in the workspace it
+                                  runs in tiles as well) */
 #define OPDHG_WINDOWS_ALWAYS 2 /* every windowable chunk, however few (small LPs, checks) */
 
 /* ---- where the rescaling and the scaled data are computed ---- */
@@ -154,7 +157,7 @@ typedef struct opdhg_params {
   double step_scale;     /* constant step: eta = step_scale / estimate of |A~|_2 (> 0) */
   double power_tol;      /* power iteration stops when |A~|_2^2 moves less than this, relatively */
   int32_t step_norm;     /* OPDHG_STEP_NORM_*: norms of the adaptive rule's movement term */
-  int32_t windows;       /* OPDHG_WINDOWS_*: FP32 only; FP64 and the server never use windows */
+  int32_t windows;       /* OPDHG_WINDOWS_*: windows are FP32 only; the server never uses them */
   int32_t window_buckets; /* LDS window per pass in buckets of 1024 entries, 1..28, for chunks
                              of one pass and of several alike; 0: 28 per pass, and up to 38 for a
                              chunk of one pass (its row sums then reuse the window's LDS) */

@@ -83,6 +83,7 @@ int prepare_set(int count, const opdhg_lp* lps, const opdhg_params* p, std::vect
     for (int i = next++; i < count; i = next++) {
       int rc = validate_lp(&lps[i]);
       if (!rc) rc = prepare(&lps[i], &q, P[i], false);
+      P[i].one = false;  // the candidates are tilings of the step kernels
       if (rc) {
         rcs[i] = rc;
         msgs[i] = opdhg_last_error();
@@ -178,6 +179,7 @@ int opdhg_autotune_workspace_bytes(int count, const opdhg_lp* lps, const opdhg_p
   for (int i = 0; i < count; ++i) {
     if ((rc = validate_lp(&lps[i]))) return rc;
     prepare(&lps[i], p, P[i], true);
+    P[i].one = false;
   }
   *bytes = max_bytes(P, p->precision);
   if (try_windows(p)) {

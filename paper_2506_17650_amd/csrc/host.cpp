@@ -16,6 +16,7 @@
 #include <mutex>
 #include <numeric>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -1277,6 +1278,35 @@ static int prepare_finish(const opdhg_lp* lp, const opdhg_params* p, Prepared& o
   return OPDHG_OK;
 }
 
+// Whether an LP is small enough for k_one (see kOneCost), and the threads it
+// takes there: a wave per slice of 64 lane rows (per four medium rows, per
+// long row) of the larger side, 4 to 16.
+static void plan_one(const opdhg_params* p, Prepared& P) {
+  P.one = false;
+  if (p->precision != OPDHG_FP64 || p->windows == OPDHG_WINDOWS_OFF || 2 * P.m + P.n > kOneVec)
+    return;
+  int64_t units = 4, cost = 0, longest = 0;
+  auto side = [&](const std::vector<int32_t>& rp, const int64_t* cend, int64_t rows) {
+    int64_t n = 0;
+    auto group = [&](int64_t r0, int64_t r1, int64_t lanes, int64_t round, int64_t more) {
+      int64_t len = 0;
+      for (int64_t r = r0; r < r1; ++r) len = std::max<int64_t>(len, rp[r + 1] - rp[r]);
+      longest = std::max(longest, len);
+      const int64_t each = (len + lanes - 1) / lanes;
+      cost += (each + round - 1) / round * round + more;
+      ++n;
+    };
+    for (int64_t r = 0; r < cend[0]; ++r) group(r, r + 1, 64, 4, 12);
+    for (int64_t r = cend[0]; r < cend[1]; r += 4) group(r, std::min(r + 4, cend[1]), 16, 4, 12);
+    for (int64_t r = cend[1]; r < rows; r += 64) group(r, std::min(r + 64, rows), 1, 8, 8);
+    units = std::max(units, n);
+  };
+  side(P.rp_a, P.cend_a, P.m);
+  side(P.rp_t, P.cend_t, P.n);
+  P.one = cost <= kOneCost && longest <= kOneLongest;
+  P.one_threads = 64 * (int)std::min<int64_t>(units, kOneThreads / 64);
+}
+
 int prepare(const opdhg_lp* lp, const opdhg_params* p, Prepared& out, bool structure_only) {
   out.m = lp->m;
   out.n = lp->n;
@@ -1309,6 +1339,7 @@ int prepare(const opdhg_lp* lp, const opdhg_params* p, Prepared& out, bool struc
   class_order(len_t, out.perm_t, out.cend_t);
   device_row_ptr(len_a, out.perm_a, out.rp_a);
   device_row_ptr(len_t, out.perm_t, out.rp_t);
+  plan_one(p, out);
   const int64_t cap = p->tile_nnz > 0 ? std::min<int64_t>(p->tile_nnz, kTileCap) : kTileCap;
   out.tiles_a = build_tiles(out.rp_a.data(), m, cap, p->lanes);
   out.tiles_t = build_tiles(out.rp_t.data(), n, cap, p->lanes);
@@ -1540,6 +1571,13 @@ SlotLayout slot_layout(const Prepared& P, int prec) {
     L.st_ti = take(4 * nnz);
     L.st_tk = take(4 * nnz);
   }
+  L.base = off;
+  if (P.one) {
+    L.one_col_t = take(2 * nnz);
+    L.one_col_a = take(2 * nnz);
+    L.one_val_t = take(8 * nnz);
+    L.one_val_a = take(8 * nnz);
+  }
   L.total = off;
   return L;
 }
@@ -1618,6 +1656,16 @@ LpDev slot_pointers(uint8_t* base, const SlotLayout& L, const Prepared& P) {
     d.sptr_a = reinterpret_cast<const int32_t*>(base + L.sptr_a);
     d.sids_a = reinterpret_cast<const int32_t*>(base + L.sids_a);
   }
+  if (P.one) {
+    d.one_col_t = reinterpret_cast<uint16_t*>(base + L.one_col_t);
+    d.one_col_a = reinterpret_cast<uint16_t*>(base + L.one_col_a);
+    d.one_val_t = reinterpret_cast<double*>(base + L.one_val_t);
+    d.one_val_a = reinterpret_cast<double*>(base + L.one_val_a);
+    d.one_long_t = (int32_t)P.cend_t[0];
+    d.one_med_t = (int32_t)P.cend_t[1];
+    d.one_long_a = (int32_t)P.cend_a[0];
+    d.one_med_a = (int32_t)P.cend_a[1];
+  }
   return d;
 }
 
@@ -1648,11 +1696,11 @@ Ctl initial_ctl(const Prepared& P) {
 }
 
 // Byte ranges of a slot that the host image fills and uploads: the whole
-// slot, or with the device-side structure everything but the CSR copies
+// slot (but the packed entries of a small LP), or with the device-side structure everything but the CSR copies
 // and their values (built on the device) and the staging of the caller's
 // arrays (uploaded from them directly).
 static std::vector<std::pair<size_t, size_t>> image_ranges(const SlotLayout& L, const Prepared& P) {
-  if (!P.dstruct) return {{0, L.total}};
+  if (!P.dstruct) return {{0, L.base}};
   return {{0, L.ci_a}, {L.rp_t, L.ci_t}, {L.vn[0], L.raw_a}, {L.raw_b, L.st_rp}};
 }
 
@@ -1777,6 +1825,18 @@ int Group::enqueue(hipStream_t s, int attempts) {
       rc |= Kernels<V>::apply(cfg, s, mid);
     };
     evaluation(0);
+    if (cfg.one_threads > 0) {
+      // small LPs: one launch runs attempts until an evaluation falls due or
+      // the sequence's attempts are done; an LP that began the sequence off
+      // its evaluation points (after a rejected attempt) meets one inside it
+      rc |= Kernels<V>::one(cfg, s, attempts);
+      if (mid_every > 0) {
+        evaluation(1);
+        rc |= Kernels<V>::one(cfg, s, attempts);
+      }
+      rc |= launch_board(cfg, s);
+      return;
+    }
     for (int a = 0, b = 0; a < attempts; ++a) {
       if (a > 0 && mid_every > 0 && a % mid_every == 0) evaluation(++b);
       rc |= launch_side(true, 0, s);
@@ -1864,18 +1924,14 @@ int Group::init(void* stream_, int prec_, bool direct_) {
   stream = (hipStream_t)stream_;
   prec = prec_;
   direct = direct_;
-  if (direct) {
-    // outside any capture: the windowed kernels' LDS attribute (no allocation)
-    if (prec == OPDHG_FP32 && window_kernels_ready())
-      return fail(OPDHG_ERR_DEVICE, device_error_string());
-    return OPDHG_OK;
-  }
+  // outside any capture: the LDS attribute of the windowed kernels and of
+  // k_one (no allocation)
+  if (prec == OPDHG_FP32 ? window_kernels_ready() : one_kernel_ready())
+    return fail(OPDHG_ERR_DEVICE, device_error_string());
+  if (direct) return OPDHG_OK;
   HIP_TRY(hipStreamCreateWithFlags(&side_stream, hipStreamNonBlocking));
   HIP_TRY(hipEventCreateWithFlags(&ev_fork, hipEventDisableTiming));
   HIP_TRY(hipEventCreateWithFlags(&ev_join, hipEventDisableTiming));
-  // outside any capture: the windowed kernels' LDS attribute
-  if (prec == OPDHG_FP32 && window_kernels_ready())
-    return fail(OPDHG_ERR_DEVICE, device_error_string());
   HIP_TRY(hipStreamCreateWithFlags(&cap_stream, hipStreamNonBlocking));
   return OPDHG_OK;
 }
@@ -2230,6 +2286,18 @@ int write_tables(uint8_t* dst, const std::vector<LpDev>& lps_in,
     cfg->launch_ta = std::max(cfg->grid_t, cfg->grid_a);
     cfg->launch_lp = (int)std::max<size_t>(1, std::min<size_t>(lps.size(), kGridCap));
   }
+  // a set that never changes, of small LPs only: one workgroup per LP runs
+  // the attempts
+  cfg->one_lps = cfg->one_threads = 0;
+  cfg->one_lds = 0;
+  if (!fixed_launch && !lps.empty() &&
+      std::all_of(preps.begin(), preps.end(), [](const Prepared* P) { return P->one; })) {
+    cfg->one_lps = (int)lps.size();
+    for (const Prepared* P : preps) {
+      cfg->one_threads = std::max(cfg->one_threads, P->one_threads);
+      cfg->one_lds = std::max(cfg->one_lds, one_lds_bytes(P->m, P->n));
+    }
+  }
   // one LP in a set that never changes: the decision record as uploaded
   cfg->solo = !fixed_launch && lps.size() == 1 ? 1 : 0;
   cfg->solo_rec = DecideRec{};
@@ -2362,7 +2430,12 @@ int upload_slot(uint8_t* base, const SlotLayout& L, Prepared& P, int prec, hipSt
     int rc = device_structure(base, L, P, stream);
     if (rc) return rc;
   }
-  if (P.dprep) return device_prepare(base, L, P, prec, stream);
+  if (P.dprep) {
+    int rc = device_prepare(base, L, P, prec, stream);
+    if (rc) return rc;
+  }
+  if (P.one && one_pack(slot_pointers(base, L, P), stream))
+    return fail(OPDHG_ERR_DEVICE, device_error_string());
   return OPDHG_OK;
 }
 
@@ -2501,7 +2574,10 @@ static int read_vectors(SessionImpl& S, const std::array<ReadVec, 4>& vecs) {
   const int nth = (int)std::min<size_t>({(size_t)host_threads(), (size_t)kPinThreads,
                                          std::max<size_t>(1, pieces.size())});
   std::vector<std::thread> pool;
-  for (int t = 1; t < nth; ++t) pool.emplace_back(work, t);
+  try {
+    for (int t = 1; t < nth; ++t) pool.emplace_back(work, t);
+  } catch (const std::system_error&) {  // fewer threads take all the pieces
+  }
   work(0);
   for (auto& th : pool) th.join();
   if (err != (int)hipSuccess) return fail_hip((hipError_t)err.load(), "reading the vectors");
@@ -2710,9 +2786,15 @@ static int session_from_prepared(opdhg_prepared& pr, void* d_workspace, size_t w
   if (!d_workspace) return fail(OPDHG_ERR_INVALID_ARGUMENT, "workspace is NULL");
   const opdhg_params* p = &pr.p;
   const size_t need = pr.need;
-  if (workspace_bytes < need)
-    return fail(OPDHG_ERR_WORKSPACE_TOO_SMALL,
-                "workspace needs " + std::to_string(need) + " bytes");
+  if (workspace_bytes < need) {
+    // a small LP also solves, more slowly, without its packed entries
+    const size_t packed = pr.L.total - pr.L.base;
+    if (workspace_bytes < need - packed)
+      return fail(OPDHG_ERR_WORKSPACE_TOO_SMALL,
+                  "workspace needs " + std::to_string(need) + " bytes");
+    pr.P.one = false;
+    pr.L = slot_layout(pr.P, p->precision);
+  }
   int rc = OPDHG_OK;
   auto s = std::make_unique<opdhg_session>();
   SessionImpl& S = s->impl;
@@ -3073,11 +3155,23 @@ static int batch_solve(opdhg_batch& B, void* d_workspace, size_t workspace_bytes
   std::vector<Prepared>& P = B.P;
   std::vector<SlotLayout>& L = B.L;
   std::vector<size_t>& offs = B.offs;
-  const size_t off = B.off;
+  size_t off = B.off;
   std::vector<std::string> msgs(count);
   const size_t need = B.need;
-  if (workspace_bytes < need)
-    return fail(OPDHG_ERR_WORKSPACE_TOO_SMALL, "workspace needs " + std::to_string(need) + " bytes");
+  if (workspace_bytes < need) {
+    // small LPs also solve, more slowly, without their packed entries
+    size_t packed = 0;
+    for (int i = 0; i < count; ++i) packed += L[i].total - L[i].base;
+    if (workspace_bytes < need - packed)
+      return fail(OPDHG_ERR_WORKSPACE_TOO_SMALL, "workspace needs " + std::to_string(need) + " bytes");
+    off = 0;
+    for (int i = 0; i < count; ++i) {
+      P[i].one = false;
+      L[i] = slot_layout(P[i], p->precision);
+      offs[i] = off;
+      off += L[i].total;
+    }
+  }
   uint8_t* ws = static_cast<uint8_t*>(d_workspace);
   Group grp;
   if ((rc = grp.init(hip_stream, p->precision))) return rc;

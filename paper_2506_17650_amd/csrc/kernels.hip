@@ -1074,8 +1074,8 @@ struct CtlView {
   }
 };
 
-__device__ __forceinline__ CtlView ctl_view(const Ctl* c) {
-  const gptr<const Ctl> g = gp(c);
+template <typename P>
+__device__ __forceinline__ CtlView ctl_view_at(P g) {
   CtlView v;
   v.eta = uni(g->eta);
   v.omega = uni(g->omega);
@@ -1095,6 +1095,7 @@ __device__ __forceinline__ CtlView ctl_view(const Ctl* c) {
   v.weighted_step = uni(g->weighted_step);
   return v;
 }
+__device__ __forceinline__ CtlView ctl_view(const Ctl* c) { return ctl_view_at(gp(c)); }
 
 // The same work item in every thread, moved to scalar registers: the
 // compiler then branches on its fields and divides by its lane count with
@@ -1342,6 +1343,39 @@ struct PrimalPre {
   V c, x, T, l, u, xs, H, G;
 };
 
+// What a step reads from the LP's record, in scalar registers.
+struct PrimalPtrs {
+  const void *c, *l, *u, *y0, *y1, *va;
+  void *T, *H, *G, *x0, *x1, *s0, *s1, *seg;
+  const int32_t *rp, *ci;
+  const DevParams* prm;
+  double* part;
+  int stride;
+  int32_t flags;
+  __device__ __forceinline__ explicit PrimalPtrs(gptr<const LpDev> L) {
+    c = uni(L->c);
+    l = uni(L->l);
+    u = uni(L->u);
+    T = uni(L->T);
+    H = uni(L->Hp);
+    G = uni(L->Gp);
+    x0 = uni(L->x[0]);
+    x1 = uni(L->x[1]);
+    s0 = uni(L->xs[0]);
+    s1 = uni(L->xs[1]);
+    y0 = uni((const void*)L->y[0]);
+    y1 = uni((const void*)L->y[1]);
+    rp = uni(L->rp_t);
+    ci = uni(L->ci_t);
+    va = uni(L->va_t);
+    prm = uni(L->prm);
+    part = uni(L->part_t);
+    stride = uni(L->ntiles_t);
+    seg = uni(L->segp_t);
+    flags = uni(L->s_flags);
+  }
+};
+
 // Context of the primal step for one LP (A^T y, eq. (6)'s primal update and
 // projection, the running sum, the primal online gradient of eq. (7) and
 // the deferred learner update of T), loaded once per LP by begin(). Every
@@ -1380,27 +1414,7 @@ struct PrimalStep {
     // The LP's record and its control block do not depend on each other:
     // both are read before the first wait.
     const CtlView v = ctl_view(ctl);
-    const gptr<const LpDev> L = gp(lp);
-    const void* const pc = uni(L->c);
-    const void* const pl = uni(L->l);
-    const void* const pu = uni(L->u);
-    void* const pT = uni(L->T);
-    void* const pH = uni(L->Hp);
-    void* const pG = uni(L->Gp);
-    void* const px0 = uni(L->x[0]);
-    void* const px1 = uni(L->x[1]);
-    void* const ps0 = uni(L->xs[0]);
-    void* const ps1 = uni(L->xs[1]);
-    const void* const py0 = uni(L->y[0]);
-    const void* const py1 = uni(L->y[1]);
-    const int32_t* const prp = uni(L->rp_t);
-    const int32_t* const pci = uni(L->ci_t);
-    const void* const pva = uni(L->va_t);
-    const DevParams* const pprm = uni(L->prm);
-    double* const ppart = uni(L->part_t);
-    const int pstride = uni(L->ntiles_t);
-    void* const pseg = uni(L->segp_t);
-    const int32_t pflags = uni(L->s_flags);
+    const PrimalPtrs ptr(gp(lp));
     // the restart / final copy of the evaluation step ran before this
     // launch; the workgroup with the LP's first item clears the flags
     if (first && threadIdx.x == 0 && (v.restart_pending | v.finalize_avg)) {
@@ -1408,11 +1422,17 @@ struct PrimalStep {
       c->finalize_avg = 0;
     }
     if (!uni((int)(force || v.attempt()))) return false;
+    arm(ptr, v, force);
+    return true;
+  }
+
+  // The context of an attempt of the LP.
+  __device__ __forceinline__ void arm(const PrimalPtrs& ptr, const CtlView& v, int force) {
     const int cur = uni(v.cur);
     const double eta = uni(v.eta), om = uni(v.omega);
     tau = (V)(eta / om);
     etav = (V)eta;
-    prm = uni(pprm);
+    prm = uni(ptr.prm);
     // a forced (timing) launch writes only the candidate buffers
     learn = uni((int)(!force && v.learn_now != 0)) != 0;
     wstep = uni(v.weighted_step) != 0;
@@ -1421,29 +1441,28 @@ struct PrimalStep {
                     learn_side(v.learn_pending, v.g2, prm, &lscale))) != 0;
     lscale = uni(lscale);
     hnorm = uni(v.hp_norm);
-    cc = uni(gp(static_cast<const V*>(pc)));
-    lo = uni(gp(static_cast<const V*>(pl)));
-    hi = uni(gp(static_cast<const V*>(pu)));
-    T = uni(gp(static_cast<V*>(pT)));
-    Hp = uni(gp(static_cast<V*>(pH)));
-    Gp = uni(gp(static_cast<V*>(pG)));
-    x = uni(gp(static_cast<const V*>(cur ? px1 : px0)));
-    xs = uni(gp(static_cast<const V*>(cur ? ps1 : ps0)));
-    xn = uni(gp(static_cast<V*>(cur ? px0 : px1)));
-    xsn = uni(gp(static_cast<V*>(cur ? ps0 : ps1)));
-    vecs[0] = uni(gp(static_cast<const V*>(cur ? py1 : py0)));
+    cc = uni(gp(static_cast<const V*>(ptr.c)));
+    lo = uni(gp(static_cast<const V*>(ptr.l)));
+    hi = uni(gp(static_cast<const V*>(ptr.u)));
+    T = uni(gp(static_cast<V*>(ptr.T)));
+    Hp = uni(gp(static_cast<V*>(ptr.H)));
+    Gp = uni(gp(static_cast<V*>(ptr.G)));
+    x = uni(gp(static_cast<const V*>(cur ? ptr.x1 : ptr.x0)));
+    xs = uni(gp(static_cast<const V*>(cur ? ptr.s1 : ptr.s0)));
+    xn = uni(gp(static_cast<V*>(cur ? ptr.x0 : ptr.x1)));
+    xsn = uni(gp(static_cast<V*>(cur ? ptr.s0 : ptr.s1)));
+    vecs[0] = uni(gp(static_cast<const V*>(cur ? ptr.y1 : ptr.y0)));
     Hsrc = upd ? Hp : x;
     Gsrc = upd ? Gp : x;
-    rp = uni(gp(prp));
-    ci = uni(gp(pci));
-    va = uni(gp(static_cast<const V*>(pva)));
-    part_ = uni(ppart);
-    stride_ = uni(pstride);
-    segp_ = uni(pseg);
-    lzero = (pflags & kLowerZero) != 0;
-    noup = (pflags & kNoUpper) != 0;
+    rp = uni(gp(ptr.rp));
+    ci = uni(gp(ptr.ci));
+    va = uni(gp(static_cast<const V*>(ptr.va)));
+    part_ = uni(ptr.part);
+    stride_ = uni(ptr.stride);
+    segp_ = uni(ptr.seg);
+    lzero = (ptr.flags & kLowerZero) != 0;
+    noup = (ptr.flags & kNoUpper) != 0;
     tau = uni(tau), etav = uni(etav);
-    return true;
   }
 
   __device__ __forceinline__ PrimalPre<V> load(int j) const {
@@ -1523,6 +1542,39 @@ struct DualPre {
   int8_t ineq;
 };
 
+// As PrimalPtrs.
+struct DualPtrs {
+  const void *b, *x0, *x1, *va;
+  void *S, *H, *G, *y0, *y1, *s0, *s1, *a0, *a1, *seg;
+  const int8_t* sense;
+  const int32_t *rp, *ci;
+  const DevParams* prm;
+  double* part;
+  int stride;
+  __device__ __forceinline__ explicit DualPtrs(gptr<const LpDev> L) {
+    b = uni((const void*)L->b);
+    S = uni(L->S);
+    H = uni(L->Hd);
+    G = uni(L->Gd);
+    y0 = uni(L->y[0]);
+    y1 = uni(L->y[1]);
+    s0 = uni(L->ys[0]);
+    s1 = uni(L->ys[1]);
+    a0 = uni(L->Ax[0]);
+    a1 = uni(L->Ax[1]);
+    x0 = uni((const void*)L->x[0]);
+    x1 = uni((const void*)L->x[1]);
+    sense = uni(L->sense);
+    rp = uni(L->rp_a);
+    ci = uni(L->ci_a);
+    va = uni(L->va_a);
+    prm = uni(L->prm);
+    part = uni(L->part_a);
+    stride = uni(L->ntiles_a);
+    seg = uni(L->segp_a);
+  }
+};
+
 // Context of the dual step for one LP (A x', the extrapolation, eq. (6)'s
 // dual update and sign projection, the running sum, the dual online
 // gradient of eq. (7) and the deferred learner update of Sigma).
@@ -1553,33 +1605,18 @@ struct DualStep {
     // as in PrimalStep: the LP's record and its control block are read
     // together, and uniform values live in scalar registers
     const CtlView v = ctl_view(ctl);
-    const gptr<const LpDev> L = gp(lp);
-    const void* const pb = uni(L->b);
-    void* const pS = uni(L->S);
-    void* const pH = uni(L->Hd);
-    void* const pG = uni(L->Gd);
-    void* const py0 = uni(L->y[0]);
-    void* const py1 = uni(L->y[1]);
-    void* const ps0 = uni(L->ys[0]);
-    void* const ps1 = uni(L->ys[1]);
-    void* const pa0 = uni(L->Ax[0]);
-    void* const pa1 = uni(L->Ax[1]);
-    const void* const px0 = uni(L->x[0]);
-    const void* const px1 = uni(L->x[1]);
-    const int8_t* const psense = uni(L->sense);
-    const int32_t* const prp = uni(L->rp_a);
-    const int32_t* const pci = uni(L->ci_a);
-    const void* const pva = uni(L->va_a);
-    const DevParams* const pprm = uni(L->prm);
-    double* const ppart = uni(L->part_a);
-    const int pstride = uni(L->ntiles_a);
-    void* const pseg = uni(L->segp_a);
+    const DualPtrs ptr(gp(lp));
     if (!uni((int)(force || v.attempt()))) return false;
+    arm(ptr, v, force);
+    return true;
+  }
+
+  __device__ __forceinline__ void arm(const DualPtrs& ptr, const CtlView& v, int force) {
     const int cur = uni(v.cur);
     const double eta = uni(v.eta), om = uni(v.omega);
     sig = (V)(eta * om);
     etav = (V)eta;
-    prm = uni(pprm);
+    prm = uni(ptr.prm);
     learn = uni((int)(!force && v.learn_now != 0)) != 0;
     wstep = uni(v.weighted_step) != 0;
     lscale = 1.0;
@@ -1587,29 +1624,28 @@ struct DualStep {
                     learn_side(v.learn_pending, v.r2, prm, &lscale))) != 0;
     lscale = uni(lscale);
     hnorm = uni(v.hd_norm);
-    b = uni(gp(static_cast<const V*>(pb)));
-    S = uni(gp(static_cast<V*>(pS)));
-    Hd = uni(gp(static_cast<V*>(pH)));
-    Gd = uni(gp(static_cast<V*>(pG)));
-    y = uni(gp(static_cast<const V*>(cur ? py1 : py0)));
-    ys = uni(gp(static_cast<const V*>(cur ? ps1 : ps0)));
-    Ax = uni(gp(static_cast<const V*>(cur ? pa1 : pa0)));
-    yn = uni(gp(static_cast<V*>(cur ? py0 : py1)));
-    ysn = uni(gp(static_cast<V*>(cur ? ps0 : ps1)));
-    Axn = uni(gp(static_cast<V*>(cur ? pa0 : pa1)));
+    b = uni(gp(static_cast<const V*>(ptr.b)));
+    S = uni(gp(static_cast<V*>(ptr.S)));
+    Hd = uni(gp(static_cast<V*>(ptr.H)));
+    Gd = uni(gp(static_cast<V*>(ptr.G)));
+    y = uni(gp(static_cast<const V*>(cur ? ptr.y1 : ptr.y0)));
+    ys = uni(gp(static_cast<const V*>(cur ? ptr.s1 : ptr.s0)));
+    Ax = uni(gp(static_cast<const V*>(cur ? ptr.a1 : ptr.a0)));
+    yn = uni(gp(static_cast<V*>(cur ? ptr.y0 : ptr.y1)));
+    ysn = uni(gp(static_cast<V*>(cur ? ptr.s0 : ptr.s1)));
+    Axn = uni(gp(static_cast<V*>(cur ? ptr.a0 : ptr.a1)));
     // x' was written by this attempt's primal step into the other buffer
-    vecs[0] = uni(gp(static_cast<const V*>(cur ? px0 : px1)));
-    sense = uni(gp(psense));
+    vecs[0] = uni(gp(static_cast<const V*>(cur ? ptr.x0 : ptr.x1)));
+    sense = uni(gp(ptr.sense));
     Hsrc = upd ? Hd : y;
     Gsrc = upd ? Gd : y;
-    rp = uni(gp(prp));
-    ci = uni(gp(pci));
-    va = uni(gp(static_cast<const V*>(pva)));
-    part_ = uni(ppart);
-    stride_ = uni(pstride);
-    segp_ = uni(pseg);
+    rp = uni(gp(ptr.rp));
+    ci = uni(gp(ptr.ci));
+    va = uni(gp(static_cast<const V*>(ptr.va)));
+    part_ = uni(ptr.part);
+    stride_ = uni(ptr.stride);
+    segp_ = uni(ptr.seg);
     sig = uni(sig), etav = uni(etav);
-    return true;
   }
 
   __device__ __forceinline__ DualPre<V> load(int i) const {
@@ -2288,6 +2324,303 @@ __global__ __launch_bounds__(PLAIN ? kBlock : kDecBlock)
     if (li < nlps) {
       __syncthreads();  // s_red is reused by the next LP
       d = decide_lp(&cfg.lps[li]);
+    }
+  }
+}
+
+// ---- small FP64 LPs: the attempts of a launch sequence in one workgroup ----
+//
+// On a small LP an attempt's three launches are all latency: a launch and
+// drain each, the work item, the record and control block, the tile's loads,
+// the gathers, and the partial sums' way through memory (16 us per attempt
+// on 200 x 500, 19 on 1203 x 2411). Here one workgroup per LP keeps the
+// control block, y and x' in LDS and runs attempt after attempt until an
+// evaluation falls due or the sequence's attempts are done; what is left
+// per attempt is one round of loads a side (entries and row vectors
+// together, nothing depends on another load), the LDS gathers, and the
+// decision. Rows of up to 32 entries take a lane each, so their entries'
+// loads are contiguous over the wave (see kOneThreads); medium rows take 16
+// lanes, long ones a wave. Every sum is a double-double as in the step
+// kernels, so the results are theirs bit for bit. Bound by the latency of
+// those rounds on the smallest LPs (6.5 us per attempt on 60 x 150, the
+// evaluations' share of 0.9 included, against 13.9 for the step kernels) and
+// by one CU's FP64 arithmetic on the larger ones (see kOneCost): 7.4 us
+// against 15.2 on 200 x 500, 10.0 against 15.6 on 500 x 1000.
+
+// The side's rows: finish(row, sum, pre) per row, in the first lane of its
+// group, with pre = load(row). rows = number of rows, e_long and e_med the
+// ends of the long and medium classes (the first rows in device order); vec
+// is the gathered vector, cnt and base the lane rows' entry counts and their
+// slices' offsets, all three in LDS.
+template <typename Pre, typename Load, typename Finish>
+__device__ __forceinline__ void one_side(int rows, int e_long, int e_med, gptr<const int32_t> rp,
+                                         gptr<const uint16_t> col, gptr<const double> val,
+                                         const double* vec, const uint8_t* cnt, const int32_t* base,
+                                         Load&& load, Finish&& finish) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int nw = __builtin_amdgcn_readfirstlane((int)blockDim.x >> 6);
+  const int nlane = rows - e_med, nsl = (nlane + 63) >> 6;
+  for (int s = wave; s < nsl; s += nw) {
+    const int i = s * 64 + lane;
+    const bool on = i < nlane;
+    const int r = e_med + (on ? i : nlane - 1);
+    const Pre q0 = load(r);
+    const int len = on ? cnt[i] : 0;
+    int at = __builtin_amdgcn_readfirstlane(base[s]);
+    Acc<double> acc;
+    acc.zero();
+    constexpr int U = 8;
+    for (int k = 0; __ballot(k < len) != 0; k += U) {
+      double a[U];
+      uint32_t c[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        // entry k + u of the rows that have one: side by side in row order
+        const bool has = k + u < len;
+        const uint64_t who = __ballot(has);
+        const uint32_t p = (uint32_t)at + __builtin_amdgcn_mbcnt_hi(
+                                              (uint32_t)(who >> 32),
+                                              __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0));
+        at += __builtin_popcountll(who);
+        a[u] = 0.0;
+        c[u] = 0;
+        if (has) {
+          a[u] = ldg(val, p);
+          c[u] = ldg(col, p);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        acc.add(Num<double>::mask(k + u < len, Num<double>::mul(a[u], vec[c[u]])));
+    }
+    Pre q = q0;
+    if (on) finish(r, acc.value(), q);
+  }
+  // rows of several lanes: LG lanes each, 64 / LG rows of a wave at a time
+  auto groups = [&](int r0, int r1, auto lg) {
+    constexpr int LG = decltype(lg)::value;
+    constexpr int per = 64 / LG;
+    const int sub = lane & (LG - 1);
+    for (int g = r0 + wave * per; g < r1; g += nw * per) {
+      const int r_ = g + lane / LG;
+      const bool on = r_ < r1;
+      const int r = on ? r_ : r1 - 1;
+      const Pre q0 = load(r);
+      const int e0 = ldg(rp, (uint32_t)r), e1 = ldg(rp, (uint32_t)r + 1u);
+      Acc<double> acc;
+      acc.zero();
+      constexpr int U = 4;
+      for (int k = e0 + sub; __ballot(k < e1) != 0; k += U * LG) {
+        double a[U];
+        uint32_t c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const uint32_t p = (uint32_t)min(k + u * LG, e1 - 1);
+          a[u] = ldg(val, p);
+          c[u] = ldg(col, p);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          acc.add(Num<double>::mask(k + u * LG < e1, Num<double>::mul(a[u], vec[c[u]])));
+      }
+      DD d = acc.v;
+      if constexpr (LG == 64) {
+        const DD one[1] = {d};
+        d = wave_totals<1>(one);
+      } else {
+        static_assert(LG == 16, "a row of 16 lanes");
+        d = dd_merge(d, dd_dpp<0x128>(d));  // row_ror:8
+        d = dd_merge(d, dd_dpp<0x141>(d));  // row_half_mirror
+        d = dd_merge(d, dd_dpp<0x4E>(d));   // quad_perm:[2,3,0,1]
+        d = dd_merge(d, dd_dpp<0xB1>(d));   // quad_perm:[1,0,3,2]
+      }
+      Pre q = q0;
+      if (on && sub == 0) finish(r, dd_value(d), q);
+    }
+  };
+  groups(0, e_long, std::integral_constant<int, 64>{});
+  groups(e_long, e_med, std::integral_constant<int, 16>{});
+}
+
+__global__ __launch_bounds__(kOneThreads) void k_one(LaunchCfg cfg, int attempts) {
+  extern __shared__ double one_lds[];
+  __shared__ Ctl s_ctl;
+  __shared__ DevParams s_prm;
+  __shared__ double s_ring[2 * kPowRing];
+  __shared__ DD s_red[(kOneThreads / 64) * 7];
+  const int t = threadIdx.x, nt = blockDim.x;
+  const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const gptr<const LpDev> L = gp(&cfg.lps[blockIdx.x]);
+  Ctl* const ctl = uni(L->ctl);
+  {
+    const CtlView v = ctl_view(ctl);
+    // the restart / final copy of the evaluation step ran before this launch
+    if (t == 0 && (v.restart_pending | v.finalize_avg)) {
+      ctl->restart_pending = 0;
+      ctl->finalize_avg = 0;
+    }
+    if (!uni((int)v.attempt())) return;
+  }
+  const PrimalPtrs pp(L);
+  const DualPtrs dp(L);
+  const int m = uni(L->m), n = uni(L->n);
+  const int long_t = uni(L->one_long_t), med_t = uni(L->one_med_t);
+  const int long_a = uni(L->one_long_a), med_a = uni(L->one_med_a);
+  const gptr<const uint16_t> col_t = uni(gp((const uint16_t*)L->one_col_t));
+  const gptr<const uint16_t> col_a = uni(gp((const uint16_t*)L->one_col_a));
+  const gptr<const double> val_t = uni(gp((const double*)L->one_val_t));
+  const gptr<const double> val_a = uni(gp((const double*)L->one_val_a));
+  StepIn in;
+  in.lr = uni(L->s_lr);
+  in.max_iter = uni(L->s_max_iter);
+  in.phi = uni(L->s_phi);
+  in.schedule = uni(L->s_schedule);
+  in.normalize = uni(L->s_normalize);
+  in.eval_every = uni(L->s_eval_every);
+  in.max_retries = uni(L->s_max_retries);
+  in.flags = uni(L->s_flags);
+  const double* const ring = uni((const double*)L->pow_ring);
+  // the LP's LDS: y (both copies), x', then the slices' offsets and the lane
+  // rows' entry counts of both sides
+  double* const yb = one_lds;
+  double* const xb = one_lds + 2 * m;
+  int32_t* const base_t = reinterpret_cast<int32_t*>(xb + n);
+  int32_t* const base_a = base_t + ((n - med_t + 63) >> 6);
+  uint8_t* const cnt_t = reinterpret_cast<uint8_t*>(base_a + ((m - med_a + 63) >> 6));
+  uint8_t* const cnt_a = cnt_t + (n - med_t);
+  {
+    const gptr<const uint64_t> src = gp(reinterpret_cast<const uint64_t*>(ctl));
+    for (int w = t; w < (int)(sizeof(Ctl) / 8); w += nt)
+      reinterpret_cast<uint64_t*>(&s_ctl)[w] = src[w];
+    static_assert(sizeof(DevParams) % 8 == 0, "copied as 64-bit words");
+    const gptr<const uint64_t> sp = gp(reinterpret_cast<const uint64_t*>(pp.prm));
+    for (int w = t; w < (int)(sizeof(DevParams) / 8); w += nt)
+      reinterpret_cast<uint64_t*>(&s_prm)[w] = sp[w];
+    for (int w = t; w < 2 * kPowRing; w += nt) s_ring[w] = gp(ring)[w];
+    const int cur = uni(gp(ctl)->cur);
+    const gptr<const double> y = gp(static_cast<const double*>(cur ? pp.y1 : pp.y0));
+    for (int i = t; i < m; i += nt) yb[cur * m + i] = y[i];
+    auto lengths = [&](const int32_t* rp_, int rows, int med, uint8_t* cnt, int32_t* base) {
+      const gptr<const int32_t> rp = gp(rp_);
+      for (int i = t; i < rows - med; i += nt) {
+        const int e0 = rp[med + i];
+        cnt[i] = (uint8_t)(rp[med + i + 1] - e0);
+        if ((i & 63) == 0) base[i >> 6] = e0;
+      }
+    };
+    lengths(pp.rp, n, med_t, cnt_t, base_t);
+    lengths(dp.rp, m, med_a, cnt_a, base_a);
+  }
+  __syncthreads();
+  if (t == 0) {
+    s_ctl.restart_pending = 0;
+    s_ctl.finalize_avg = 0;
+  }
+  PrimalStep<double> ps;
+  DualStep<double> ds;
+  for (;;) {
+    const CtlView v = ctl_view_at(&s_ctl);
+    if (!uni((int)(v.attempt() && s_ctl.attempts - s_ctl.ring_base < attempts))) break;
+    const int cur = uni(v.cur);
+    DD p[3], d[4];
+    dd_reset(p);
+    dd_reset(d);
+    ps.arm(pp, v, 0);
+    ps.prm = &s_prm;
+    one_side<PrimalPre<double>>(
+        n, long_t, med_t, ps.rp, col_t, val_t, yb + cur * m, cnt_t, base_t,
+        [&](int j) { return ps.load(j); },
+        [&](int j, double s, PrimalPre<double>& q) {
+          ps.finish(j, s, q, p);
+          xb[j] = ps.w_x;
+        });
+    ps.commit();
+    lds_barrier();
+    ds.arm(dp, v, 0);
+    ds.prm = &s_prm;
+    one_side<DualPre<double>>(
+        m, long_a, med_a, ds.rp, col_a, val_a, xb, cnt_a, base_a,
+        [&](int i) { return ds.load(i); },
+        [&](int i, double s, DualPre<double>& q) {
+          ds.finish(i, s, q, d);
+          yb[(cur ^ 1) * m + i] = ds.w_y;
+        });
+    ds.commit();
+    DD all[7] = {p[0], p[1], p[2], d[0], d[1], d[2], d[3]};
+    store_wave_totals<7, false>(all, s_red);
+    lds_barrier();
+    if (wave == 0) {
+      // lane 8 q + w merges quantity q of waves w and w + 8, then the eight
+      const int nw = nt >> 6, q = lane >> 3, w = lane & 7;
+      DD s = q < 7 && w < nw ? s_red[w * 7 + q] : dd_zero();
+      if (q < 7 && w + 8 < nw) s = dd_merge(s, s_red[(w + 8) * 7 + q]);
+      s = dd_merge(s, dd_dpp<0x141>(s));  // row_half_mirror
+      s = dd_merge(s, dd_dpp<0x4E>(s));   // quad_perm:[2,3,0,1]
+      s = dd_merge(s, dd_dpp<0xB1>(s));   // quad_perm:[1,0,3,2]
+      const double total = dd_value(s);
+      double sv[7];
+#pragma unroll
+      for (int k = 0; k < 7; ++k) sv[k] = lane_value(total, 8 * k);
+      if (lane == 0) {
+        in.eta = s_ctl.eta;
+        in.omega = s_ctl.omega;
+        in.w = s_ctl.w;
+        in.hp_norm = s_ctl.hp_norm;
+        in.hd_norm = s_ctl.hd_norm;
+        in.k = s_ctl.k;
+        in.t = s_ctl.t;
+        in.attempts = s_ctl.attempts;
+        in.retries = s_ctl.retries;
+        in.cur = s_ctl.cur;
+        const int64_t r = in.attempts - s_ctl.ring_base;  // in [0, kPowRing) (see attempts)
+        in.f_red = s_ring[r];
+        in.f_gro = s_ring[kPowRing + r];
+        // an evaluation due with attempts left is the guarded one's; due at
+        // the sequence's end it opens the next sequence
+        if (decide_step(s_ctl, in, sv) && r + 1 < attempts) {
+          const gptr<Counts> cn = gp(const_cast<Counts*>(cfg.counts));
+          cn->hint[0] = 1;
+          cn->hint[1] = 1;
+        }
+      }
+    }
+    lds_barrier();
+  }
+  const gptr<uint64_t> dst = gp(reinterpret_cast<uint64_t*>(ctl));
+  for (int w = t; w < (int)(sizeof(Ctl) / 8); w += nt)
+    dst[w] = reinterpret_cast<const uint64_t*>(&s_ctl)[w];
+}
+
+// The packed entries of a side (see kOneThreads): a wave per slice of 64
+// lane rows; the rows before them keep their order.
+__global__ __launch_bounds__(kBlock) void k_one_pack(LpDev lp, int tside) {
+  const int rows = tside ? lp.n : lp.m, med = tside ? lp.one_med_t : lp.one_med_a;
+  const gptr<const int32_t> rp = gp(tside ? lp.rp_t : lp.rp_a);
+  const gptr<const int32_t> ci = gp(tside ? lp.ci_t : lp.ci_a);
+  const gptr<const double> va = gp(static_cast<const double*>(tside ? lp.va_t : lp.va_a));
+  const gptr<uint16_t> col = gp(tside ? lp.one_col_t : lp.one_col_a);
+  const gptr<double> val = gp(tside ? lp.one_val_t : lp.one_val_a);
+  const int t0 = blockIdx.x * kBlock + threadIdx.x, nt = gridDim.x * kBlock;
+  for (int k = t0; k < rp[med]; k += nt) {
+    col[k] = (uint16_t)ci[k];
+    val[k] = va[k];
+  }
+  const int lane = threadIdx.x & 63;
+  for (int s = t0 >> 6; s * 64 < rows - med; s += nt >> 6) {
+    const int r = med + s * 64 + lane;
+    const bool on = r < rows;
+    const int e0 = on ? rp[r] : 0, len = on ? rp[r + 1] - e0 : 0;
+    int at = __builtin_amdgcn_readfirstlane(e0);
+    for (int k = 0; __ballot(k < len) != 0; ++k) {
+      const uint64_t who = __ballot(k < len);
+      const int p = at + (int)__builtin_amdgcn_mbcnt_hi(
+                             (uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0));
+      at += __builtin_popcountll(who);
+      if (k < len) {
+        col[p] = (uint16_t)ci[e0 + k];
+        val[p] = va[e0 + k];
+      }
     }
   }
 }
@@ -3145,6 +3478,39 @@ int Kernels<V>::decide(const LaunchCfg& c, void* stream) {
                      0, (hipStream_t)stream, c);
   return launched();
 }
+int one_kernel_ready() {
+  static std::once_flag once;
+  static hipError_t err = hipSuccess;
+  std::call_once(once, [] {
+    err = hipFuncSetAttribute((const void*)k_one, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)kOneLdsMax);
+  });
+  if (err != hipSuccess) g_last_device_error = err;
+  return err == hipSuccess ? 0 : -1;
+}
+
+template <typename V>
+int Kernels<V>::one(const LaunchCfg& c, void* stream, int attempts) {
+  if constexpr (!std::is_same<V, double>::value) {
+    return -1;  // planned for FP64 only
+  } else {
+    if (one_kernel_ready()) return -1;
+    hipLaunchKernelGGL(k_one, dim3(c.one_lps), dim3(c.one_threads), c.one_lds,
+                       (hipStream_t)stream, c, std::min(attempts, kPowRing));
+    return launched();
+  }
+}
+
+int one_pack(const LpDev& lp, void* stream) {
+  for (int tside = 0; tside < 2; ++tside) {
+    const int rows = tside ? lp.n : lp.m;
+    hipLaunchKernelGGL(k_one_pack, dim3(std::max(1, (rows + kBlock - 1) / kBlock)), dim3(kBlock), 0,
+                       (hipStream_t)stream, lp, tside);
+    if (launched()) return -1;
+  }
+  return 0;
+}
+
 template <typename V>
 int Kernels<V>::learn_flush(const LaunchCfg& c, void* stream) {
   OPDHG_LAUNCH(k_learn_flush<V>, c.launch_ta, c);

@@ -129,6 +129,10 @@ struct Prepared {
   const int32_t* h_ci = nullptr;
   const double* h_val = nullptr;
   std::vector<int32_t> inv_a, inv_t;
+  // a small FP64 LP (see kOneThreads): its attempts can run in k_one, with
+  // this many threads
+  bool one = false;
+  int one_threads = 0;
   // partial slots per side: evaluation tiles, or step tiles plus windowed chunks
   int64_t part_stride_t() const {
     return (int64_t)std::max(tiles_t.size(),
@@ -165,6 +169,9 @@ struct SlotLayout {
   // the orders, the fill cursors and the entries' places
   size_t st_rp = 0, st_perm_a = 0, st_inv_a = 0, st_inv_t = 0, st_cur = 0, st_ci = 0,
          st_val = 0, st_ti = 0, st_tk = 0;
+  // packed entries of a small FP64 LP, after everything else: `base` bytes
+  // hold the slot without them
+  size_t base = 0, one_col_t = 0, one_col_a = 0, one_val_t = 0, one_val_a = 0;
   size_t total = 0;
 };
 

@@ -183,6 +183,27 @@ struct SegItem {
   int32_t s0, s1;
 };
 
+// Small FP64 LPs: one workgroup runs a launch sequence's attempts by itself
+// (k_one), with y and x' in its LDS. Rows of up to 32 entries (the short
+// class) take a lane each; their entries are stored again in slices of 64
+// rows, entry k of every row that has one side by side in row order
+// (one_col, one_val; a slice's place is its place in the CSR arrays).
+// Medium rows take 16 lanes, long ones 64.
+//
+// An LP qualifies by its work in double-double additions of a wavefront (the
+// arithmetic of one CU bounds k_one): per slice its longest row rounded up to
+// 8, plus 8 for the rows' epilogues; per four medium rows or one long one
+// the additions of a lane plus 12. Measured, an attempt takes 5 us + 0.0098
+// a unit, against 15.7 for the step kernels at any of these sizes (64 x 64 to
+// 1500 x 3000): 7.4 us at 256 units (200 x 500), 12.6 at 704 (700 x 1400),
+// 15.6 at 1024. kOneCost leaves a fifth for LPs whose learner runs on every
+// iteration (13.9 against 16.8 at 704). Rows above kOneLongest entries
+// would hold their wave for several rounds of loads.
+constexpr int kOneThreads = 1024;
+constexpr int kOneCost = 768;
+constexpr int kOneLongest = 512;
+constexpr int kOneVec = 8192;  // two copies of y and one of x' in LDS, doubles
+
 // One LP slot as the kernels see it (device pointers into the workspace).
 struct LpDev {
   int32_t m, n;
@@ -266,7 +287,21 @@ struct LpDev {
   float* evp_t0;
   float* evp_t1;
   float* evp_a;
+  // small FP64 LPs (k_one): the packed entries of each side and the ends of
+  // its long and medium row classes
+  uint16_t* one_col_t;
+  uint16_t* one_col_a;
+  double* one_val_t;
+  double* one_val_a;
+  int32_t one_long_t, one_med_t, one_long_a, one_med_a;
 };
+
+// LDS of k_one's dynamic part for an LP: y twice, x', an entry count per
+// lane row and an offset per slice of 64 lane rows.
+constexpr size_t one_lds_bytes(int64_t m, int64_t n) {
+  return 8 * (size_t)(2 * m + n) + 4 * (size_t)((m + 63) / 64 + (n + 63) / 64) + (size_t)(m + n);
+}
+constexpr size_t kOneLdsMax = 9 * kOneVec + 4 * (kOneVec / 64 + 2);  // 2 m + n = kOneVec
 
 // A set of LPs launched together. A work item is one tile of one LP, with
 // the tile's rows and the LP's control block inline so a workgroup reaches
@@ -348,7 +383,12 @@ struct LaunchCfg {
   int nseg_t, nseg_a;
   // a fixed set of one LP: its decision record comes with the launch
   // arguments, so the decision kernel skips reading the LP table
-  int solo, pad2_;
+  int solo;
+  // every LP of the set is small: the attempts run in k_one, a workgroup of
+  // one_threads threads and one_lds bytes of LDS for each of the one_lps LPs
+  // (0: the step kernels run them)
+  int one_lps, one_threads, pad2_;
+  size_t one_lds;
   DecideRec solo_rec;
 };
 
@@ -364,6 +404,9 @@ struct Kernels {
   static int primal_seg(const LaunchCfg& c, void* stream, int force);
   static int dual_seg(const LaunchCfg& c, void* stream, int force = 0);
   static int decide(const LaunchCfg& c, void* stream);
+  // up to `attempts` attempts of the launch sequence for a set of small LPs
+  // (FP64 only)
+  static int one(const LaunchCfg& c, void* stream, int attempts);
   static int learn_flush(const LaunchCfg& c, void* stream);
   // mid: 0 for the evaluation opening a launch sequence, b > 0 for the b-th
   // guarded evaluation step inside it (see Counts::hint)
@@ -456,6 +499,11 @@ struct StructCfg {
   int32_t nmed_t;   // rows of A^T longer than 32 (first in device order)
 };
 int struct_build(const StructCfg& c, void* stream);
+
+// The packed entries of a small FP64 LP (see kOneThreads), from its CSR copies.
+int one_pack(const LpDev& lp, void* stream);
+// Sets k_one's LDS attribute (once per process); 0 on success.
+int one_kernel_ready();
 
 // kind 0: maxima of |a~|, 1: sums of |a~|^e, 2: L2 norms
 int prep_stats(const PrepCfg& c, void* stream, bool tside, int kind, double e);

@@ -463,10 +463,19 @@ void ServerImpl::fallback_loop() {
     }
     opdhg_params p64 = j->p;
     p64.precision = OPDHG_FP64;
+    // small LPs solve in one workgroup where the budget holds their packed
+    // entries too (windows are off for the shared sequence; FP64 results do
+    // not depend on it)
+    p64.windows = OPDHG_WINDOWS_AUTO;
     const opdhg_lp v = lp_view(*j);
     size_t need = 0;
     int rc = opdhg_workspace_bytes(&v, &p64, &need);
     need = align256(need);
+    if (!rc && need > budget) {
+      p64.windows = OPDHG_WINDOWS_OFF;
+      rc = opdhg_workspace_bytes(&v, &p64, &need);
+      need = align256(need);
+    }
     size_t off = 0;
     bool got = false;
     {
