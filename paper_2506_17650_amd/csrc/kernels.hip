@@ -130,6 +130,23 @@ __device__ __forceinline__ gptr<T> gp(T* p) {
   return (gptr<T>)p;
 }
 
+// The same address as constant memory: with a uniform pointer its loads are
+// scalar loads into scalar registers, several words each, where a vector
+// load of a uniform value takes a v_readfirstlane per word behind its wait.
+// Only for what no lane of the launch writes before it is read (launch
+// tables, LP records; control blocks, which a kernel reads before it writes
+// them). With the work items, records and control blocks of the step kernels
+// read this way an attempt takes 20.1 us in FP32 and 26.4 in FP64 on
+// 50k x 100k (23.1 and 29.6 with vector loads and the items staged in LDS
+// behind a barrier), 16.5 in FP64 on 15k x 10k (17.5).
+template <typename T>
+using cptr = __attribute__((address_space(4))) const T*;
+
+template <typename T>
+__device__ __forceinline__ cptr<T> cp(const T* p) {
+  return (cptr<T>)p;
+}
+
 // Element idx of a global array with a 32-bit byte offset: with the base
 // in scalar registers this is one global load with a 32-bit vector offset
 // (a 64-bit address would take two registers per load in flight). Every
@@ -1036,13 +1053,8 @@ __device__ void decide_eval(Ctl* c, const DevParams* p, const double* st, const 
   }
 }
 
-// Work items of a chunk are staged in LDS, kItemWin at a time, so that a
-// tile's start waits on LDS only: a work item loaded through the vector
-// memory path would make the tile's first wait also wait for the previous
-// tile's stores.
+// Tiles of a chunk between two stores of their partial sums.
 constexpr int kItemWin = 32;
-constexpr int kItemWords = sizeof(WorkItem) / 4;
-static_assert(sizeof(WorkItem) % 4 == 0, "work items are copied as 32-bit words");
 
 // A value that is the same in every thread, moved to scalar registers. A
 // pointer loaded once per LP then needs no wait where the tiles use it.
@@ -1074,8 +1086,13 @@ struct CtlView {
   }
 };
 
-template <typename P>
+// SCALAR: the fields arrive in scalar registers (a uniform cptr).
+template <bool SCALAR, typename P>
 __device__ __forceinline__ CtlView ctl_view_at(P g) {
+  const auto uni = [](auto x) {
+    if constexpr (SCALAR) return x;
+    else return opdhg::uni(x);
+  };
   CtlView v;
   v.eta = uni(g->eta);
   v.omega = uni(g->omega);
@@ -1095,28 +1112,13 @@ __device__ __forceinline__ CtlView ctl_view_at(P g) {
   v.weighted_step = uni(g->weighted_step);
   return v;
 }
-__device__ __forceinline__ CtlView ctl_view(const Ctl* c) { return ctl_view_at(gp(c)); }
+__device__ __forceinline__ CtlView ctl_view(const Ctl* c) { return ctl_view_at<true>(cp(c)); }
 
-// The same work item in every thread, moved to scalar registers: the
-// compiler then branches on its fields and divides by its lane count with
-// scalar instructions.
-__device__ __forceinline__ WorkItem uniform_item(const WorkItem& w) {
-  WorkItem u;
-  const uint64_t cp = reinterpret_cast<uint64_t>(w.ctl);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)cp);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(cp >> 32));
-  u.ctl = reinterpret_cast<Ctl*>(((uint64_t)hi << 32) | lo);
-  u.lp = __builtin_amdgcn_readfirstlane(w.lp);
-  u.tile = __builtin_amdgcn_readfirstlane(w.tile);
-  u.rb = __builtin_amdgcn_readfirstlane(w.rb);
-  u.re = __builtin_amdgcn_readfirstlane(w.re);
-  u.s = __builtin_amdgcn_readfirstlane(w.s);
-  u.e = __builtin_amdgcn_readfirstlane(w.e);
-  u.lanes = __builtin_amdgcn_readfirstlane(w.lanes);
-  u.slot = __builtin_amdgcn_readfirstlane(w.slot);
-  u.seg = __builtin_amdgcn_readfirstlane(w.seg);
-  u.first = __builtin_amdgcn_readfirstlane(w.first);
-  return u;
+// A work item in scalar registers: the compiler branches on its fields and
+// divides by its lane count with scalar instructions.
+__device__ __forceinline__ WorkItem load_item(cptr<WorkItem> w) {
+  return WorkItem{w->ctl, w->lp,    w->tile, w->rb,  w->re,   w->s,
+                  w->e,   w->lanes, w->slot, w->seg, w->first};
 }
 
 // A side's chunking as the launch sees it, in scalar registers.
@@ -1125,8 +1127,8 @@ struct SideChunks {
 };
 
 __device__ __forceinline__ SideChunks side_chunks(const Counts* counts, bool tside) {
-  const gptr<const Counts> c = gp(counts);
-  return SideChunks{uni(tside ? c->grid_t : c->grid_a), uni(tside ? c->chunk_t : c->chunk_a)};
+  const cptr<Counts> c = cp(counts);
+  return SideChunks{tside ? c->grid_t : c->grid_a, tside ? c->chunk_t : c->chunk_a};
 }
 
 // Partial sums of the tiles of one window of work items: the four waves'
@@ -1162,7 +1164,7 @@ struct TilePartials {
 template <typename V, int NA, int NV, bool PLAIN, typename Begin, typename Load, typename Finish,
           typename Dest, typename Commit, typename Piece>
 __device__ __forceinline__ void run_chunk_spmv(const WorkItem* __restrict__ work, SideChunks sc,
-                                               WorkItem* s_items, const gptr<const int32_t>& rp,
+                                               const gptr<const int32_t>& rp,
                                                const gptr<const int32_t>& ci,
                                                const gptr<const V>& va, const gptr<const V>* vec,
                                                const double* div, Begin&& begin, Load&& load,
@@ -1208,17 +1210,15 @@ __device__ __forceinline__ void run_chunk_spmv(const WorkItem* __restrict__ work
       sum = dd_zero();
     }
   };
+  // the next tile's item is read while the current tile runs
+  const cptr<WorkItem> items = cp(work) + w0;
+  WorkItem next = load_item(items);
   for (int k0 = 0; k0 < chunk; k0 += kItemWin) {
     const int cnt = min(kItemWin, chunk - k0);
-    {
-      const gptr<const int32_t> src = gp(reinterpret_cast<const int32_t*>(work + w0 + k0));
-      int32_t* dst = reinterpret_cast<int32_t*>(s_items);
-      for (int q = threadIdx.x; q < cnt * kItemWords; q += kBlock) dst[q] = src[q];
-    }
-    lds_barrier();
     int kb = 0, last = 0;  // the current LP's items in the window
     for (int k = 0; k < cnt; ++k) {
-      const WorkItem it = uniform_item(s_items[k]);
+      const WorkItem it = next;
+      next = load_item(items + min(k0 + k + 1, chunk - 1));
       bool on = false;
       if (it.lp >= 0) {
         if (it.lp != lp) {
@@ -1343,45 +1343,42 @@ struct PrimalPre {
   V c, x, T, l, u, xs, H, G;
 };
 
-// What a step reads from the LP's record, in scalar registers.
+// What a step reads from the LP's record, in scalar registers; arm() picks
+// the copies of the iterate from the record once it knows which is current
+// (reading both copies' addresses beside the control block took more scalar
+// registers than there are).
 struct PrimalPtrs {
-  const void *c, *l, *u, *y0, *y1, *va;
-  void *T, *H, *G, *x0, *x1, *s0, *s1, *seg;
+  cptr<LpDev> L;
+  const void *c, *l, *u, *va;
+  void *T, *H, *G, *seg;
   const int32_t *rp, *ci;
   const DevParams* prm;
   double* part;
   int stride;
   int32_t flags;
-  __device__ __forceinline__ explicit PrimalPtrs(gptr<const LpDev> L) {
-    c = uni(L->c);
-    l = uni(L->l);
-    u = uni(L->u);
-    T = uni(L->T);
-    H = uni(L->Hp);
-    G = uni(L->Gp);
-    x0 = uni(L->x[0]);
-    x1 = uni(L->x[1]);
-    s0 = uni(L->xs[0]);
-    s1 = uni(L->xs[1]);
-    y0 = uni((const void*)L->y[0]);
-    y1 = uni((const void*)L->y[1]);
-    rp = uni(L->rp_t);
-    ci = uni(L->ci_t);
-    va = uni(L->va_t);
-    prm = uni(L->prm);
-    part = uni(L->part_t);
-    stride = uni(L->ntiles_t);
-    seg = uni(L->segp_t);
-    flags = uni(L->s_flags);
+  __device__ __forceinline__ explicit PrimalPtrs(cptr<LpDev> L_) : L(L_) {
+    c = L->c;
+    l = L->l;
+    u = L->u;
+    T = L->T;
+    H = L->Hp;
+    G = L->Gp;
+    rp = L->rp_t;
+    ci = L->ci_t;
+    va = L->va_t;
+    prm = L->prm;
+    part = L->part_t;
+    stride = L->ntiles_t;
+    seg = L->segp_t;
+    flags = L->s_flags;
   }
 };
 
 // Context of the primal step for one LP (A^T y, eq. (6)'s primal update and
 // projection, the running sum, the primal online gradient of eq. (7) and
-// the deferred learner update of T), loaded once per LP by begin(). Every
-// value begin() reads is the same in all threads: it is moved to scalar
-// registers (uni) so the branches on it are uniform and the pointers stay
-// out of vector registers.
+// the deferred learner update of T), loaded once per LP by begin() with scalar
+// loads: every value it reads is the same in all threads, the branches on it
+// are uniform and the pointers stay out of vector registers.
 template <typename V>
 struct PrimalStep {
   // FP32 runs accumulate the partial sums in plain FP64 (see acc_prod)
@@ -1414,7 +1411,7 @@ struct PrimalStep {
     // The LP's record and its control block do not depend on each other:
     // both are read before the first wait.
     const CtlView v = ctl_view(ctl);
-    const PrimalPtrs ptr(gp(lp));
+    const PrimalPtrs ptr(cp(lp));
     // the restart / final copy of the evaluation step ran before this
     // launch; the workgroup with the LP's first item clears the flags
     if (first && threadIdx.x == 0 && (v.restart_pending | v.finalize_avg)) {
@@ -1432,7 +1429,7 @@ struct PrimalStep {
     const double eta = uni(v.eta), om = uni(v.omega);
     tau = (V)(eta / om);
     etav = (V)eta;
-    prm = uni(ptr.prm);
+    prm = ptr.prm;
     // a forced (timing) launch writes only the candidate buffers
     learn = uni((int)(!force && v.learn_now != 0)) != 0;
     wstep = uni(v.weighted_step) != 0;
@@ -1441,25 +1438,25 @@ struct PrimalStep {
                     learn_side(v.learn_pending, v.g2, prm, &lscale))) != 0;
     lscale = uni(lscale);
     hnorm = uni(v.hp_norm);
-    cc = uni(gp(static_cast<const V*>(ptr.c)));
-    lo = uni(gp(static_cast<const V*>(ptr.l)));
-    hi = uni(gp(static_cast<const V*>(ptr.u)));
-    T = uni(gp(static_cast<V*>(ptr.T)));
-    Hp = uni(gp(static_cast<V*>(ptr.H)));
-    Gp = uni(gp(static_cast<V*>(ptr.G)));
-    x = uni(gp(static_cast<const V*>(cur ? ptr.x1 : ptr.x0)));
-    xs = uni(gp(static_cast<const V*>(cur ? ptr.s1 : ptr.s0)));
-    xn = uni(gp(static_cast<V*>(cur ? ptr.x0 : ptr.x1)));
-    xsn = uni(gp(static_cast<V*>(cur ? ptr.s0 : ptr.s1)));
-    vecs[0] = uni(gp(static_cast<const V*>(cur ? ptr.y1 : ptr.y0)));
+    cc = gp(static_cast<const V*>(ptr.c));
+    lo = gp(static_cast<const V*>(ptr.l));
+    hi = gp(static_cast<const V*>(ptr.u));
+    T = gp(static_cast<V*>(ptr.T));
+    Hp = gp(static_cast<V*>(ptr.H));
+    Gp = gp(static_cast<V*>(ptr.G));
+    x = gp(static_cast<const V*>(ptr.L->x[cur]));
+    xs = gp(static_cast<const V*>(ptr.L->xs[cur]));
+    xn = gp(static_cast<V*>(ptr.L->x[cur ^ 1]));
+    xsn = gp(static_cast<V*>(ptr.L->xs[cur ^ 1]));
+    vecs[0] = gp(static_cast<const V*>(ptr.L->y[cur]));
     Hsrc = upd ? Hp : x;
     Gsrc = upd ? Gp : x;
-    rp = uni(gp(ptr.rp));
-    ci = uni(gp(ptr.ci));
-    va = uni(gp(static_cast<const V*>(ptr.va)));
-    part_ = uni(ptr.part);
-    stride_ = uni(ptr.stride);
-    segp_ = uni(ptr.seg);
+    rp = gp(ptr.rp);
+    ci = gp(ptr.ci);
+    va = gp(static_cast<const V*>(ptr.va));
+    part_ = ptr.part;
+    stride_ = ptr.stride;
+    segp_ = ptr.seg;
     lzero = (ptr.flags & kLowerZero) != 0;
     noup = (ptr.flags & kNoUpper) != 0;
     tau = uni(tau), etav = uni(etav);
@@ -1544,34 +1541,27 @@ struct DualPre {
 
 // As PrimalPtrs.
 struct DualPtrs {
-  const void *b, *x0, *x1, *va;
-  void *S, *H, *G, *y0, *y1, *s0, *s1, *a0, *a1, *seg;
+  cptr<LpDev> L;
+  const void *b, *va;
+  void *S, *H, *G, *seg;
   const int8_t* sense;
   const int32_t *rp, *ci;
   const DevParams* prm;
   double* part;
   int stride;
-  __device__ __forceinline__ explicit DualPtrs(gptr<const LpDev> L) {
-    b = uni((const void*)L->b);
-    S = uni(L->S);
-    H = uni(L->Hd);
-    G = uni(L->Gd);
-    y0 = uni(L->y[0]);
-    y1 = uni(L->y[1]);
-    s0 = uni(L->ys[0]);
-    s1 = uni(L->ys[1]);
-    a0 = uni(L->Ax[0]);
-    a1 = uni(L->Ax[1]);
-    x0 = uni((const void*)L->x[0]);
-    x1 = uni((const void*)L->x[1]);
-    sense = uni(L->sense);
-    rp = uni(L->rp_a);
-    ci = uni(L->ci_a);
-    va = uni(L->va_a);
-    prm = uni(L->prm);
-    part = uni(L->part_a);
-    stride = uni(L->ntiles_a);
-    seg = uni(L->segp_a);
+  __device__ __forceinline__ explicit DualPtrs(cptr<LpDev> L_) : L(L_) {
+    b = L->b;
+    S = L->S;
+    H = L->Hd;
+    G = L->Gd;
+    sense = L->sense;
+    rp = L->rp_a;
+    ci = L->ci_a;
+    va = L->va_a;
+    prm = L->prm;
+    part = L->part_a;
+    stride = L->ntiles_a;
+    seg = L->segp_a;
   }
 };
 
@@ -1603,9 +1593,9 @@ struct DualStep {
     c = ctl;
     lp = &cfg.lps[lpi];
     // as in PrimalStep: the LP's record and its control block are read
-    // together, and uniform values live in scalar registers
+    // together
     const CtlView v = ctl_view(ctl);
-    const DualPtrs ptr(gp(lp));
+    const DualPtrs ptr(cp(lp));
     if (!uni((int)(force || v.attempt()))) return false;
     arm(ptr, v, force);
     return true;
@@ -1616,7 +1606,7 @@ struct DualStep {
     const double eta = uni(v.eta), om = uni(v.omega);
     sig = (V)(eta * om);
     etav = (V)eta;
-    prm = uni(ptr.prm);
+    prm = ptr.prm;
     learn = uni((int)(!force && v.learn_now != 0)) != 0;
     wstep = uni(v.weighted_step) != 0;
     lscale = 1.0;
@@ -1624,27 +1614,27 @@ struct DualStep {
                     learn_side(v.learn_pending, v.r2, prm, &lscale))) != 0;
     lscale = uni(lscale);
     hnorm = uni(v.hd_norm);
-    b = uni(gp(static_cast<const V*>(ptr.b)));
-    S = uni(gp(static_cast<V*>(ptr.S)));
-    Hd = uni(gp(static_cast<V*>(ptr.H)));
-    Gd = uni(gp(static_cast<V*>(ptr.G)));
-    y = uni(gp(static_cast<const V*>(cur ? ptr.y1 : ptr.y0)));
-    ys = uni(gp(static_cast<const V*>(cur ? ptr.s1 : ptr.s0)));
-    Ax = uni(gp(static_cast<const V*>(cur ? ptr.a1 : ptr.a0)));
-    yn = uni(gp(static_cast<V*>(cur ? ptr.y0 : ptr.y1)));
-    ysn = uni(gp(static_cast<V*>(cur ? ptr.s0 : ptr.s1)));
-    Axn = uni(gp(static_cast<V*>(cur ? ptr.a0 : ptr.a1)));
+    b = gp(static_cast<const V*>(ptr.b));
+    S = gp(static_cast<V*>(ptr.S));
+    Hd = gp(static_cast<V*>(ptr.H));
+    Gd = gp(static_cast<V*>(ptr.G));
+    y = gp(static_cast<const V*>(ptr.L->y[cur]));
+    ys = gp(static_cast<const V*>(ptr.L->ys[cur]));
+    Ax = gp(static_cast<const V*>(ptr.L->Ax[cur]));
+    yn = gp(static_cast<V*>(ptr.L->y[cur ^ 1]));
+    ysn = gp(static_cast<V*>(ptr.L->ys[cur ^ 1]));
+    Axn = gp(static_cast<V*>(ptr.L->Ax[cur ^ 1]));
     // x' was written by this attempt's primal step into the other buffer
-    vecs[0] = uni(gp(static_cast<const V*>(cur ? ptr.x0 : ptr.x1)));
-    sense = uni(gp(ptr.sense));
+    vecs[0] = gp(static_cast<const V*>(ptr.L->x[cur ^ 1]));
+    sense = gp(ptr.sense);
     Hsrc = upd ? Hd : y;
     Gsrc = upd ? Gd : y;
-    rp = uni(gp(ptr.rp));
-    ci = uni(gp(ptr.ci));
-    va = uni(gp(static_cast<const V*>(ptr.va)));
-    part_ = uni(ptr.part);
-    stride_ = uni(ptr.stride);
-    segp_ = uni(ptr.seg);
+    rp = gp(ptr.rp);
+    ci = gp(ptr.ci);
+    va = gp(static_cast<const V*>(ptr.va));
+    part_ = ptr.part;
+    stride_ = ptr.stride;
+    segp_ = ptr.seg;
     sig = uni(sig), etav = uni(etav);
   }
 
@@ -1743,18 +1733,20 @@ __device__ __forceinline__ SideChunks step_chunks(const LaunchCfg& cfg, bool tsi
   return side_chunks(cfg.counts, tside);
 }
 
+// At most five workgroups share a CU: told so, the compiler does not trade
+// loads in flight for a sixth.
 template <typename V>
-__global__ __launch_bounds__(kBlock) void k_primal(LaunchCfg cfg, int force) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 5))) void k_primal(
+    LaunchCfg cfg, int force) {
   __shared__ SpmvShared<V, 1> sh;
   __shared__ TilePartials<3> tp;
   const double nodiv[1] = {0.0};
   DD p[3];
   dd_reset(p);
   PrimalStep<V> st;
-  __shared__ WorkItem s_items[kItemWin];
   sgpr_ready(cfg.lps, cfg.step_t, cfg.counts, cfg.step_fixed, cfg.sgrid_t, cfg.schunk_t, force);
   run_chunk_spmv<V, 1, 3, PrimalStep<V>::kPlain>(
-      cfg.step_t, step_chunks(cfg, true), s_items, st.rp, st.ci,
+      cfg.step_t, step_chunks(cfg, true), st.rp, st.ci,
       st.va, st.vecs, nodiv,
       [&](const WorkItem& it) { return st.begin(cfg, it.ctl, it.lp, it.first, force); },
       [&](int j) { return st.load(j); },
@@ -1768,17 +1760,17 @@ __global__ __launch_bounds__(kBlock) void k_primal(LaunchCfg cfg, int force) {
 }
 
 template <typename V>
-__global__ __launch_bounds__(kBlock) void k_dual(LaunchCfg cfg, int force) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, 5))) void k_dual(
+    LaunchCfg cfg, int force) {
   __shared__ SpmvShared<V, 1> sh;
   __shared__ TilePartials<4> tp;
   const double nodiv[1] = {0.0};
   DD p[4];
   dd_reset(p);
   DualStep<V> st;
-  __shared__ WorkItem s_items[kItemWin];
   sgpr_ready(cfg.lps, cfg.step_a, cfg.counts, cfg.step_fixed, cfg.sgrid_a, cfg.schunk_a, force);
   run_chunk_spmv<V, 1, 4, DualStep<V>::kPlain>(
-      cfg.step_a, step_chunks(cfg, false), s_items, st.rp, st.ci,
+      cfg.step_a, step_chunks(cfg, false), st.rp, st.ci,
       st.va, st.vecs, nodiv,
       [&](const WorkItem& it) { return st.begin(cfg, it.ctl, it.lp, it.first, force); },
       [&](int i) { return st.load(i); },
@@ -2144,9 +2136,8 @@ __global__ __launch_bounds__(kBlock) void k_prod_tiles(LaunchCfg cfg) {
   DD p[1];
   dd_reset(p);
   ProdStep<TSIDE, WHICH> st;
-  __shared__ WorkItem s_items[kItemWin];
   run_chunk_spmv<float, 1, 1, true>(
-      TSIDE ? cfg.step_t : cfg.step_a, step_chunks(cfg, TSIDE), s_items, st.rp, st.ci, st.va,
+      TSIDE ? cfg.step_t : cfg.step_a, step_chunks(cfg, TSIDE), st.rp, st.ci, st.va,
       st.vecs, nodiv,
       [&](const WorkItem& it) { return st.begin(cfg, it.ctl, it.lp, it.first, 0); },
       [&](int j) { return st.load(j); },
@@ -2183,25 +2174,25 @@ __global__ __launch_bounds__(kWinBlock) void k_dual_win(LaunchCfg cfg, int force
 using DecideLp = DecideRec;
 
 __device__ __forceinline__ DecideLp decide_lp(const LpDev* rec) {
-  const gptr<const LpDev> L = gp(rec);
+  const cptr<LpDev> L = cp(rec);
   DecideLp d;
-  d.ctl = uni(L->ctl);
-  d.ring = uni((const double*)L->pow_ring);
-  d.part_t = uni((const double*)L->part_t);
-  d.part_a = uni((const double*)L->part_a);
-  d.ntiles_t = uni(L->ntiles_t);
-  d.ntiles_a = uni(L->ntiles_a);
+  d.ctl = L->ctl;
+  d.ring = L->pow_ring;
+  d.part_t = L->part_t;
+  d.part_a = L->part_a;
+  d.ntiles_t = L->ntiles_t;
+  d.ntiles_a = L->ntiles_a;
   // slots of the step kernels (one per tile, then the windowed chunks)
-  d.ns_t = uni(L->nslot_st);
-  d.ns_a = uni(L->nslot_sa);
-  d.lr = uni(L->s_lr);
-  d.max_iter = uni(L->s_max_iter);
-  d.phi = uni(L->s_phi);
-  d.schedule = uni(L->s_schedule);
-  d.normalize = uni(L->s_normalize);
-  d.eval_every = uni(L->s_eval_every);
-  d.max_retries = uni(L->s_max_retries);
-  d.flags = uni(L->s_flags);
+  d.ns_t = L->nslot_st;
+  d.ns_a = L->nslot_sa;
+  d.lr = L->s_lr;
+  d.max_iter = L->s_max_iter;
+  d.phi = L->s_phi;
+  d.schedule = L->s_schedule;
+  d.normalize = L->s_normalize;
+  d.eval_every = L->s_eval_every;
+  d.max_retries = L->s_max_retries;
+  d.flags = L->s_flags;
   return d;
 }
 
@@ -2238,10 +2229,10 @@ __global__ __launch_bounds__(PLAIN ? kBlock : kDecBlock)
     nlps = 1;
   } else {
     d = decide_lp(&cfg.lps[li]);
-    nlps = uni(gp(cfg.counts)->nlps);
+    nlps = cp(cfg.counts)->nlps;
   }
   while (li < nlps) {
-    const gptr<const Ctl> g = gp(d.ctl);
+    const cptr<Ctl> g = cp(d.ctl);
     StepIn in;
     in.lr = d.lr;
     in.max_iter = d.max_iter;
@@ -2262,27 +2253,20 @@ __global__ __launch_bounds__(PLAIN ? kBlock : kDecBlock)
     // the control block is read after the first round of partial loads is
     // issued, in the same round trip
     auto control = [&]() {
-      // every load first, then the moves to scalar registers (each of
-      // which waits for its load)
-      const int st0 = g->status, ne0 = g->need_eval, cu0 = g->cur;
-      const int64_t kl0 = g->k_limit, rb0 = g->ring_base, k0 = g->k;
-      const int64_t t0 = g->t, at0 = g->attempts, re0 = g->retries;
-      const double et0 = g->eta, om0 = g->omega, w0 = g->w;
-      const double hp0 = g->hp_norm, hd0 = g->hd_norm;
-      status = uni(st0);
-      need = uni(ne0);
-      k_limit = uni(kl0);
-      ring_base = uni(rb0);
-      in.eta = uni(et0);
-      in.omega = uni(om0);
-      in.w = uni(w0);
-      in.hp_norm = uni(hp0);
-      in.hd_norm = uni(hd0);
-      in.k = uni(k0);
-      in.t = uni(t0);
-      in.attempts = uni(at0);
-      in.retries = uni(re0);
-      in.cur = uni(cu0);
+      status = g->status;
+      need = g->need_eval;
+      k_limit = g->k_limit;
+      ring_base = g->ring_base;
+      in.eta = g->eta;
+      in.omega = g->omega;
+      in.w = g->w;
+      in.hp_norm = g->hp_norm;
+      in.hd_norm = g->hd_norm;
+      in.k = g->k;
+      in.t = g->t;
+      in.attempts = g->attempts;
+      in.retries = g->retries;
+      in.cur = g->cur;
     };
     if constexpr (PLAIN) {
       sum_partials2<3, 4>(d.part_t, d.ntiles_t, d.ns_t, d.part_a, d.ntiles_a, d.ns_a, sv, s_red,
@@ -2451,8 +2435,8 @@ __global__ __launch_bounds__(kOneThreads) void k_one(LaunchCfg cfg, int attempts
   __shared__ DD s_red[(kOneThreads / 64) * 7];
   const int t = threadIdx.x, nt = blockDim.x;
   const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const gptr<const LpDev> L = gp(&cfg.lps[blockIdx.x]);
-  Ctl* const ctl = uni(L->ctl);
+  const cptr<LpDev> L = cp(&cfg.lps[blockIdx.x]);
+  Ctl* const ctl = L->ctl;
   {
     const CtlView v = ctl_view(ctl);
     // the restart / final copy of the evaluation step ran before this launch
@@ -2464,23 +2448,23 @@ __global__ __launch_bounds__(kOneThreads) void k_one(LaunchCfg cfg, int attempts
   }
   const PrimalPtrs pp(L);
   const DualPtrs dp(L);
-  const int m = uni(L->m), n = uni(L->n);
-  const int long_t = uni(L->one_long_t), med_t = uni(L->one_med_t);
-  const int long_a = uni(L->one_long_a), med_a = uni(L->one_med_a);
-  const gptr<const uint16_t> col_t = uni(gp((const uint16_t*)L->one_col_t));
-  const gptr<const uint16_t> col_a = uni(gp((const uint16_t*)L->one_col_a));
-  const gptr<const double> val_t = uni(gp((const double*)L->one_val_t));
-  const gptr<const double> val_a = uni(gp((const double*)L->one_val_a));
+  const int m = L->m, n = L->n;
+  const int long_t = L->one_long_t, med_t = L->one_med_t;
+  const int long_a = L->one_long_a, med_a = L->one_med_a;
+  const gptr<const uint16_t> col_t = gp((const uint16_t*)L->one_col_t);
+  const gptr<const uint16_t> col_a = gp((const uint16_t*)L->one_col_a);
+  const gptr<const double> val_t = gp((const double*)L->one_val_t);
+  const gptr<const double> val_a = gp((const double*)L->one_val_a);
   StepIn in;
-  in.lr = uni(L->s_lr);
-  in.max_iter = uni(L->s_max_iter);
-  in.phi = uni(L->s_phi);
-  in.schedule = uni(L->s_schedule);
-  in.normalize = uni(L->s_normalize);
-  in.eval_every = uni(L->s_eval_every);
-  in.max_retries = uni(L->s_max_retries);
-  in.flags = uni(L->s_flags);
-  const double* const ring = uni((const double*)L->pow_ring);
+  in.lr = L->s_lr;
+  in.max_iter = L->s_max_iter;
+  in.phi = L->s_phi;
+  in.schedule = L->s_schedule;
+  in.normalize = L->s_normalize;
+  in.eval_every = L->s_eval_every;
+  in.max_retries = L->s_max_retries;
+  in.flags = L->s_flags;
+  const double* const ring = L->pow_ring;
   // the LP's LDS: y (both copies), x', then the slices' offsets and the lane
   // rows' entry counts of both sides
   double* const yb = one_lds;
@@ -2499,7 +2483,7 @@ __global__ __launch_bounds__(kOneThreads) void k_one(LaunchCfg cfg, int attempts
       reinterpret_cast<uint64_t*>(&s_prm)[w] = sp[w];
     for (int w = t; w < 2 * kPowRing; w += nt) s_ring[w] = gp(ring)[w];
     const int cur = uni(gp(ctl)->cur);
-    const gptr<const double> y = gp(static_cast<const double*>(cur ? pp.y1 : pp.y0));
+    const gptr<const double> y = gp(static_cast<const double*>(L->y[cur]));
     for (int i = t; i < m; i += nt) yb[cur * m + i] = y[i];
     auto lengths = [&](const int32_t* rp_, int rows, int med, uint8_t* cnt, int32_t* base) {
       const gptr<const int32_t> rp = gp(rp_);
@@ -2520,7 +2504,7 @@ __global__ __launch_bounds__(kOneThreads) void k_one(LaunchCfg cfg, int attempts
   PrimalStep<double> ps;
   DualStep<double> ds;
   for (;;) {
-    const CtlView v = ctl_view_at(&s_ctl);
+    const CtlView v = ctl_view_at<false>(&s_ctl);
     if (!uni((int)(v.attempt() && s_ctl.attempts - s_ctl.ring_base < attempts))) break;
     const int cur = uni(v.cur);
     DD p[3], d[4];
