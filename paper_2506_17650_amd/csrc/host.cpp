@@ -1819,8 +1819,7 @@ int Group::enqueue(hipStream_t s, int attempts) {
       // the opening evaluation of LPs with windowed chunks takes its sparse
       // products from the windowed machinery; the guarded ones gather
       if (mid == 0) rc |= Kernels<V>::eval_products(cfg, s);
-      rc |= Kernels<V>::eval_t(cfg, s, mid);
-      rc |= Kernels<V>::eval_a(cfg, s, mid);
+      rc |= Kernels<V>::eval(cfg, s, mid);
       rc |= Kernels<V>::eval_decide(cfg, s, mid);
       rc |= Kernels<V>::apply(cfg, s, mid);
     };

@@ -191,12 +191,12 @@ __device__ __forceinline__ void lds_barrier() {
 // in that XCD's L2 instead of being spread over all eight.
 // g is the side's chunk count (read from the device-side counts); the
 // launch grid may be larger, and workgroups b >= g get -1 (no chunk).
-__device__ __forceinline__ int chunk_index(int g) {
-  const int b = blockIdx.x;
+__device__ __forceinline__ int chunk_index(int g, int b) {
   if (b >= g) return -1;
   if (g & 7) return b;
   return (b & 7) * (g >> 3) + (b >> 3);
 }
+__device__ __forceinline__ int chunk_index(int g) { return chunk_index(g, blockIdx.x); }
 
 __device__ __forceinline__ DD dd_shfl_xor(const DD& a, int off) {
   return DD{__shfl_xor(a.hi, off, 64), __shfl_xor(a.lo, off, 64)};
@@ -829,7 +829,7 @@ __device__ __forceinline__ V clampv(V v, V lo, V hi) {
 // a launch sequence serves every due LP; the guarded evaluations inside the
 // sequence (mid) serve only LPs below their pause point, so a session paused
 // at k_limit keeps the evaluation due there for its next run.
-__device__ __forceinline__ bool eval_guard(const Ctl* c, int mid) {
+__device__ __forceinline__ bool eval_guard(cptr<Ctl> c, int mid) {
   return c->status == kRunning && c->need_eval != 0 && (!mid || c->k < c->k_limit);
 }
 
@@ -851,7 +851,7 @@ __device__ __forceinline__ void flush_partials(DD (&p)[NV], DD* s_red, double* p
 
 // Whether work item wi is the last of its LP in the chunk [i0, i0 + chunk)
 // (an LP's items are consecutive in the list).
-__device__ __forceinline__ bool last_of_lp(const WorkItem* work, int wi, int i0, int chunk,
+__device__ __forceinline__ bool last_of_lp(cptr<WorkItem> work, int wi, int i0, int chunk,
                                            int lp) {
   return wi + 1 == i0 + chunk || work[wi + 1].lp != lp;
 }
@@ -2671,18 +2671,18 @@ struct EvalT {
   gptr<const int8_t> bfin;
   double w;
   bool has_avg;
-  __device__ __forceinline__ EvalT(const LpDev& lp, const Ctl* c) {
+  __device__ __forceinline__ EvalT(cptr<LpDev> L, cptr<Ctl> c) {
     const int cur = c->cur;
     w = c->w;
     has_avg = w > 0.0;
-    cc = gp(static_cast<const V*>(lp.c));
-    lo = gp(static_cast<const V*>(lp.l));
-    hi = gp(static_cast<const V*>(lp.u));
-    x = gp(static_cast<const V*>(lp.x[cur]));
-    xs = gp(static_cast<const V*>(lp.xs[cur]));
-    xa = gp(static_cast<const V*>(lp.xa));
-    dc = gp(lp.dc);
-    bfin = gp(lp.bfin);
+    cc = gp(static_cast<const V*>(L->c));
+    lo = gp(static_cast<const V*>(L->l));
+    hi = gp(static_cast<const V*>(L->u));
+    x = gp(static_cast<const V*>(L->x[cur]));
+    xs = gp(static_cast<const V*>(L->xs[cur]));
+    xa = gp(static_cast<const V*>(L->xa));
+    dc = gp(L->dc);
+    bfin = gp(L->bfin);
   }
   __device__ __forceinline__ void row(int j, const V (&acc)[2], DD* p) const {
     const double cj = (double)cc[j];
@@ -2718,18 +2718,18 @@ struct EvalA {
   gptr<const int8_t> sense;
   double w;
   bool has_avg;
-  __device__ __forceinline__ EvalA(const LpDev& lp, const Ctl* c) {
+  __device__ __forceinline__ EvalA(cptr<LpDev> L, cptr<Ctl> c) {
     const int cur = c->cur;
     w = c->w;
     has_avg = w > 0.0;
-    b = gp(static_cast<const V*>(lp.b));
-    y = gp(static_cast<const V*>(lp.y[cur]));
-    ys = gp(static_cast<const V*>(lp.ys[cur]));
-    ya = gp(static_cast<const V*>(lp.ya));
-    Ax = gp(static_cast<const V*>(lp.Ax[cur]));
-    Axa = gp(static_cast<V*>(lp.Axa));
-    dr = gp(lp.dr);
-    sense = gp(lp.sense);
+    b = gp(static_cast<const V*>(L->b));
+    y = gp(static_cast<const V*>(L->y[cur]));
+    ys = gp(static_cast<const V*>(L->ys[cur]));
+    ya = gp(static_cast<const V*>(L->ya));
+    Ax = gp(static_cast<const V*>(L->Ax[cur]));
+    Axa = gp(static_cast<V*>(L->Axa));
+    dr = gp(L->dr);
+    sense = gp(L->sense);
   }
   __device__ __forceinline__ void row(int i, const V (&acc)[1], DD* p) const {
     const double bi = (double)b[i];
@@ -2755,78 +2755,75 @@ struct EvalA {
 };
 
 // Whether an LP's opening evaluation takes precomputed products (then
-// k_eval_pre serves it and the tile kernels below skip it).
-__device__ __forceinline__ bool eval_pre(const LpDev& lp, int mid, bool tside) {
-  return mid == 0 && (tside ? lp.evp_t0 : lp.evp_a) != nullptr;
+// k_eval_pre serves it and the tile kernel below skips it).
+__device__ __forceinline__ bool eval_pre(cptr<LpDev> L, int mid, bool tside) {
+  return mid == 0 && (tside ? L->evp_t0 : L->evp_a) != nullptr;
 }
 
-template <typename V>
-__global__ __launch_bounds__(kBlock) void k_eval_t(LaunchCfg cfg, int mid) {
-  __shared__ SpmvShared<V, 2> sh;
-  __shared__ DD s_red[4 * 2 * kEvT];
-  if (eval_step_skips(cfg, mid, true)) return;
-  DD p[2 * kEvT];
+// A chunk of one side of an evaluation.
+template <typename V, bool TSIDE>
+__device__ __forceinline__ void eval_chunk(const LaunchCfg& cfg, int mid, int b,
+                                           SpmvShared<V, 2>& lds, DD* s_red) {
+  constexpr int NA = TSIDE ? 2 : 1;
+  constexpr int NV = TSIDE ? 2 * kEvT : 2 * kEvA;
+  static_assert(sizeof(SpmvShared<V, NA>) <= sizeof(lds), "one LDS area for both sides");
+  SpmvShared<V, NA>& sh = reinterpret_cast<SpmvShared<V, NA>&>(lds);
+  DD p[NV];
   dd_reset(p);
-  const SideChunks sc = side_chunks(cfg.counts, true);
-  const int ch = chunk_index(sc.grid);
+  const SideChunks sc = side_chunks(cfg.counts, TSIDE);
+  const int ch = chunk_index(sc.grid, b);
   if (ch < 0) return;
+  const cptr<WorkItem> work = cp(TSIDE ? cfg.work_t : cfg.work_a);
   const int i0 = ch * sc.chunk;
   for (int wi = i0; wi < i0 + sc.chunk; ++wi) {
-    const WorkItem it = cfg.work_t[wi];
+    const WorkItem it = load_item(work + wi);
     if (it.lp < 0) continue;
     // the evaluation's double-double sums do not depend on their order, so
     // the workgroup reduces an LP's part of the chunk once, into the slot of
     // the chunk's ordinal among those touching the LP
-    const bool endc = last_of_lp(cfg.work_t, wi, i0, sc.chunk, it.lp);
-    const Ctl* c = it.ctl;
-    const LpDev& lp = cfg.lps[it.lp];
-    if (!eval_guard(c, mid) || eval_pre(lp, mid, true)) {
+    const bool endc = last_of_lp(work, wi, i0, sc.chunk, it.lp);
+    const cptr<Ctl> c = cp(it.ctl);
+    const cptr<LpDev> L = cp(&cfg.lps[it.lp]);
+    if (!eval_guard(c, mid) || eval_pre(L, mid, TSIDE)) {
       if (endc) dd_reset(p);
       continue;
     }
-    const EvalT<V> E(lp, c);
-    const gptr<const V> vecs[2] = {gp(static_cast<const V*>(lp.y[c->cur])),
-                                   gp(static_cast<const V*>(lp.ys[c->cur]))};
-    const double divs[2] = {0.0, E.has_avg ? E.w : -1.0};
-    spmv_tile<V, 2>(it, gp(lp.rp_t), gp(lp.ci_t), gp(static_cast<const V*>(lp.va_t)), vecs,
-                    divs, [&](int) { return 0; },
-                    [&](int j, V (&acc)[2], int) { E.row(j, acc, p); }, sh);
-    if (endc)
-      flush_partials<2 * kEvT>(p, s_red, lp.part_t, lp.ntiles_t, ch - lp.item0_t / sc.chunk);
+    const int cur = c->cur;
+    if constexpr (TSIDE) {
+      const EvalT<V> E(L, c);
+      const gptr<const V> vecs[2] = {gp(static_cast<const V*>(L->y[cur])),
+                                     gp(static_cast<const V*>(L->ys[cur]))};
+      const double divs[2] = {0.0, E.has_avg ? E.w : -1.0};
+      spmv_tile<V, 2>(it, gp(L->rp_t), gp(L->ci_t), gp(static_cast<const V*>(L->va_t)), vecs,
+                      divs, [&](int) { return 0; },
+                      [&](int j, V (&acc)[2], int) { E.row(j, acc, p); }, sh);
+      if (endc)
+        flush_partials<NV>(p, s_red, L->part_t, L->ntiles_t, ch - L->item0_t / sc.chunk);
+    } else {
+      const EvalA<V> E(L, c);
+      const gptr<const V> vecs[1] = {gp(static_cast<const V*>(L->xs[cur]))};
+      const double divs[1] = {E.has_avg ? E.w : -1.0};
+      spmv_tile<V, 1>(it, gp(L->rp_a), gp(L->ci_a), gp(static_cast<const V*>(L->va_a)), vecs,
+                      divs, [&](int) { return 0; },
+                      [&](int i, V (&acc)[1], int) { E.row(i, acc, p); }, sh);
+      if (endc)
+        flush_partials<NV>(p, s_red, L->part_a, L->ntiles_a, ch - L->item0_a / sc.chunk);
+    }
   }
 }
 
+// Both sides of an evaluation, which do not depend on each other, in one
+// launch: the first launch_t workgroups take the rows of A^T, the others
+// those of A. A guarded step with no LP due is then three empty launches
+// instead of four (seven such steps a sequence). @S5@
 template <typename V>
-__global__ __launch_bounds__(kBlock) void k_eval_a(LaunchCfg cfg, int mid) {
-  __shared__ SpmvShared<V, 1> sh;
-  __shared__ DD s_red[4 * 2 * kEvA];
-  if (eval_step_skips(cfg, mid, false)) return;
-  DD p[2 * kEvA];
-  dd_reset(p);
-  const SideChunks sc = side_chunks(cfg.counts, false);
-  const int ch = chunk_index(sc.grid);
-  if (ch < 0) return;
-  const int i0 = ch * sc.chunk;
-  for (int wi = i0; wi < i0 + sc.chunk; ++wi) {
-    const WorkItem it = cfg.work_a[wi];
-    if (it.lp < 0) continue;
-    // as in k_eval_t: one reduction per LP and chunk
-    const bool endc = last_of_lp(cfg.work_a, wi, i0, sc.chunk, it.lp);
-    const Ctl* c = it.ctl;
-    const LpDev& lp = cfg.lps[it.lp];
-    if (!eval_guard(c, mid) || eval_pre(lp, mid, false)) {
-      if (endc) dd_reset(p);
-      continue;
-    }
-    const EvalA<V> E(lp, c);
-    const gptr<const V> vecs[1] = {gp(static_cast<const V*>(lp.xs[c->cur]))};
-    const double divs[1] = {E.has_avg ? E.w : -1.0};
-    spmv_tile<V, 1>(it, gp(lp.rp_a), gp(lp.ci_a), gp(static_cast<const V*>(lp.va_a)), vecs,
-                    divs, [&](int) { return 0; },
-                    [&](int i, V (&acc)[1], int) { E.row(i, acc, p); }, sh);
-    if (endc)
-      flush_partials<2 * kEvA>(p, s_red, lp.part_a, lp.ntiles_a, ch - lp.item0_a / sc.chunk);
-  }
+__global__ __launch_bounds__(kBlock) void k_eval(LaunchCfg cfg, int mid) {
+  __shared__ SpmvShared<V, 2> sh;
+  __shared__ DD s_red[4 * 2 * kEvT];
+  if (eval_step_skips(cfg, mid, true)) return;
+  const int b = blockIdx.x;
+  if (b < cfg.launch_t) eval_chunk<V, true>(cfg, mid, b, sh, s_red);
+  else eval_chunk<V, false>(cfg, mid, b - cfg.launch_t, sh, s_red);
 }
 
 // The opening evaluation of LPs with precomputed products (FP32 windowed
@@ -2844,40 +2841,40 @@ __global__ __launch_bounds__(kBlock) void k_eval_pre(LaunchCfg cfg) {
   const SideChunks sc = side_chunks(cfg.counts, TSIDE);
   const int ch = chunk_index(sc.grid);
   if (ch < 0) return;
-  const WorkItem* work = TSIDE ? cfg.work_t : cfg.work_a;
+  const cptr<WorkItem> work = cp(TSIDE ? cfg.work_t : cfg.work_a);
   const int i0 = ch * sc.chunk;
   int prev = -1;
   for (int wi = i0; wi < i0 + sc.chunk; ++wi) {
-    const int lpi = uni(work[wi].lp);
+    const int lpi = work[wi].lp;
     if (lpi < 0 || lpi == prev) continue;  // an LP's items are consecutive
     prev = lpi;
-    const LpDev& lp = cfg.lps[lpi];
-    const Ctl* c = lp.ctl;
-    if (!uni((int)(eval_guard(c, 0) && eval_pre(lp, 0, TSIDE)))) continue;
-    const int c0 = (TSIDE ? lp.item0_t : lp.item0_a) / sc.chunk;
-    const int ns = TSIDE ? lp.nslot_t : lp.nslot_a;
+    const cptr<LpDev> L = cp(&cfg.lps[lpi]);
+    const cptr<Ctl> c = cp(L->ctl);
+    if (!(eval_guard(c, 0) && eval_pre(L, 0, TSIDE))) continue;
+    const int c0 = (TSIDE ? L->item0_t : L->item0_a) / sc.chunk;
+    const int ns = TSIDE ? L->nslot_t : L->nslot_a;
     const int slot = ch - c0;
-    const int64_t rows = TSIDE ? lp.n : lp.m;
+    const int64_t rows = TSIDE ? L->n : L->m;
     const int r0 = (int)(rows * slot / ns), r1 = (int)(rows * (slot + 1) / ns);
     DD p[NV];
     dd_reset(p);
     if constexpr (TSIDE) {
-      const EvalT<float> E(lp, c);
-      const gptr<const float> e0 = gp(static_cast<const float*>(lp.evp_t0));
-      const gptr<const float> e1 = gp(static_cast<const float*>(lp.evp_t1));
+      const EvalT<float> E(L, c);
+      const gptr<const float> e0 = gp((const float*)L->evp_t0);
+      const gptr<const float> e1 = gp((const float*)L->evp_t1);
       for (int j = r0 + (int)threadIdx.x; j < r1; j += kBlock) {
         const float acc[2] = {ldg(e0, (uint32_t)j), ldg(e1, (uint32_t)j)};
         E.row(j, acc, p);
       }
-      flush_partials<NV>(p, s_red, lp.part_t, lp.ntiles_t, slot);
+      flush_partials<NV>(p, s_red, L->part_t, L->ntiles_t, slot);
     } else {
-      const EvalA<float> E(lp, c);
-      const gptr<const float> e = gp(static_cast<const float*>(lp.evp_a));
+      const EvalA<float> E(L, c);
+      const gptr<const float> e = gp((const float*)L->evp_a);
       for (int i = r0 + (int)threadIdx.x; i < r1; i += kBlock) {
         const float acc[1] = {ldg(e, (uint32_t)i)};
         E.row(i, acc, p);
       }
-      flush_partials<NV>(p, s_red, lp.part_a, lp.ntiles_a, slot);
+      flush_partials<NV>(p, s_red, L->part_a, L->ntiles_a, slot);
     }
   }
 }
@@ -2887,54 +2884,68 @@ __global__ __launch_bounds__(kBlock) void k_eval_pre(LaunchCfg cfg) {
 // step-rule factor ring for the sequence; the guarded ones inside it
 // (mid = 1, 2, ...) leave the ring alone (it already covers every attempt
 // of the sequence).
-// Each of the evaluation's sums gets a wave of the workgroup (wave_partials).
+// Each of the evaluation's sums gets a wave of the workgroup (wave_partials);
+// meanwhile the control block and the parameters come to LDS, where one
+// thread decides: its reads were a chain of memory round trips there. @S6@
 __global__ __launch_bounds__(kDecBlock) void k_eval_decide(LaunchCfg cfg, int mid) {
   __shared__ double s_sum[2 * kEvT + 2 * kEvA];
+  __shared__ Ctl s_ctl;
+  __shared__ DevParams s_prm;
   if (eval_step_skips(cfg, mid, false)) return;
-  auto decide = [&](const LpDev& lp, Ctl* c) {
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    for (int q = wave; q < 2 * kEvT + 2 * kEvA; q += kDecBlock / 64) {
-      const bool ts = q < 2 * kEvT;
-      const int stride = ts ? lp.ntiles_t : lp.ntiles_a;
-      const DD t = wave_partials(
-          gp((const double*)(ts ? lp.part_t : lp.part_a)) +
-              (size_t)(2 * (ts ? q : q - 2 * kEvT)) * stride,
-          stride, ts ? lp.nslot_t : lp.nslot_a);
-      if ((threadIdx.x & 63) == 0) s_sum[q] = dd_value(t);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) decide_eval(c, lp.prm, s_sum, s_sum + 2 * kEvT);
-    __syncthreads();
-  };
-  const int nlps = cfg.counts->nlps;
+  const int nlps = cp(cfg.counts)->nlps;
+  const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   for (int li = blockIdx.x; li < nlps; li += gridDim.x) {
-    const LpDev& lp = cfg.lps[li];
-    Ctl* c = lp.ctl;
-    if (c->status != kRunning) continue;
-    if (mid) {
-      if (eval_guard(c, 1)) decide(lp, c);
-      continue;
-    }
+    const cptr<LpDev> L = cp(&cfg.lps[li]);
+    Ctl* const c = L->ctl;
+    const cptr<Ctl> g = cp(c);
+    if (g->status != kRunning) continue;
+    const bool due = eval_guard(g, mid);
     // step-rule factors for the attempts j = a0 + 1 .. a0 + kPowRing of this
     // launch sequence (which holds at most kPowRing attempts): the host
     // table's values while it covers j, else the same correctly rounded
     // powers computed here. The step decision reads the whole ring beside
     // its partial sums.
-    const int64_t a0 = c->attempts;
-    const DevParams* p = lp.prm;
-    for (int t = threadIdx.x; t < kPowRing; t += kDecBlock) {
-      const int64_t j = a0 + 1 + t;
-      if (j <= kPowTab) {
-        lp.pow_ring[t] = lp.pow_tab[j - 1];
-        lp.pow_ring[kPowRing + t] = lp.pow_tab[kPowTab + j - 1];
-      } else {
-        const double j1 = (double)j + 1.0;
-        lp.pow_ring[t] = crm::cr_pow(j1, -p->step_reduction);
-        lp.pow_ring[kPowRing + t] = crm::cr_pow(j1, -p->step_growth);
+    const int64_t a0 = g->attempts;
+    if (!mid) {
+      const DevParams* p = L->prm;
+      for (int k = t; k < kPowRing; k += kDecBlock) {
+        const int64_t j = a0 + 1 + k;
+        if (j <= kPowTab) {
+          gp(L->pow_ring)[k] = gp(L->pow_tab)[j - 1];
+          gp(L->pow_ring)[kPowRing + k] = gp(L->pow_tab)[kPowTab + j - 1];
+        } else {
+          const double j1 = (double)j + 1.0;
+          gp(L->pow_ring)[k] = crm::cr_pow(j1, -p->step_reduction);
+          gp(L->pow_ring)[kPowRing + k] = crm::cr_pow(j1, -p->step_growth);
+        }
       }
+      if (!due && t == 0) c->ring_base = a0;
     }
-    if (threadIdx.x == 0) c->ring_base = a0;
-    if (eval_guard(c, 0)) decide(lp, c);
+    if (!due) continue;
+    constexpr int kCtlWords = sizeof(Ctl) / 8, kPrmWords = sizeof(DevParams) / 8;
+    static_assert(kCtlWords + kPrmWords <= kDecBlock, "a word per thread");
+    if (t < kCtlWords)
+      reinterpret_cast<uint64_t*>(&s_ctl)[t] = gp(reinterpret_cast<const uint64_t*>(c))[t];
+    else if (t < kCtlWords + kPrmWords)
+      reinterpret_cast<uint64_t*>(&s_prm)[t - kCtlWords] =
+          gp(reinterpret_cast<const uint64_t*>(L->prm))[t - kCtlWords];
+    for (int q = wave; q < 2 * kEvT + 2 * kEvA; q += kDecBlock / 64) {
+      const bool ts = q < 2 * kEvT;
+      const int stride = ts ? L->ntiles_t : L->ntiles_a;
+      const DD v = wave_partials(gp((const double*)(ts ? L->part_t : L->part_a)) +
+                                     (size_t)(2 * (ts ? q : q - 2 * kEvT)) * stride,
+                                 stride, ts ? L->nslot_t : L->nslot_a);
+      if ((t & 63) == 0) s_sum[q] = dd_value(v);
+    }
+    __syncthreads();
+    if (t == 0) {
+      if (!mid) s_ctl.ring_base = a0;
+      decide_eval(&s_ctl, &s_prm, s_sum, s_sum + 2 * kEvT);
+    }
+    __syncthreads();
+    if (t < kCtlWords)
+      gp(reinterpret_cast<uint64_t*>(c))[t] = reinterpret_cast<const uint64_t*>(&s_ctl)[t];
+    __syncthreads();  // the next LP's words take the same LDS
   }
 }
 
@@ -2947,23 +2958,25 @@ __global__ __launch_bounds__(kDecBlock) void k_eval_decide(LaunchCfg cfg, int mi
 template <typename V>
 __global__ __launch_bounds__(kBlock) void k_apply(LaunchCfg cfg, int mid) {
   if (eval_step_skips(cfg, mid, false)) return;
-  auto body = [&](const WorkItem& it, bool tside) {
-    const Ctl* c = it.ctl;
+  auto body = [&](cptr<WorkItem> w, bool tside) {
+    if (w->lp < 0) return;
+    const WorkItem it = load_item(w);
+    const cptr<Ctl> c = cp(it.ctl);
     const bool restart = c->restart_pending != 0;
     const bool fin = c->finalize_avg != 0;
     if (!restart && !fin) return;
-    const LpDev& lp = cfg.lps[it.lp];
+    const cptr<LpDev> L = cp(&cfg.lps[it.lp]);
     const int cur = c->cur;
     const bool to_avg = restart ? (c->restart_avg != 0) : true;
-    const double w = c->restart_w;
+    const double wsum = c->restart_w;
     if (tside) {
-      V* x = static_cast<V*>(lp.x[cur]);
-      V* xs = static_cast<V*>(lp.xs[cur]);
-      V* xa = static_cast<V*>(lp.xa);
+      const gptr<V> x = gp(static_cast<V*>(L->x[cur]));
+      const gptr<V> xs = gp(static_cast<V*>(L->xs[cur]));
+      const gptr<V> xa = gp(static_cast<V*>(L->xa));
       for (int j = it.rb + threadIdx.x; j < it.re; j += kBlock) {
         V xv = x[j];
         if (to_avg) {
-          xv = (V)((double)xs[j] / w);
+          xv = (V)((double)xs[j] / wsum);
           x[j] = xv;
         }
         if (restart) {
@@ -2972,15 +2985,15 @@ __global__ __launch_bounds__(kBlock) void k_apply(LaunchCfg cfg, int mid) {
         }
       }
     } else {
-      V* y = static_cast<V*>(lp.y[cur]);
-      V* ys = static_cast<V*>(lp.ys[cur]);
-      V* ya = static_cast<V*>(lp.ya);
-      V* Ax = static_cast<V*>(lp.Ax[cur]);
-      const V* Axa = static_cast<const V*>(lp.Axa);
+      const gptr<V> y = gp(static_cast<V*>(L->y[cur]));
+      const gptr<V> ys = gp(static_cast<V*>(L->ys[cur]));
+      const gptr<V> ya = gp(static_cast<V*>(L->ya));
+      const gptr<V> Ax = gp(static_cast<V*>(L->Ax[cur]));
+      const gptr<const V> Axa = gp(static_cast<const V*>(L->Axa));
       for (int i = it.rb + threadIdx.x; i < it.re; i += kBlock) {
         V yv = y[i];
         if (to_avg) {
-          yv = (V)((double)ys[i] / w);
+          yv = (V)((double)ys[i] / wsum);
           y[i] = yv;
           if (restart) Ax[i] = Axa[i];
         }
@@ -2995,10 +3008,10 @@ __global__ __launch_bounds__(kBlock) void k_apply(LaunchCfg cfg, int mid) {
   const int b = blockIdx.x;
   if (b < st.grid)
     for (int wi = b * st.chunk; wi < (b + 1) * st.chunk; ++wi)
-      if (cfg.work_t[wi].lp >= 0) body(cfg.work_t[wi], true);
+      body(cp(cfg.work_t) + wi, true);
   if (b < sa.grid)
     for (int wi = b * sa.chunk; wi < (b + 1) * sa.chunk; ++wi)
-      if (cfg.work_a[wi].lp >= 0) body(cfg.work_a[wi], false);
+      body(cp(cfg.work_a) + wi, false);
 }
 
 // Gathers every LP's control block into one array, so the host reads the
@@ -3006,9 +3019,9 @@ __global__ __launch_bounds__(kBlock) void k_apply(LaunchCfg cfg, int mid) {
 __global__ __launch_bounds__(kBlock) void k_board(LaunchCfg cfg) {
   constexpr int kWords = sizeof(Ctl) / 8;
   static_assert(sizeof(Ctl) % 8 == 0, "Ctl is copied as 64-bit words");
-  const int nlps = uni(gp(cfg.counts)->nlps);
+  const int nlps = cp(cfg.counts)->nlps;
   for (int li = blockIdx.x; li < nlps; li += gridDim.x) {
-    const gptr<const uint64_t> src = gp(reinterpret_cast<const uint64_t*>(cfg.lps[li].ctl));
+    const gptr<const uint64_t> src = gp(reinterpret_cast<const uint64_t*>(cp(&cfg.lps[li])->ctl));
     const gptr<uint64_t> dst = gp(reinterpret_cast<uint64_t*>(cfg.board + li));
     for (int w = threadIdx.x; w < kWords; w += kBlock) dst[w] = src[w];
   }
@@ -3536,32 +3549,23 @@ int Kernels<V>::eval_products(const LaunchCfg& c, void* stream) {
   }
 }
 
-// The opening evaluation of a set with evaluation products: the streaming
-// kernel for the LPs that have them, the tile kernel for the others (not
-// launched when every LP has them).
+// An evaluation's sums. The opening one of a set with evaluation products:
+// the streaming kernels for the LPs that have them, the tile kernel for the
+// others (not launched when every LP has them).
 template <typename V>
-int Kernels<V>::eval_t(const LaunchCfg& c, void* stream, int mid) {
+int Kernels<V>::eval(const LaunchCfg& c, void* stream, int mid) {
   if constexpr (std::is_same<V, float>::value) {
     if (mid == 0 && c.evprod) {
       hipLaunchKernelGGL(k_eval_pre<true>, dim3(c.launch_t), dim3(kBlock), 0,
                          (hipStream_t)stream, c);
       if (launched()) return -1;
-      if (c.evprod == 2) return 0;
-    }
-  }
-  OPDHG_LAUNCH(k_eval_t<V>, c.launch_t, c, mid);
-}
-template <typename V>
-int Kernels<V>::eval_a(const LaunchCfg& c, void* stream, int mid) {
-  if constexpr (std::is_same<V, float>::value) {
-    if (mid == 0 && c.evprod) {
       hipLaunchKernelGGL(k_eval_pre<false>, dim3(c.launch_a), dim3(kBlock), 0,
                          (hipStream_t)stream, c);
       if (launched()) return -1;
       if (c.evprod == 2) return 0;
     }
   }
-  OPDHG_LAUNCH(k_eval_a<V>, c.launch_a, c, mid);
+  OPDHG_LAUNCH(k_eval<V>, c.launch_t + c.launch_a, c, mid);
 }
 template <typename V>
 int Kernels<V>::eval_decide(const LaunchCfg& c, void* stream, int mid) {

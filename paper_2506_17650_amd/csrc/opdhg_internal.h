@@ -414,8 +414,7 @@ struct Kernels {
   // (FP32; nothing to launch otherwise): tiles, windowed chunks and
   // segments of each side, one vector at a time
   static int eval_products(const LaunchCfg& c, void* stream);
-  static int eval_t(const LaunchCfg& c, void* stream, int mid);
-  static int eval_a(const LaunchCfg& c, void* stream, int mid);
+  static int eval(const LaunchCfg& c, void* stream, int mid);
   static int eval_decide(const LaunchCfg& c, void* stream, int mid);
   static int apply(const LaunchCfg& c, void* stream, int mid);
 };
