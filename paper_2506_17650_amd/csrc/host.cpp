@@ -1972,6 +1972,17 @@ int Group::replay() {
   return OPDHG_OK;
 }
 
+int Group::close() {
+  auto K = [&](auto tag) {
+    using V = decltype(tag);
+    return Kernels<V>::eval(cfg, stream, kClosing) | Kernels<V>::eval_decide(cfg, stream, kClosing) |
+           Kernels<V>::apply(cfg, stream, kClosing);
+  };
+  if ((prec == OPDHG_FP32 ? K(float{}) : K(double{})) || launch_board(cfg, stream, true))
+    return fail(OPDHG_ERR_DEVICE, std::string("kernel launch failed: ") + device_error_string());
+  return OPDHG_OK;
+}
+
 // ---------------------------------------------------------------------------
 // single-LP session
 // ---------------------------------------------------------------------------
@@ -2612,7 +2623,13 @@ int run_group(Group& grp, const std::vector<Ctl*>& d_ctls, std::vector<Ctl>& h_c
   HIP_TRY(hipStreamSynchronize(grp.stream));
   bool stop_sent = false;
   while (any_running) {
+    // (past the time limit the final evaluation is the stop request's)
+    const bool closing =
+        !grp.cfg.evprod && !stop_sent &&
+        std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() <= time_limit &&
+        std::any_of(h_ctls.begin(), h_ctls.end(), [&](const Ctl& c) { return grp.may_close(c); });
     int rc = grp.replay();
+    if (!rc && closing) rc = grp.close();
     if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(pinned, grp.cfg.board, sizeof(Ctl) * cnt, hipMemcpyDeviceToHost,
                            grp.stream));
@@ -2805,6 +2822,8 @@ static int session_from_prepared(opdhg_prepared& pr, void* d_workspace, size_t w
   S.direct = direct;
   if ((rc = S.grp.init(hip_stream, p->precision, direct))) return rc;
   S.grp.mid_every = mid_eval_every(p, 1);
+  S.grp.tol = p->tol;
+  S.grp.max_iter = p->max_iter;
   SlotImage img;
   if ((rc = upload_slot(S.ws, S.L, S.P, p->precision, S.grp.stream, img))) return rc;
   S.lpd = slot_pointers(S.ws, S.L, S.P);
@@ -3175,6 +3194,8 @@ static int batch_solve(opdhg_batch& B, void* d_workspace, size_t workspace_bytes
   Group grp;
   if ((rc = grp.init(hip_stream, p->precision))) return rc;
   grp.mid_every = mid_eval_every(p, count);
+  grp.tol = p->tol;
+  grp.max_iter = p->max_iter;
   std::vector<LpDev> lpd(count);
   {
     // The slots are filled and copied by several threads, each with its own

@@ -2654,6 +2654,7 @@ __device__ __forceinline__ void reduced_cost(double q, int8_t bf, double& lam, d
 // guarded step inside it) returns at once when its hint word is clear; the
 // first kernel of each step (clear_next) clears the next step's word.
 __device__ __forceinline__ bool eval_step_skips(const LaunchCfg& cfg, int mid, bool clear_next) {
+  if (mid == kClosing) return false;
   const gptr<Counts> cn = gp(const_cast<Counts*>(cfg.counts));
   if (clear_next && blockIdx.x == 0 && threadIdx.x == 0) cn->hint[(mid + 1) & 1] = 0;
   return mid != 0 && uni(cn->hint[mid & 1]) == 0;
@@ -3019,7 +3020,7 @@ __global__ __launch_bounds__(kBlock) void k_apply(LaunchCfg cfg, int mid) {
 
 // Gathers every LP's control block into one array, so the host reads the
 // state of a whole set with one copy.
-__global__ __launch_bounds__(kBlock) void k_board(LaunchCfg cfg) {
+__global__ __launch_bounds__(kBlock) void k_board(LaunchCfg cfg, int clear) {
   constexpr int kWords = sizeof(Ctl) / 8;
   static_assert(sizeof(Ctl) % 8 == 0, "Ctl is copied as 64-bit words");
   const int nlps = cp(cfg.counts)->nlps;
@@ -3027,6 +3028,11 @@ __global__ __launch_bounds__(kBlock) void k_board(LaunchCfg cfg) {
     const gptr<const uint64_t> src = gp(reinterpret_cast<const uint64_t*>(cp(&cfg.lps[li])->ctl));
     const gptr<uint64_t> dst = gp(reinterpret_cast<uint64_t*>(cfg.board + li));
     for (int w = threadIdx.x; w < kWords; w += kBlock) dst[w] = src[w];
+    if (clear && threadIdx.x == 0) {
+      Ctl* const c = cp(&cfg.lps[li])->ctl;
+      c->restart_pending = 0;
+      c->finalize_avg = 0;
+    }
   }
 }
 
@@ -3581,7 +3587,9 @@ int Kernels<V>::apply(const LaunchCfg& c, void* stream, int mid) {
   OPDHG_LAUNCH(k_apply<V>, c.launch_ta, c, mid);
 }
 
-int launch_board(const LaunchCfg& c, void* stream) { OPDHG_LAUNCH(k_board, c.launch_lp, c); }
+int launch_board(const LaunchCfg& c, void* stream, bool clear) {
+  OPDHG_LAUNCH(k_board, c.launch_lp, c, clear ? 1 : 0);
+}
 
 int prep_stats(const PrepCfg& c, void* stream, bool tside, int kind, double e) {
   const int rows = tside ? c.n : c.m;

@@ -252,6 +252,21 @@ struct Group {
   bool direct = false;
   int seq_attempts = 0;  // attempts per sequence (direct mode)
   int mid_every = kMidEvalEvery;
+  double tol = 0.0;      // of the set's LPs (see may_close)
+  int64_t max_iter = 0;
+  // An evaluation after a launch sequence, for LPs that fell due at its very
+  // end: an LP that finishes there needs no further sequence, whose slots
+  // would all be idle (64 empty attempts, 0.35 ms for one LP). Launched where
+  // the last evaluation says that an LP may finish: within a sequence of its
+  // iteration limit, or at no more than kCloseKkt times its tolerance. Not
+  // for sets with evaluation products, whose opening evaluation is the
+  // cheaper one.
+  static constexpr double kCloseKkt = 8.0;
+  bool may_close(const Ctl& c) const {
+    return c.status == kRunning && (c.k + kPowRing >= max_iter ||
+                                    (c.out_rel > 0.0 && c.out_rel <= kCloseKkt * tol));
+  }
+  int close();
   int init(void* stream, int prec, bool direct = false);
   int launch_side(bool primal, int force, hipStream_t s);
   // enqueue one launch sequence (evaluation, attempts, board) on s

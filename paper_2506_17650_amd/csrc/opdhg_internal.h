@@ -419,8 +419,15 @@ struct Kernels {
   static int apply(const LaunchCfg& c, void* stream, int mid);
 };
 
-// Copies every LP's Ctl into c.board (precision independent).
-int launch_board(const LaunchCfg& c, void* stream);
+// Copies every LP's Ctl into c.board (precision independent). clear: and
+// clears the flags of a restart or final copy just applied, which otherwise
+// the next attempt does (after a closing evaluation, whose next launch is
+// another evaluation).
+int launch_board(const LaunchCfg& c, void* stream, bool clear = false);
+
+// `mid` of the evaluation that closes a run (Group::close): as a guarded one,
+// without a hint.
+constexpr int kClosing = -1;
 
 // Device-side preparation of one slot (FP64 arithmetic, results in V):
 // the rescaling passes over the two stored CSR copies in device order,
