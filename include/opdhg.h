@@ -103,7 +103,8 @@ extern "C" {
                                < 0) */
 #define OPDHG_PREP_HOST 1   /* host threads (FP64) */
 #define OPDHG_PREP_DEVICE 2 /* device kernels (FP64), same results (with OPDHG_STEP_CONSTANT the
-                               power iteration runs on the device too) */
+                               power iteration runs on the device too; in FP64 it does so under
+                               OPDHG_PREP_AUTO for every size) */
 
 /* ---- restart scheme ---- */
 #define OPDHG_RESTART_ADAPTIVE 0 /* PDLP's KKT-based restarts, preconditioners kept (Section 3.2) */

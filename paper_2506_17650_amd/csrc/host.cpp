@@ -1307,6 +1307,9 @@ static void plan_one(const opdhg_params* p, Prepared& P) {
   P.one_threads = 64 * (int)std::min<int64_t>(units, kOneThreads / 64);
 }
 
+// Rounds of the power iteration that are launched one by one at most.
+constexpr int kPowerDevIters = 1000;
+
 int prepare(const opdhg_lp* lp, const opdhg_params* p, Prepared& out, bool structure_only) {
   out.m = lp->m;
   out.n = lp->n;
@@ -1392,7 +1395,12 @@ int prepare(const opdhg_lp* lp, const opdhg_params* p, Prepared& out, bool struc
   double spec = -1.0;
   if (!structure_only && !out.dprep) {
     rescale_with(lp, C, p->ruiz_iters, p->l2_rescale != 0, p->pc_beta, sval, out.dr, out.dc);
-    if (p->step_rule == OPDHG_STEP_CONSTANT)
+    // the constant step's norm: by kernels over the uploaded values, which
+    // are FP64 as here (13k entries and 200 rounds: 13 ms on the host, 2.7 ms
+    // there), or here
+    out.power_dev = p->step_rule == OPDHG_STEP_CONSTANT && p->prep == OPDHG_PREP_AUTO &&
+                    p->precision == OPDHG_FP64 && !out.host_power && p->power_iters <= kPowerDevIters;
+    if (p->step_rule == OPDHG_STEP_CONSTANT && !out.power_dev)
       spec = spectral_norm_with(lp, C, sval, p->power_iters, p->power_tol);
   }
   // values go to the device order: scaled on the host, or unscaled (raw)
@@ -2367,6 +2375,8 @@ static int device_prepare(uint8_t* base, const SlotLayout& L, Prepared& P, int p
   c.step_scale = P.prep_step_scale;
   c.power_tol = P.prep_power_tol;
   c.power_iters = P.prep_power_iters;
+  c.pw_grid = kPrepGrid;
+  c.pw_at = 4 * kPrepGrid + 3;
   int rc = 0;
   // Ruiz passes, the L2 pass, the Pock-Chambolle pass (Section 2), as on the host
   for (int it = 0; it < P.prep_ruiz && !rc; ++it)
@@ -2426,6 +2436,35 @@ static int device_structure(uint8_t* base, const SlotLayout& L, const Prepared& 
   return OPDHG_OK;
 }
 
+// The constant step's eta0 of an uploaded FP64 slot. The kernels scale by
+// T and Sigma, which are all 1 at the start; the products go to the copies of
+// x and y that the first attempt overwrites, the norm's partials and scalars
+// (2 G + 5 doubles, G workgroups of 32 rows of A^T) to the A^T side's
+// partials, which hold 32 doubles for each of its tiles of at most 256 rows.
+static int power_upload(const LpDev& d, const Prepared& P, hipStream_t stream) {
+  PrepCfg c{};
+  c.rp_a = d.rp_a;
+  c.ci_a = d.ci_a;
+  c.rp_t = d.rp_t;
+  c.ci_t = d.ci_t;
+  c.raw_a = static_cast<const double*>(d.va_a);
+  c.raw_t = static_cast<const double*>(d.va_t);
+  c.dr = static_cast<double*>(d.S);
+  c.dc = static_cast<double*>(d.T);
+  c.sr = static_cast<double*>(d.y[1]);
+  c.sc = static_cast<double*>(d.x[1]);
+  c.scr = d.part_t;
+  c.ctl = d.ctl;
+  c.m = d.m;
+  c.n = d.n;
+  c.step_scale = P.prep_step_scale;
+  c.power_tol = P.prep_power_tol;
+  c.power_iters = P.prep_power_iters;
+  c.pw_grid = std::max(1, std::min(kPrepGrid, (d.n + 31) / 32));
+  c.pw_at = 2 * c.pw_grid + 2;
+  return power_norm(c, stream);
+}
+
 int upload_slot(uint8_t* base, const SlotLayout& L, Prepared& P, int prec, hipStream_t stream,
                 SlotImage& img) {
   if (prec == OPDHG_FP32) slot_image<float>(L, P, img);
@@ -2444,6 +2483,8 @@ int upload_slot(uint8_t* base, const SlotLayout& L, Prepared& P, int prec, hipSt
     int rc = device_prepare(base, L, P, prec, stream);
     if (rc) return rc;
   }
+  if (P.power_dev && power_upload(slot_pointers(base, L, P), P, stream))
+    return fail(OPDHG_ERR_DEVICE, device_error_string());
   if (P.one && one_pack(slot_pointers(base, L, P), stream))
     return fail(OPDHG_ERR_DEVICE, device_error_string());
   return OPDHG_OK;

@@ -3141,54 +3141,91 @@ __global__ __launch_bounds__(kBlock) void k_prep_stats(PrepCfg a, int tside, int
 // Power iteration on A~^T A~ for |A~|_2 (vanilla PDHG's constant step
 // needs tau sigma |A~|_2^2 < 1, Section 2), round by round as on the host:
 // v_0 = 1 / sqrt(n); each round forms av = A~ v and w = A~^T av, each row's
-// products added one at a time in stored order in double-double and
-// rounded once, with the entries formed from the raw values and the
-// diagonals by the host's expression; then lam = |w| and v = w / lam. It
-// stops after power_iters rounds, when lam moves by at most
-// power_tol * lam, or when w = 0. av lives in sr, w in sc, and v = w / lam
-// is formed where it is read. The rounds after the stop return at once.
-constexpr int kPwLam = 4 * kPrepGrid + 3, kPwDone = kPwLam + 1, kPwZero = kPwLam + 2;
+// products added in double-double and rounded once, with the entries formed
+// from the raw values and the diagonals by the host's expression; then
+// lam = |w| and v = w / lam. It stops after power_iters rounds, when lam
+// moves by at most power_tol * lam, or when w = 0. av lives in sr, w in sc,
+// and v = w / lam is formed where it is read. The rounds after the stop
+// return at once.
+// lam, the stopping flag and the flag of w = 0 are scr[pw_at] on.
+
+// One row's sum of entry(value, col) products by eight lanes, in each of
+// them; a double-double's value does not depend on its order. A thread per
+// row took 11 us a round for 1203 rows of 11 entries, most of it its chain
+// of loads, 4.4 us so.
+constexpr int kPwLanes = 8;
+template <typename Entry>
+__device__ __forceinline__ double power_row(const int32_t* rp, const int32_t* ci,
+                                            const double* raw, int r, Entry&& entry) {
+  constexpr int U = 2;
+  const int e0 = gp(rp)[r], e1 = gp(rp)[r + 1];
+  DD acc = dd_zero();
+  for (int k = e0 + (int)(threadIdx.x & (kPwLanes - 1)); k < e1; k += U * kPwLanes) {
+    int c[U];
+    double a[U], s[U], x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int kk = min(k + u * kPwLanes, e1 - 1);
+      c[u] = gp(ci)[kk];
+      a[u] = gp(raw)[kk];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) entry(a[u], c[u], s[u], x[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (k + u * kPwLanes < e1) dd_add_prod(acc, s[u], x[u]);
+  }
+  acc = dd_merge(acc, dd_dpp<0x141>(acc));  // row_half_mirror
+  acc = dd_merge(acc, dd_dpp<0x4E>(acc));   // quad_perm:[2,3,0,1]
+  acc = dd_merge(acc, dd_dpp<0xB1>(acc));   // quad_perm:[1,0,3,2]
+  return dd_value(acc);
+}
 
 __global__ __launch_bounds__(kBlock) void k_power_av(PrepCfg a, int round) {
   if (round == 0) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-      a.scr[kPwLam] = 0.0;
-      a.scr[kPwDone] = 0.0;
-      a.scr[kPwZero] = 0.0;
+      a.scr[a.pw_at] = 0.0;
+      a.scr[a.pw_at + 1] = 0.0;
+      a.scr[a.pw_at + 2] = 0.0;
     }
-  } else if (a.scr[kPwDone] != 0.0) {
+  } else if (a.scr[a.pw_at + 1] != 0.0) {
     return;
   }
-  const double lam = round ? a.scr[kPwLam] : 1.0;
+  const double lam = round ? a.scr[a.pw_at] : 1.0;
   const double v0 = 1.0 / sqrt((double)a.n);
-  for (int r = blockIdx.x * kBlock + threadIdx.x; r < a.m; r += gridDim.x * kBlock) {
-    SeqDD acc;
-    for (int k = a.rp_a[r]; k < a.rp_a[r + 1]; ++k) {
-      const int c = a.ci_a[k];
-      const double sv = (a.raw_a[k] * a.dr[r]) * a.dc[c];
-      acc.add_prod(sv, round ? a.sc[c] / lam : v0);
-    }
-    a.sr[r] = acc.value();
+  const bool first = (threadIdx.x & (kPwLanes - 1)) == 0;
+  for (int r = (blockIdx.x * kBlock + threadIdx.x) / kPwLanes; r < a.m;
+       r += gridDim.x * kBlock / kPwLanes) {
+    const double dr = gp(a.dr)[r];
+    const double av =
+        power_row(a.rp_a, a.ci_a, a.raw_a, r, [&](double v, int c, double& s, double& x) {
+          s = (v * dr) * gp(a.dc)[c];
+          x = round ? gp(a.sc)[c] / lam : v0;
+        });
+    if (first) a.sr[r] = av;
   }
 }
 
 // w = A~^T av (sc), and per-workgroup double-double partials of |w|^2 in
-// scr (kPrepGrid workgroups).
+// scr (pw_grid workgroups).
 __global__ __launch_bounds__(kBlock) void k_power_w(PrepCfg a, int round) {
   __shared__ DD s_red[4];
-  if (round > 0 && a.scr[kPwDone] != 0.0) return;
+  if (round > 0 && a.scr[a.pw_at + 1] != 0.0) return;
   DD p[1];
   p[0] = dd_zero();
-  for (int j = blockIdx.x * kBlock + threadIdx.x; j < a.n; j += gridDim.x * kBlock) {
-    SeqDD acc;
-    for (int k = a.rp_t[j]; k < a.rp_t[j + 1]; ++k) {
-      const int i = a.ci_t[k];
-      const double sv = (a.raw_t[k] * a.dr[i]) * a.dc[j];
-      acc.add_prod(sv, a.sr[i]);
+  const bool first = (threadIdx.x & (kPwLanes - 1)) == 0;
+  for (int j = (blockIdx.x * kBlock + threadIdx.x) / kPwLanes; j < a.n;
+       j += gridDim.x * kBlock / kPwLanes) {
+    const double dc = gp(a.dc)[j];
+    const double w =
+        power_row(a.rp_t, a.ci_t, a.raw_t, j, [&](double v, int i, double& s, double& x) {
+          s = (v * gp(a.dr)[i]) * dc;
+          x = gp(a.sr)[i];
+        });
+    if (first) {
+      a.sc[j] = w;
+      dd_add_prod(p[0], w, w);
     }
-    const double w = acc.value();
-    a.sc[j] = w;
-    dd_add_prod(p[0], w, w);
   }
   const DD t = block_total<1, kBlock / 64, false>(p, s_red);
   if (threadIdx.x == 0) {
@@ -3197,31 +3234,35 @@ __global__ __launch_bounds__(kBlock) void k_power_w(PrepCfg a, int round) {
   }
 }
 
-// lam = |w| and the stopping test of the round (one thread).
+// lam = |w| and the stopping test of the round (one wave).
 __global__ void k_power_step(PrepCfg a, int round) {
-  if (threadIdx.x != 0 || (round > 0 && a.scr[kPwDone] != 0.0)) return;
-  DD t = dd_zero();
-  for (int g = 0; g < kPrepGrid; ++g) t = dd_merge(t, DD{a.scr[2 * g], a.scr[2 * g + 1]});
+  if (round > 0 && a.scr[a.pw_at + 1] != 0.0) return;
+  DD v[1] = {dd_zero()};
+  for (int g = threadIdx.x; g < a.pw_grid; g += 64)
+    v[0] = dd_merge(v[0], DD{a.scr[2 * g], a.scr[2 * g + 1]});
+  const DD t = wave_totals<1>(v);
+  if (threadIdx.x != 0) return;
   const double lam_new = sqrt(dd_value(t));
   if (lam_new == 0.0) {
-    a.scr[kPwZero] = 1.0;
-    a.scr[kPwDone] = 1.0;
+    a.scr[a.pw_at + 2] = 1.0;
+    a.scr[a.pw_at + 1] = 1.0;
     return;
   }
-  const double lam = a.scr[kPwLam];
+  const double lam = a.scr[a.pw_at];
   const bool done = fabs(lam_new - lam) <= a.power_tol * lam_new;
-  a.scr[kPwLam] = lam_new;
-  if (done) a.scr[kPwDone] = 1.0;
+  a.scr[a.pw_at] = lam_new;
+  if (done) a.scr[a.pw_at + 1] = 1.0;
 }
 
 // eta0 = step_scale / |A~|_2 (step_scale when the norm is 0) into the
-// control block and the scalars read back by the host.
+// control block and, of a slot prepared on the device, the scalars read back
+// by the host.
 __global__ void k_power_final(PrepCfg a) {
   if (threadIdx.x != 0) return;
-  const double nu = a.scr[kPwZero] != 0.0 ? 0.0 : sqrt(a.scr[kPwLam]);
+  const double nu = a.scr[a.pw_at + 2] != 0.0 ? 0.0 : sqrt(a.scr[a.pw_at]);
   const double eta0 = nu > 0.0 ? a.step_scale / nu : a.step_scale;
   a.ctl->eta = eta0;
-  a.scr[4 * kPrepGrid + 1] = eta0;
+  a.scr[a.pw_at - 2] = eta0;  // eta0's place of the preparation's scalars
 }
 
 // d_r /= sqrt(s_r), d_c /= sqrt(s_c), a zero statistic read as 1.
@@ -3609,11 +3650,12 @@ int struct_build(const StructCfg& c, void* stream) {
 }
 
 int power_norm(const PrepCfg& c, void* stream) {
-  const int ga = std::max(1, std::min(4096, (c.m + kBlock - 1) / kBlock));
+  const int64_t lanes = (int64_t)c.m * kPwLanes;
+  const int ga = (int)std::max<int64_t>(1, std::min<int64_t>(4096, (lanes + kBlock - 1) / kBlock));
   for (int r = 0; r < c.power_iters; ++r) {
     hipLaunchKernelGGL(k_power_av, dim3(ga), dim3(kBlock), 0, (hipStream_t)stream, c, r);
     if (launched()) return -1;
-    hipLaunchKernelGGL(k_power_w, dim3(kPrepGrid), dim3(kBlock), 0, (hipStream_t)stream, c, r);
+    hipLaunchKernelGGL(k_power_w, dim3(c.pw_grid), dim3(kBlock), 0, (hipStream_t)stream, c, r);
     if (launched()) return -1;
     hipLaunchKernelGGL(k_power_step, dim3(1), dim3(64), 0, (hipStream_t)stream, c, r);
     if (launched()) return -1;

@@ -118,6 +118,9 @@ struct Prepared {
   // the constant step: the power iteration's limits and eta0's scale
   bool prep_power = false;
   int prep_power_iters = 0;
+  // FP64 data scaled on the host, the power iteration after their upload
+  // (never with host_power, which the caller of prepare sets)
+  bool power_dev = false, host_power = false;
   double prep_power_tol = 0.0, prep_step_scale = 1.0;
   HostArray<double> raw_a, raw_t;
   std::vector<double> raw_b, raw_c, raw_l, raw_u;

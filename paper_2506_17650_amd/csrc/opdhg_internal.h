@@ -471,7 +471,10 @@ struct PrepCfg {
   // the constant step (vanilla PDHG): eta0 = step_scale / |A~|_2, the norm
   // from power_iters rounds of power iteration stopped at power_tol
   double step_scale, power_tol;
-  int32_t power_iters, pad;
+  int32_t power_iters;
+  // its workgroups, whose norm partials start scr, and the place of its
+  // scalars there (see k_power_av)
+  int32_t pw_grid, pw_at, pad;
 };
 constexpr int kPrepScr = 4 * kPrepGrid + 6;
 // Device-side structure of one slot (the host keeps only the row and

@@ -292,6 +292,7 @@ void ServerImpl::prep_loop() {
       if (j->cancel || j->state != JobState::kQueued) continue;
     }
     const opdhg_lp v = lp_view(*j);
+    j->P.host_power = true;  // on the preparing thread, not the scheduler's
     int rc = prepare(&v, &j->p, j->P, false);
     std::string msg = rc ? std::string(opdhg_last_error()) : std::string();
     if (!rc) {
