@@ -89,7 +89,8 @@ extern "C" {
                                      preconditioned step (eq. (6)); equal to PLAIN at T = Sigma = I */
 
 /* ---- windowed sparse products (FP32) ---- */
-#define OPDHG_WINDOWS_AUTO 0   /* a side whose rows give at least 128 windowed chunks uses them */
+#define OPDHG_WINDOWS_AUTO 0   /* a side whose rows give at least 128 windowed chunks uses them
+                                  (FP64: 256 chunks of 2048 rows) */
 #define OPDHG_WINDOWS_OFF 1    /* every row in tiles that gather from global memory; a small FP64
                                   LP too, whose attempts otherwise run in one workgroup (same
                                   results; without room for its packed entries in the workspace it
@@ -158,11 +159,15 @@ typedef struct opdhg_params {
   double step_scale;     /* constant step: eta = step_scale / estimate of |A~|_2 (> 0) */
   double power_tol;      /* power iteration stops when |A~|_2^2 moves less than this, relatively */
   int32_t step_norm;     /* OPDHG_STEP_NORM_*: norms of the adaptive rule's movement term */
-  int32_t windows;       /* OPDHG_WINDOWS_*: windows are FP32 only; the server never uses them */
+  int32_t windows;       /* OPDHG_WINDOWS_*: windows of FP32 LPs, and of FP64 LPs solved alone
+                            whose structure the device builds (see prep); the server's shared
+                            sequence never uses them */
   int32_t window_buckets; /* LDS window per pass in buckets of 1024 entries, 1..28, for chunks
                              of one pass and of several alike; 0: 28 per pass, and up to 38 for a
-                             chunk of one pass (its row sums then reuse the window's LDS) */
-  int32_t window_rows;   /* rows per windowed chunk, 1..10240; 0: picked from the side's size */
+                             chunk of one pass (its row sums then reuse the window's LDS). FP64:
+                             up to 19 */
+  int32_t window_rows;   /* rows per windowed chunk, 1..10240 (FP64: about, and up to 8192); 0:
+                             picked from the side's size */
   int32_t prep;          /* OPDHG_PREP_*: rescaling passes and scaled data on the host or device */
   int32_t eval_slots;    /* attempt slots between the guarded evaluation steps inside a launch
                             sequence (an LP that becomes due mid-sequence waits at most this

@@ -1890,7 +1890,8 @@ int Group::capture(int attempts_per_replay) {
 // two overlap on the device.
 int Group::launch_side(bool primal, int force, hipStream_t s) {
   const bool tiles = !cfg.step_fixed || (primal ? cfg.sgrid_t : cfg.sgrid_a) > 0;
-  const bool wins = (primal ? cfg.nwin_t : cfg.nwin_a) > 0;
+  const bool wins = (primal ? cfg.nwin_t : cfg.nwin_a) > 0 ||
+                    (primal ? cfg.w64_t.nch : cfg.w64_a.nch) > 0;
   auto tile = [&](hipStream_t q) {
     if (prec == OPDHG_FP32)
       return primal ? Kernels<float>::primal(cfg, q, force) : Kernels<float>::dual(cfg, q, force);
@@ -1933,7 +1934,7 @@ int Group::init(void* stream_, int prec_, bool direct_) {
   direct = direct_;
   // outside any capture: the LDS attribute of the windowed kernels and of
   // k_one (no allocation)
-  if (prec == OPDHG_FP32 ? window_kernels_ready() : one_kernel_ready())
+  if (prec == OPDHG_FP32 ? window_kernels_ready() : one_kernel_ready() | w64_kernels_ready())
     return fail(OPDHG_ERR_DEVICE, device_error_string());
   if (direct) return OPDHG_OK;
   HIP_TRY(hipStreamCreateWithFlags(&side_stream, hipStreamNonBlocking));
@@ -2154,6 +2155,7 @@ int write_tables(uint8_t* dst, const std::vector<LpDev>& lps_in,
   std::vector<WinItem> vt, va;
   std::vector<SegItem> gt, ga;
   const bool chunk_slots = prec == OPDHG_FP64;
+  cfg->w64_t = cfg->w64_a = Win64{};
   side_items(lps, preps, true, cap, &cfg->grid_t, &cfg->chunk_t, wt, false, chunk_slots);
   side_items(lps, preps, false, cap, &cfg->grid_a, &cfg->chunk_a, wa, false, chunk_slots);
   if (fixed_launch) {
@@ -2232,6 +2234,17 @@ int write_tables(uint8_t* dst, const std::vector<LpDev>& lps_in,
     };
     wins(true, vt);
     wins(false, va);
+    auto win64 = [&](const Win64& w, Win64& out, int32_t& ns) {
+      if (w.nch == 0) return;
+      out = w;
+      out.ctl = lps[0].ctl;
+      out.slot0 = ns;
+      ns += w.nch;
+    };
+    if (lps.size() == 1) {  // planned for sessions only
+      win64(preps[0]->w64_t, cfg->w64_t, lps[0].nslot_st);
+      win64(preps[0]->w64_a, cfg->w64_a, lps[0].nslot_sa);
+    }
     // segmented long rows, kSegRows per workgroup, take the slots after the chunks
     auto segs = [&](bool tside, std::vector<SegItem>& out) {
       for (size_t i = 0; i < lps.size(); ++i) {
@@ -2835,6 +2848,317 @@ static int prepared_make(const opdhg_lp* lp, const opdhg_params* p, opdhg_prepar
   return OPDHG_OK;
 }
 
+// Cuts a side's `rows` short rows into chunks of about `target` (at most
+// kW64Rows): row[0] = 0 .. row.back() = rows. Where every key (the highest
+// column of a row) before a row is below every key from it on, the rows on
+// the two sides gather from different places (two blocks of a block-angular
+// LP), and a chunk across would stage both: the rows are cut there first,
+// unless that leaves less than half a chunk, and the pieces evenly. Chunks
+// grow where there would be more than `most` (a last round of a few would
+// take as long as a full one).
+// range: the keys' lowest and highest per 64 rows. first: the first chunk of
+// each group of rows between two cuts, then the chunk count; bound: the keys
+// of group g are above bound[g] and at most bound[g + 1].
+static int cut_rows64(const std::vector<int2>& range, const int32_t* key, int64_t rows,
+                      int64_t target, int64_t most, hipStream_t stream, std::vector<int32_t>& row,
+                      std::vector<int32_t>& first, std::vector<int32_t>& bound) {
+  const int64_t ns = (int64_t)range.size();
+  std::vector<int32_t> below(ns + 1, -1), above(ns + 1, INT32_MAX);
+  for (int64_t s = 0; s < ns; ++s) below[s + 1] = std::max(below[s], range[s].y);
+  for (int64_t s = ns; s-- > 0;) above[s] = std::min(above[s + 1], range[s].x);
+  std::vector<int64_t> cuts;  // ascending, at least half a chunk apart
+  std::vector<int32_t> keys(kWinSlice);
+  int looks = 512;  // reads of a slice's keys, some 10 us each
+  bound.assign(1, -1);
+  auto add = [&](int64_t r, int32_t key_below) {
+    if (r - (cuts.empty() ? 0 : cuts.back()) < (target + 1) / 2) return;
+    cuts.push_back(r);
+    bound.push_back(key_below);
+  };
+  for (int64_t s = 0; s < ns; ++s) {
+    const int64_t a = s * kWinSlice, e = std::min(rows, a + kWinSlice);
+    if (s > 0 && below[s] < above[s]) add(a, below[s]);
+    // within the slice: only where its neighbours are apart
+    if (below[s] >= above[s + 1] || e - (cuts.empty() ? 0 : cuts.back()) < (target + 1) / 2)
+      continue;
+    if (below[s] < above[s] || below[s + 1] < above[s + 1]) continue;  // at one of its ends
+    if (--looks < 0) continue;
+    HIP_TRY(hipMemcpyAsync(keys.data(), key + a, 4 * (e - a), hipMemcpyDeviceToHost, stream));
+    HIP_TRY(hipStreamSynchronize(stream));
+    int32_t lowest[kWinSlice + 1], high = below[s];
+    lowest[e - a] = above[s + 1];
+    for (int64_t i = e - a; i-- > 0;)
+      lowest[i] = keys[i] < 0 ? lowest[i + 1] : std::min(lowest[i + 1], keys[i]);
+    for (int64_t i = 0; i + 1 < e - a; ++i) {
+      high = std::max(high, keys[i]);
+      if (high < lowest[i + 1]) add(a + i + 1, high);
+    }
+  }
+  if (!cuts.empty() && rows - cuts.back() < (target + 1) / 2) {
+    cuts.pop_back();
+    bound.pop_back();
+  }
+  cuts.push_back(rows);
+  bound.push_back(INT32_MAX);
+  row.assign(1, 0);
+  auto pieces = [&](int64_t len) {
+    return std::max((len + target / 2) / target, (len + kW64Rows - 1) / kW64Rows);
+  };
+  auto count = [&] {
+    int64_t n = 0, at = 0;
+    for (const int64_t c : cuts) n += pieces(c - at), at = c;
+    return n;
+  };
+  while (count() > most) {
+    if (target < kW64Rows) {
+      target = std::min<int64_t>(kW64Rows, target + target / 16 + 1);
+    } else {  // one round more
+      most += kWinRound;
+      target = (rows + most - 1) / most;
+    }
+  }
+  first.clear();
+  int64_t at = 0;
+  for (const int64_t c : cuts) {
+    const int64_t len = c - at;
+    first.push_back((int32_t)row.size() - 1);
+    const int64_t n = pieces(len);
+    for (int64_t i = 1; i <= n; ++i) row.push_back((int32_t)(at + len * i / n));
+    at = c;
+  }
+  first.push_back((int32_t)row.size() - 1);
+  return OPDHG_OK;
+}
+
+constexpr int64_t kW64MinRows = 2048;
+
+// Windows of the short rows of an uploaded FP64 LP (see Win64), for the
+// session's step kernels. The plan is made on the device, in the parts of the
+// slot that held the caller's arrays and the unscaled values, which nothing
+// reads after the preparation: it takes no memory of its own.
+// Automatic windows need 2048 rows a chunk at 256 chunks, no more staged
+// entries than 1.5 for each that gathers from them, and three quarters of the
+// side's entries. Measured on block-angular LPs of 30000 x 80000 a block and
+// 2000 linking rows (tiles, windows, us a side): A^T of 5 blocks 39.2, 65.5
+// (1568 rows, 1.2 staged), 12 blocks 61, 48.5 (3800, 0.8), 24 129, 81; A of 5
+// blocks 52, 70 (588 rows, 3.1 staged), 12 82, 83 (1428, 2.0), 24 134, 89 (3000,
+// 1.2), 64 310, 185 (7500, 0.6). Below, a chunk's few slices leave its waves
+// with nothing in flight, and what L1 holds of the vector is as near as LDS.
+static int plan_windows64(uint8_t* base, const SlotLayout& L, Prepared& P, const opdhg_params* p,
+                          hipStream_t stream) {
+  if (p->precision != OPDHG_FP64 || p->windows == OPDHG_WINDOWS_OFF || !P.dstruct || P.one)
+    return OPDHG_OK;
+  const bool always = p->windows == OPDHG_WINDOWS_ALWAYS;
+  const int per = p->window_buckets > 0
+                      ? std::min(kW64Buckets, p->window_buckets * (kWinParamBucket / kWinBucket))
+                      : kW64Buckets;
+  const LpDev d = slot_pointers(base, L, P);
+  const size_t nnz = (size_t)P.nnz;
+  // the caller's arrays and the entries' places, at the slot's end
+  size_t at = L.st_ci;
+  auto take = [&](size_t bytes) -> void* {
+    const size_t o = align_up(at);
+    if (o + bytes > L.base) return nullptr;
+    at = o + bytes;
+    return base + o;
+  };
+  struct Side {
+    Win64 w{};
+    int64_t ncols = 0, target = 0, most = 0, stride = 0;
+    int64_t before = 0;  // entries of the rows before the windowed ones
+    std::vector<int2> range;
+    std::vector<int32_t> row, first, bound, cnt;
+    std::vector<W64Chunk> chunk;
+    int32_t* key = nullptr;
+  } side[2];
+  const size_t tables = tables_bytes({&P}, grid_cap(p));  // the launch tables' room
+  const int64_t cap = p->tile_nnz > 0 ? std::min<int64_t>(p->tile_nnz, kTileCap) : kTileCap;
+  for (int k = 0; k < 2; ++k) {
+    const bool tside = k == 0;
+    const std::vector<int32_t>& rp = tside ? P.rp_t : P.rp_a;
+    const int64_t lo = tside ? P.cend_t[1] : P.cend_a[1], hi = tside ? P.n : P.m;
+    const int64_t ncols = tside ? P.m : P.n, nz = rp[hi] - rp[lo];
+    if (nz <= 0 || ncols > (int64_t)kW64Words * 32 * kWinBucket) continue;
+    if (!always && (nz < kWinMinChunks * kWinMinNnz || hi - lo < kWinRound * kW64MinRows)) continue;
+    Side& S = side[k];
+    Win64& w = S.w;
+    const int64_t round = kWinRound * ((hi - lo + kWinRound * kW64Rows - 1) / (kWinRound * kW64Rows));
+    S.target = std::min<int64_t>(kW64Rows, p->window_rows > 0
+                                               ? p->window_rows
+                                               : std::max<int64_t>(512, (hi - lo + round - 1) / round));
+    S.most = p->window_rows > 0 ? INT64_MAX : round;
+    S.ncols = ncols;
+    S.before = rp[lo];
+    // slots beside those of the tiles and segmented rows left
+    S.stride = (tside ? P.part_stride_t() : P.part_stride_a()) - lo -
+               (lo + kSegRows - 1) / kSegRows;
+    // values where the unscaled ones were; segments join the short rows' entries
+    w.val = reinterpret_cast<double*>(base + (tside ? L.raw_t : L.raw_a));
+    w.col = static_cast<uint16_t*>(take(2 * nnz));
+    S.key = static_cast<int32_t*>(take(4 * (hi - lo)));
+    const int64_t slices = (hi - lo + kWinSlice - 1) / kWinSlice;
+    int2* const range = static_cast<int2*>(take(sizeof(int2) * slices));
+    if (!w.col || !S.key || !range) continue;
+    w.rp = tside ? d.rp_t : d.rp_a;
+    w.ci = tside ? d.ci_t : d.ci_a;
+    w.va = static_cast<const double*>(tside ? d.va_t : d.va_a);
+    w.row0 = (int32_t)lo;
+    w.end = (int32_t)hi;
+    w.per = per;
+    w.last = (int32_t)(nz - 1);
+    S.range.resize(slices);
+    if (w64_keys(w, S.key, range, stream)) return fail(OPDHG_ERR_DEVICE, device_error_string());
+    HIP_TRY(hipMemcpyAsync(S.range.data(), range, sizeof(int2) * slices, hipMemcpyDeviceToHost,
+                           stream));
+  }
+  if (side[0].range.empty() && side[1].range.empty()) return OPDHG_OK;
+  HIP_TRY(hipStreamSynchronize(stream));
+  for (Side& S : side) {
+    if (S.range.empty()) continue;
+    Win64& w = S.w;
+    int rc = cut_rows64(S.range, S.key, w.end - w.row0, S.target, S.most, stream, S.row, S.first, S.bound);
+    if (rc) return rc;
+    const int64_t nch = (int64_t)S.row.size() - 1, groups = (int64_t)S.first.size() - 1;
+    if (nch > S.stride) continue;
+    w.nch = (int32_t)nch;
+    W64Chunk* const chunk = static_cast<W64Chunk*>(take(sizeof(W64Chunk) * nch));
+    w.cnt = static_cast<int32_t*>(take(4 * 2 * nch));
+    w.list = static_cast<uint16_t*>(take(2 * nch * kW64List));
+    w.base = static_cast<int32_t*>(take(4 * nch * kW64MaxPass * (kW64Slices + 1)));
+    if (!chunk || !w.cnt || !w.list || !w.base) continue;
+    w.chunk = chunk;
+    w.nseg_ent = w.cnt + nch;
+    // the chunks, with an even share of the group's segments each
+    // (worth it at four entries each)
+    const int64_t nseg = (int64_t)w.row0 * groups;
+    bool segs = w.row0 > 0 && (always || 4 * nseg <= S.before);
+    for (int64_t g = 0; g < groups; ++g) {
+      const int64_t c0 = S.first[g], n = S.first[g + 1] - c0;
+      for (int64_t i = 0; i < n; ++i) {
+        const int32_t a = S.row[c0 + i], e = S.row[c0 + i + 1];
+        const int32_t s0 = (int32_t)(w.row0 * i / n), s1 = (int32_t)(w.row0 * (i + 1) / n);
+        S.chunk.push_back(W64Chunk{w.row0 + a, e - a, s0, s1 - s0, (int32_t)g, 0, 0, 0});
+        segs = segs && e - a + s1 - s0 <= kW64Rows;
+      }
+    }
+    if (segs) {
+      int2* const seg = static_cast<int2*>(take(sizeof(int2) * nseg));
+      int32_t* const bound = static_cast<int32_t*>(take(4 * (groups + 1)));
+      int32_t* const ids = static_cast<int32_t*>(take(4 * nseg));
+      int32_t* const srow = static_cast<int32_t*>(take(4 * w.row0));
+      int32_t* const sptr = static_cast<int32_t*>(take(4 * (w.row0 + 1)));
+      w.segp = take(16 * nseg);
+      segs = seg && bound && ids && srow && sptr && w.segp;
+      w.seg = seg, w.bound = bound, w.sids = ids, w.srow = srow, w.sptr = sptr;
+    }
+    w.groups = segs ? (int32_t)groups : 0;
+    S.cnt.assign(2 * nch, 0);
+    HIP_TRY(hipMemcpyAsync(chunk, S.chunk.data(), sizeof(W64Chunk) * nch, hipMemcpyHostToDevice,
+                           stream));
+    if (w64_mark(w, S.ncols, stream)) return fail(OPDHG_ERR_DEVICE, device_error_string());
+    HIP_TRY(hipMemcpyAsync(S.cnt.data(), w.cnt, 4 * nch, hipMemcpyDeviceToHost, stream));
+  }
+  HIP_TRY(hipStreamSynchronize(stream));
+  for (Side& S : side) {
+    Win64& w = S.w;
+    if (S.cnt.empty()) continue;
+    const int64_t nch = w.nch;
+    const int64_t most = *std::max_element(S.cnt.begin(), S.cnt.begin() + nch);
+    if (most > (int64_t)kW64MaxPass * per) {
+      S.cnt.clear();
+      continue;
+    }
+    if (w.groups == 0) continue;
+    HIP_TRY(hipMemcpyAsync(const_cast<int32_t*>(w.bound), S.bound.data(), 4 * S.bound.size(),
+                           hipMemcpyHostToDevice, stream));
+    if (w64_segs(w, stream)) return fail(OPDHG_ERR_DEVICE, device_error_string());
+    HIP_TRY(hipMemcpyAsync(S.cnt.data() + nch, w.nseg_ent, 4 * nch, hipMemcpyDeviceToHost, stream));
+  }
+  HIP_TRY(hipStreamSynchronize(stream));
+  for (int k = 0; k < 2; ++k) {
+    const bool tside = k == 0;
+    Side& S = side[k];
+    Win64& w = S.w;
+    if (S.cnt.empty()) continue;
+    const int64_t nch = w.nch;
+    const std::vector<int32_t>& rp = tside ? P.rp_t : P.rp_a;
+    const int32_t* const ent = S.cnt.data() + nch;
+    if (std::any_of(ent, ent + nch, [](int32_t e) { return e < 0; })) w.groups = 0;
+    int64_t total = 0, rel = 0;
+    for (int64_t c = 0; c < nch; ++c) {
+      W64Chunk& h = S.chunk[c];
+      if (w.groups == 0) h.s0 = h.nseg = 0;
+      h.start = (int32_t)total;
+      h.rel = (int32_t)rel;
+      total += rp[h.r0 + h.nrow] - rp[h.r0] + (w.groups ? ent[c] : 0);
+      rel += (h.nrow + h.nseg + kWinSlice - 1) / kWinSlice * kWinSlice;
+    }
+    const int64_t passes = (*std::max_element(S.cnt.begin(), S.cnt.begin() + nch) + per - 1) / per;
+    const int64_t staged = kWinBucket * std::accumulate(S.cnt.begin(), S.cnt.begin() + nch, int64_t(0));
+    if (!always && (2 * staged > 3 * total || total < P.nnz / 4 * 3)) continue;
+    if (total < 1 || total > P.nnz || passes * rel > INT32_MAX) continue;
+    w.last = (int32_t)(total - 1);
+    w.relstride = (int32_t)rel;
+    w.rel = static_cast<uint16_t*>(take(2 * (size_t)(passes * rel)));
+    if (!w.rel) continue;
+    // what the step kernels take besides: segmented rows, or tiles
+    WinPlan& W = tside ? P.win_t : P.win_a;
+    std::vector<Tile>& tiles = tside ? P.stiles_t : P.stiles_a;
+    const std::vector<Tile> old_tiles = tiles;
+    const WinPlan old = W;
+    tiles.clear();
+    if (w.groups) {
+      W = WinPlan();
+      W.nsegs = w.row0 * w.groups;
+      W.sptr.push_back(0);
+      for (int32_t r = 0; r < w.row0; ++r) {
+        W.srow.push_back(r);
+        for (int32_t g = 0; g < w.groups; ++g) W.sids.push_back(r * w.groups + g);
+        W.sptr.push_back((int32_t)W.sids.size());
+      }
+    } else {
+      if (w.row0 > 0) tiles = build_tiles(rp.data(), w.row0, cap, p->lanes);
+      split_long_tiles(tiles, W);
+    }
+    if (tables_bytes({&P}, grid_cap(p)) > tables) {  // no room for the lists
+      tiles = old_tiles;
+      W = old;
+      continue;
+    }
+    HIP_TRY(hipMemcpyAsync(const_cast<W64Chunk*>(w.chunk), S.chunk.data(), sizeof(W64Chunk) * nch,
+                           hipMemcpyHostToDevice, stream));
+    if (w.groups) {
+      HIP_TRY(hipMemcpyAsync(const_cast<int32_t*>(w.srow), W.srow.data(), 4 * W.srow.size(),
+                             hipMemcpyHostToDevice, stream));
+      HIP_TRY(hipMemcpyAsync(const_cast<int32_t*>(w.sptr), W.sptr.data(), 4 * W.sptr.size(),
+                             hipMemcpyHostToDevice, stream));
+      HIP_TRY(hipMemcpyAsync(const_cast<int32_t*>(w.sids), W.sids.data(), 4 * W.sids.size(),
+                             hipMemcpyHostToDevice, stream));
+    }
+    if (w64_place(w, stream)) return fail(OPDHG_ERR_DEVICE, device_error_string());
+    (tside ? P.w64_t : P.w64_a) = w;
+  }
+  HIP_TRY(hipStreamSynchronize(stream));  // the lists are still being copied
+  return OPDHG_OK;
+}
+
+// The segmented rows that come with the windows take the place of the split
+// long rows.
+static void segments64(const Prepared& P, LpDev& d) {
+  if (P.w64_t.groups) {
+    d.segp_t = P.w64_t.segp;
+    d.srow_t = P.w64_t.srow;
+    d.sptr_t = P.w64_t.sptr;
+    d.sids_t = P.w64_t.sids;
+  }
+  if (P.w64_a.groups) {
+    d.segp_a = P.w64_a.segp;
+    d.srow_a = P.w64_a.srow;
+    d.sptr_a = P.w64_a.sptr;
+    d.sids_a = P.w64_a.sids;
+  }
+}
+
 static int session_from_prepared(opdhg_prepared& pr, void* d_workspace, size_t workspace_bytes,
                                  void* hip_stream, bool direct, opdhg_session** out) {
   if (!out) return fail(OPDHG_ERR_INVALID_ARGUMENT, "out is NULL");
@@ -2867,7 +3191,9 @@ static int session_from_prepared(opdhg_prepared& pr, void* d_workspace, size_t w
   S.grp.max_iter = p->max_iter;
   SlotImage img;
   if ((rc = upload_slot(S.ws, S.L, S.P, p->precision, S.grp.stream, img))) return rc;
+  if ((rc = plan_windows64(S.ws, S.L, S.P, p, S.grp.stream))) return rc;
   S.lpd = slot_pointers(S.ws, S.L, S.P);
+  segments64(S.P, S.lpd);
   S.d_tables = S.ws + S.L.total;
   std::vector<uint8_t> staging;
   int64_t nwt = 0, nwa = 0;

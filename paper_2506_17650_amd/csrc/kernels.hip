@@ -2169,6 +2169,378 @@ __global__ __launch_bounds__(kWinBlock) void k_dual_win(LaunchCfg cfg, int force
   win_chunk<false, DualStep<float>, DualPre<float>, 4>(cfg, cfg.win_a, cfg.nwin_a, force);
 }
 
+// Windowed step kernel (FP64): one workgroup per chunk (see Win64). In tiles
+// every gather of an FP64 vector is a request of a whole line from L2 for 8
+// bytes, 35 million a side on the block-angular LP of 64 blocks (1.92M x
+// 5.12M): 4.5 GB between L2 and L1, and neither other cache hints nor agent
+// scope made them smaller. From LDS they cost a bank access, and the rest is a
+// stream: A^T takes 189 us (290 in tiles; 680 MB, 3.6 TB/s), A 185 (310), an
+// attempt 396 (619). One workgroup of 16 waves owns the CU's LDS, so that
+// windows are as large and passes as few as they can be. Each row's entries lie
+// together, so a wave's loads hit a few lines between them and rows of any
+// length need no padding; the first four of the next slice are in flight while
+// a slice is summed (three or six, or loading the first epilogue before the
+// passes, made no difference; half the rows a chunk: 432 us an attempt).
+template <bool tside, typename Step, typename Pre, int NV>
+__device__ __forceinline__ void w64_chunk(const LaunchCfg& cfg, const Win64& W, int force) {
+  extern __shared__ double wlds64[];
+  double* const win = wlds64;
+  DD* const s_red = reinterpret_cast<DD*>(wlds64 + kW64Cap);
+  __shared__ uint16_t s_list[kW64List];
+  const int chi = chunk_index(gridDim.x);
+  if (chi < 0 || chi >= W.nch) return;
+  const int slot = W.slot0 + chi;
+  const int cnt = min(cp(W.cnt)[chi], kW64List);
+  Step st;
+  if (!st.begin(cfg, W.ctl, 0, slot == 0, force)) return;
+  const int t = threadIdx.x;
+  const int lane = t & (kWinSlice - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(t / kWinSlice);
+  const cptr<W64Chunk> ch = cp(W.chunk) + chi;
+  const int r0 = ch->r0, nrow = ch->nrow, rel0 = ch->rel;
+  const int nall = nrow + ch->nseg, seg0 = ch->s0 * W.groups + ch->group;
+  const int nsl = (nall + kWinSlice - 1) / kWinSlice;
+  const int npass = (cnt + W.per - 1) / W.per;
+  const int bper = (cnt + npass - 1) / max(npass, 1);
+  const int ncols = tside ? cp(st.lp)->m : cp(st.lp)->n;
+  const gptr<const double> vec = st.vecs[0];
+  const gptr<const double> wv = gp((const double*)W.val);
+  const gptr<const uint16_t> wc = gp((const uint16_t*)W.col);
+  const gptr<const uint16_t> wr = gp((const uint16_t*)W.rel);
+  const uint32_t last = (uint32_t)W.last;
+  if (t < cnt) s_list[t] = ldg(gp((const uint16_t*)W.list), (uint32_t)(chi * kW64List + t));
+  constexpr int kJ = kW64Slices / kWinWaves;  // slices of a wave
+  constexpr int kU = 4;                       // entries of a lane loaded together
+  Acc<double> acc[kJ];
+#pragma unroll
+  for (int j = 0; j < kJ; ++j) acc[j].zero();
+  for (int ps = 0; ps < npass; ++ps) {
+    const cptr<int32_t> base = cp(W.base) + (chi * kW64MaxPass + ps) * (kW64Slices + 1);
+    // where the lane's rows start in their slices
+    int rel[kJ];
+#pragma unroll
+    for (int j = 0; j < kJ; ++j) {
+      const int sj = min(wave + kWinWaves * j, nsl - 1);
+      rel[j] = ldg(wr, (uint32_t)(ps * W.relstride + rel0 + sj * kWinSlice + lane));
+    }
+    double vv[kU];
+    int cc[kU];
+    uint32_t k0 = 0;
+    int len = 0;
+    auto head = [&](int j, uint32_t& k, int& n, double (&v)[kU], int (&c)[kU]) {
+      const int sj = wave + kWinWaves * j;
+      const int b = base[sj], e = base[sj + 1];
+      const int nxt = __shfl_down(rel[j], 1, 64);
+      n = (lane == kWinSlice - 1 ? e - b : nxt) - rel[j];
+      k = (uint32_t)(b + rel[j]);
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const uint32_t i = min(k + u, last);
+        v[u] = ldg(wv, i);
+        c[u] = ldg(wc, i);
+      }
+    };
+    if (wave < nsl) head(0, k0, len, vv, cc);
+    lds_barrier();  // the list is in LDS; the last pass is done with the window
+    {
+      using f64x2 = double __attribute__((ext_vector_type(2)));
+      const int b0 = ps * bper;
+      const int n2 = (min(bper, cnt - b0) * kWinBucket) >> 1;
+      f64x2* const w2 = reinterpret_cast<f64x2*>(win);
+      for (int q = t; q < n2; q += 4 * kWinBlock) {  // four loads in flight
+        f64x2 a[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int i = min(q + u * kWinBlock, n2 - 1);
+          const int src = (int)s_list[b0 + (i >> 8)] * kWinBucket + ((2 * i) & (kWinBucket - 1));
+          // the vector's last bucket can end early, also inside a pair
+          const int s0 = min(src, ncols - 1 - (ncols > 1));
+          a[u] = *reinterpret_cast<gptr<const f64x2>>(vec + (s0 & ~1));
+          if (src + 1 >= ncols) {
+            a[u].x = ldg(vec, (uint32_t)min(src, ncols - 1));
+            a[u].y = 0.0;
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) w2[min(q + u * kWinBlock, n2 - 1)] = a[u];
+      }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int j = 0; j < kJ; ++j) {
+      if (wave + kWinWaves * j >= nsl) break;
+      uint32_t nk = 0;
+      int nlen = 0;
+      double nv[kU];
+      int nc[kU];
+      if (j + 1 < kJ && wave + kWinWaves * (j + 1) < nsl) head(j + 1, nk, nlen, nv, nc);
+      // products of entries past the row's end are masked out
+#pragma unroll
+      for (int u = 0; u < kU; ++u)
+        acc[j].add(Num<double>::mask(u < len, Num<double>::mul(vv[u], win[cc[u]])));
+      constexpr int kM = 2;
+      for (int k = kU; __any(k < len); k += kM) {
+        double v[kM];
+        int c[kM];
+#pragma unroll
+        for (int u = 0; u < kM; ++u) {
+          const uint32_t i = min(k0 + k + u, last);
+          v[u] = ldg(wv, i);
+          c[u] = ldg(wc, i);
+        }
+#pragma unroll
+        for (int u = 0; u < kM; ++u)
+          acc[j].add(Num<double>::mask(k + u < len, Num<double>::mul(v[u], win[c[u]])));
+      }
+      k0 = nk;
+      len = nlen;
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        vv[u] = nv[u];
+        cc[u] = nc[u];
+      }
+    }
+  }
+  DD p[NV];
+  dd_reset(p);
+  // the next row's vector loads go out before a row's epilogue
+  auto at = [&](int j) { return r0 + min((wave + kWinWaves * j) * kWinSlice + lane, nrow - 1); };
+  Pre q = st.load(at(0));
+#pragma unroll
+  for (int j = 0; j < kJ; ++j) {
+    if (wave + kWinWaves * j >= nsl) break;
+    Pre nq = st.load(at(j + 1 < kJ ? j + 1 : j));
+    const int r = (wave + kWinWaves * j) * kWinSlice + lane;
+    if (r < nrow) st.finish(r0 + r, acc[j].value(), q, p);
+    else if (r < nall) st.piece(seg0 + (r - nrow) * W.groups, acc[j]);
+    q = nq;
+  }
+  store_partials<NV>(st.part(), st.stride(), slot, block_total<NV, kWinWaves, false>(p, s_red));
+  st.commit();
+}
+
+__global__ __launch_bounds__(kWinBlock) void k_primal_w64(LaunchCfg cfg, int force) {
+  w64_chunk<true, PrimalStep<double>, PrimalPre<double>, 3>(cfg, cfg.w64_t, force);
+}
+
+__global__ __launch_bounds__(kWinBlock) void k_dual_w64(LaunchCfg cfg, int force) {
+  w64_chunk<false, DualStep<double>, DualPre<double>, 4>(cfg, cfg.w64_a, force);
+}
+
+// Planning of an FP64 side's windows, a workgroup per chunk (0.2 ms a side
+// at 31 million entries).
+// Exclusive sum of one value a thread over the workgroup; s_w: kWinWaves ints.
+__device__ __forceinline__ int block_scan(int v, int* s_w, int* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int inc = v;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(inc, off, 64);
+    if (lane >= off) inc += o;
+  }
+  lds_barrier();
+  if (lane == 63) s_w[wave] = inc;
+  lds_barrier();
+  int before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < kWinWaves; ++w) {
+    const int x = s_w[w];
+    before += w < wave ? x : 0;
+    all += x;
+  }
+  *total = all;
+  return before + inc - v;
+}
+
+__global__ __launch_bounds__(kBlock) void k_w64_keys(Win64 W, int32_t* key, int2* range) {
+  const int q = blockIdx.x * kBlock + threadIdx.x;
+  const int r = W.row0 + q;
+  int k = -1;
+  if (r < W.end) {
+    const int e = W.rp[r + 1];
+    for (int p = W.rp[r]; p < e; ++p) k = max(k, W.ci[p]);
+    key[q] = k;
+  }
+  int lo = k < 0 ? INT32_MAX : k, hi = k;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    lo = min(lo, __shfl_xor(lo, off, 64));
+    hi = max(hi, __shfl_xor(hi, off, 64));
+  }
+  if (r < W.end && (threadIdx.x & 63) == 0) range[q / 64] = int2{lo, hi};
+}
+
+// The buckets a chunk's entries lie in: a bitmap, then its set bits in order.
+__global__ __launch_bounds__(kWinBlock) void k_w64_mark(Win64 W) {
+  __shared__ uint32_t bm[kW64Words];
+  __shared__ int s_w[kWinWaves];
+  const int t = threadIdx.x, chi = blockIdx.x;
+  const int r0 = W.chunk[chi].r0, r1 = r0 + W.chunk[chi].nrow;
+  for (int q = t; q < kW64Words; q += kWinBlock) bm[q] = 0u;
+  lds_barrier();
+  const int e1 = W.rp[r1];
+  for (int k = W.rp[r0] + t; k < e1; k += kWinBlock) {
+    const int b = W.ci[k] / kWinBucket;
+    const uint32_t bit = 1u << (b & 31);
+    if (!(bm[b >> 5] & bit)) atomicOr(&bm[b >> 5], bit);
+  }
+  lds_barrier();
+  static_assert(kW64Words == 2 * kWinBlock, "two words a thread");
+  const uint32_t w0 = bm[2 * t], w1 = bm[2 * t + 1];
+  int total;
+  int pos = block_scan(__popc(w0) + __popc(w1), s_w, &total);
+  for (int h = 0; h < 2; ++h) {
+    for (uint32_t w = h ? w1 : w0; w; w &= w - 1, ++pos)
+      if (pos < kW64List)
+        W.list[chi * kW64List + pos] = (uint16_t)((2 * t + h) * 32 + __ffs(w) - 1);
+  }
+  if (t == 0) W.cnt[chi] = total;
+}
+
+// The chunk's segments: a row's entries are taken to ascend by column (they do
+// where its columns are of one class) and split at the groups' bounds by
+// binary search, the same one on both sides of a bound, so that segments whose
+// ends do not cross make up the row in any case. Segments that are longer
+// than a byte counts or leave the chunk's buckets are told to the host.
+__global__ __launch_bounds__(kWinBlock) void k_w64_segs(Win64 W) {
+  __shared__ uint32_t bm[kW64Words];
+  __shared__ int s_w[kWinWaves];
+  const int t = threadIdx.x, chi = blockIdx.x;
+  const W64Chunk ch = W.chunk[chi];
+  const int cnt = W.cnt[chi];
+  for (int q = t; q < kW64Words; q += kWinBlock) bm[q] = 0u;
+  lds_barrier();
+  if (t < cnt) {
+    const int b = W.list[chi * kW64List + t];
+    atomicOr(&bm[b >> 5], 1u << (b & 31));
+  }
+  lds_barrier();
+  int mine = 0, bad = 0;
+  for (int i = t; i < ch.nseg; i += kWinBlock) {
+    const int row = ch.s0 + i;
+    const int b = W.rp[row], e = W.rp[row + 1];
+    int2 k;
+    for (int h = 0; h < 2; ++h) {
+      const int g = ch.group + h;
+      int lo = b, hi = e;  // the first entry past bound[g]
+      if (g == 0) hi = b;
+      else if (g == W.groups) lo = e;
+      const int limit = W.bound[g];
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (W.ci[mid] > limit) hi = mid;
+        else lo = mid + 1;
+      }
+      (h ? k.y : k.x) = lo;
+    }
+    if (k.y < k.x || k.y - k.x > 255) {
+      bad = 1;
+      k.y = k.x;
+    }
+    for (int q = k.x; q < k.y; ++q) {
+      const int c = W.ci[q] / kWinBucket;
+      if (!(bm[c >> 5] >> (c & 31) & 1)) bad = 1;
+    }
+    W.seg[row * W.groups + ch.group] = k;
+    mine += k.y - k.x;
+  }
+  int all, total;
+  block_scan(bad, s_w, &all);
+  block_scan(mine, s_w, &total);
+  if (t == 0) W.nseg_ent[chi] = all ? -1 : total;
+}
+
+// A chunk's entries by pass: each row's entries are counted per pass (a byte
+// each), then placed.
+__global__ __launch_bounds__(kWinBlock) void k_w64_place(Win64 W) {
+  __shared__ uint32_t bm[kW64Words];
+  __shared__ int pre[kW64Words];
+  __shared__ int s_w[kWinWaves];
+  __shared__ int s_base[kW64MaxPass * kW64Slices];
+  const int t = threadIdx.x, chi = blockIdx.x;
+  const int lane = t & 63, wave = t >> 6;
+  const W64Chunk ch = W.chunk[chi];
+  const int r0 = ch.r0, nrow = ch.nrow, nall = ch.nrow + ch.nseg;
+  uint16_t* const rel = W.rel + ch.rel;
+  const int nsl = (nall + kWinSlice - 1) / kWinSlice;
+  auto entries = [&](int r) {
+    if (r < nrow) return int2{W.rp[r0 + r], W.rp[r0 + r + 1]};
+    if (r < nall) return W.seg[(ch.s0 + r - nrow) * W.groups + ch.group];
+    return int2{0, 0};
+  };
+  const int cnt = W.cnt[chi];
+  const int npass = (cnt + W.per - 1) / W.per;
+  const int bper = (cnt + npass - 1) / max(npass, 1);
+  for (int q = t; q < kW64Words; q += kWinBlock) bm[q] = 0u;
+  for (int q = t; q < kW64MaxPass * kW64Slices; q += kWinBlock) s_base[q] = 0;
+  lds_barrier();
+  if (t < cnt) {
+    const int b = W.list[chi * kW64List + t];
+    atomicOr(&bm[b >> 5], 1u << (b & 31));
+  }
+  lds_barrier();
+  int total;
+  const int c0 = __popc(bm[2 * t]);
+  const int first = block_scan(c0 + __popc(bm[2 * t + 1]), s_w, &total);
+  pre[2 * t] = first;
+  pre[2 * t + 1] = first + c0;
+  lds_barrier();
+  // the place of a column: its bucket's rank in the list, split by passes
+  auto place = [&](int col, int& ps) {
+    const int b = col / kWinBucket;
+    const int i = pre[b >> 5] + __popc(bm[b >> 5] & ((1u << (b & 31)) - 1u));
+    ps = i / bper;
+    return (i - ps * bper) * kWinBucket + (col & (kWinBucket - 1));
+  };
+  for (int s = wave; s < nsl; s += kWinWaves) {
+    const int r = s * kWinSlice + lane;
+    unsigned long long n = 0;
+    const int2 ke = entries(r);
+    for (int k = ke.x; k < ke.y; ++k) {
+      int ps;
+      place(W.ci[k], ps);
+      n += 1ull << (8 * ps);
+    }
+    for (int ps = 0; ps < npass; ++ps) {
+      const int v = (int)((n >> (8 * ps)) & 255);
+      int inc = v;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += o;
+      }
+      rel[(size_t)ps * W.relstride + r] = (uint16_t)(inc - v);
+      if (lane == 63) s_base[ps * nsl + s] = inc;
+    }
+  }
+  lds_barrier();
+  // slices of a pass after one another, passes after one another
+  const int mine = t < npass * nsl ? s_base[t] : 0;
+  const int b = ch.start + block_scan(mine, s_w, &total);
+  if (t < npass * nsl) {
+    s_base[t] = b;
+    const int ps = t / nsl, s = t - ps * nsl;
+    int32_t* const out = W.base + (size_t)(chi * kW64MaxPass + ps) * (kW64Slices + 1);
+    out[s] = b;
+    if (s == nsl - 1) out[nsl] = b + mine;
+  }
+  lds_barrier();
+  for (int s = wave; s < nsl; s += kWinWaves) {
+    const int r = s * kWinSlice + lane;
+    unsigned long long n = 0;
+    const int2 ke = entries(r);
+    for (int k = ke.x; k < ke.y; ++k) {
+      int ps;
+      const int c = place(W.ci[k], ps);
+      const int at = s_base[ps * nsl + s] + (int)rel[(size_t)ps * W.relstride + r] +
+                     (int)((n >> (8 * ps)) & 255);
+      n += 1ull << (8 * ps);
+      W.val[at] = W.va[k];
+      W.col[at] = (uint16_t)c;
+    }
+  }
+}
+
 // What the step decision needs from an LP's record, in scalar registers:
 // pointers, partial-slot counts and the copies of the parameters it reads.
 using DecideLp = DecideRec;
@@ -3484,12 +3856,49 @@ static int win_attributes() {
 
 int window_kernels_ready() { return win_attributes(); }
 
+int w64_kernels_ready() {
+  static std::once_flag once;
+  static hipError_t err = hipSuccess;
+  std::call_once(once, [] {
+    for (const void* f : {(const void*)k_primal_w64, (const void*)k_dual_w64})
+      if (err == hipSuccess)
+        err = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kW64Lds);
+  });
+  if (err != hipSuccess) g_last_device_error = err;
+  return err == hipSuccess ? 0 : -1;
+}
+
+int w64_keys(const Win64& w, int32_t* key, int2* range, void* stream) {
+  hipLaunchKernelGGL(k_w64_keys, dim3((w.end - w.row0 + kBlock - 1) / kBlock), dim3(kBlock), 0,
+                     (hipStream_t)stream, w, key, range);
+  return launched();
+}
+
+int w64_mark(const Win64& w, int64_t ncols, void* stream) {
+  if (w.nch <= 0 || ncols > (int64_t)kW64Words * 32 * kWinBucket) return -1;
+  hipLaunchKernelGGL(k_w64_mark, dim3(w.nch), dim3(kWinBlock), 0, (hipStream_t)stream, w);
+  return launched();
+}
+
+int w64_segs(const Win64& w, void* stream) {
+  hipLaunchKernelGGL(k_w64_segs, dim3(w.nch), dim3(kWinBlock), 0, (hipStream_t)stream, w);
+  return launched();
+}
+
+int w64_place(const Win64& w, void* stream) {
+  hipLaunchKernelGGL(k_w64_place, dim3(w.nch), dim3(kWinBlock), 0, (hipStream_t)stream, w);
+  return launched();
+}
+
 template <typename V>
 int Kernels<V>::primal_win(const LaunchCfg& c, void* stream, int force) {
-  if (c.nwin_t <= 0) return 0;
   if constexpr (!std::is_same<V, float>::value) {
-    return -1;  // windowed chunks are planned for FP32 only
+    if (c.w64_t.nch <= 0) return 0;
+    hipLaunchKernelGGL(k_primal_w64, dim3((c.w64_t.nch + 7) / 8 * 8), dim3(kWinBlock), kW64Lds,
+                       (hipStream_t)stream, c, force);
+    return launched();
   } else {
+    if (c.nwin_t <= 0) return 0;
     if (win_attributes()) return -1;
     hipLaunchKernelGGL(k_primal_win, dim3(c.nwin_t), dim3(kWinBlock), kWinLds,
                        (hipStream_t)stream, c, force);
@@ -3498,10 +3907,13 @@ int Kernels<V>::primal_win(const LaunchCfg& c, void* stream, int force) {
 }
 template <typename V>
 int Kernels<V>::dual_win(const LaunchCfg& c, void* stream, int force) {
-  if (c.nwin_a <= 0) return 0;
   if constexpr (!std::is_same<V, float>::value) {
-    return -1;
+    if (c.w64_a.nch <= 0) return 0;
+    hipLaunchKernelGGL(k_dual_w64, dim3((c.w64_a.nch + 7) / 8 * 8), dim3(kWinBlock), kW64Lds,
+                       (hipStream_t)stream, c, force);
+    return launched();
   } else {
+    if (c.nwin_a <= 0) return 0;
     if (win_attributes()) return -1;
     hipLaunchKernelGGL(k_dual_win, dim3(c.nwin_a), dim3(kWinBlock), kWinLds,
                        (hipStream_t)stream, c, force);

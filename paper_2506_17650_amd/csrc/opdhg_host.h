@@ -135,6 +135,7 @@ struct Prepared {
   // a small FP64 LP (see kOneThreads): its attempts can run in k_one, with
   // this many threads
   bool one = false;
+  Win64 w64_t{}, w64_a{};  // windowed rows of an FP64 session, once planned (plan_windows64)
   int one_threads = 0;
   // partial slots per side: evaluation tiles, or step tiles plus windowed chunks
   int64_t part_stride_t() const {

@@ -183,6 +183,67 @@ struct SegItem {
   int32_t s0, s1;
 };
 
+// Windowed sparse products of one FP64 LP, planned on the device (Win64).
+// The short rows (at most 32 entries) of a side are taken in chunks of up to
+// kW64Rows consecutive ones by workgroups of kWinBlock threads, a row per lane.
+// A chunk stages the kWinBucket-entry buckets of the vector that it gathers from,
+// listed in ascending order, in passes of equal numbers of buckets, and its
+// entries are stored again by pass, in each pass by row: the entries of a row
+// lie side by side, a wavefront's rows after one another. Row sums stay in
+// registers from pass to pass; double-double sums do not depend on the order,
+// so a side has the same results in windows as in tiles.
+constexpr int kW64Rows = 8192;     // eight rows a thread
+constexpr int kW64Slices = kW64Rows / kWinSlice;
+constexpr int kW64Buckets = 38;    // a pass's window: 152 KiB of LDS
+constexpr int kW64Cap = kW64Buckets * kWinBucket;
+constexpr int kW64MaxPass = 8;     // pass counts of a row pack into 64 bits
+constexpr int kW64List = kW64MaxPass * kW64Buckets;
+constexpr int kW64Words = 2048;    // bitmap words over a side's buckets
+constexpr size_t kW64Lds = (size_t)kW64Cap * 8 + kWinWaves * 4 * 16;
+// The other rows of the side are split by column into one segment per group of
+// chunks, where the chunks allow it (k_w64_segs): segment rows follow a chunk's
+// own, their sums go to the finishing kernel. Elsewhere they stay in tiles.
+struct W64Chunk {
+  int32_t r0, nrow;    // rows [r0, r0 + nrow)
+  int32_t s0, nseg;    // segments of the rows [s0, s0 + nseg)
+  int32_t group;       // and this group (segment id: row * groups + group)
+  int32_t start;       // the chunk's first entry
+  int32_t rel;         // its first row in a pass of rel (slices are whole)
+  int32_t pad;
+};
+struct Win64 {
+  Ctl* ctl;
+  double* val;         // entries: value, place in the pass's window
+  uint16_t* col;
+  uint16_t* rel;       // first entry of a row in a pass, from its slice's first
+  int32_t* base;       // first entry of a slice in a pass; (kW64MaxPass, kW64Slices + 1) a chunk
+  uint16_t* list;      // kW64List buckets a chunk
+  int32_t* cnt;        // buckets in use
+  int32_t* nseg_ent;   // entries of the chunk's segments; -1: not all in its buckets
+  const W64Chunk* chunk;
+  int2* seg;           // each segment's entries [x, y) of the CSR
+  const int32_t* bound;  // groups + 1: group g takes columns (bound[g], bound[g + 1]]
+  const int32_t* rp;   // the side's CSR
+  const int32_t* ci;
+  const double* va;
+  int32_t nch;         // chunks (0: no windows)
+  int32_t row0, end;   // rows [row0, end)
+  int32_t per;         // buckets of a pass at most
+  int32_t relstride;   // of a pass in rel
+  int32_t last;        // last entry
+  int32_t slot0;       // partial slot of the first chunk
+  int32_t groups;      // 0: no segments
+  void* segp;          // the segments as LpDev has them
+  const int32_t *srow, *sptr, *sids;
+};
+// The highest column of each row (key; -1 without entries), and the lowest
+// and highest of each 64 rows' keys (rows without entries aside); the buckets
+// of each chunk (list, cnt); the segments; the entries by pass.
+int w64_keys(const Win64& w, int32_t* key, int2* range, void* stream);
+int w64_mark(const Win64& w, int64_t ncols, void* stream);
+int w64_segs(const Win64& w, void* stream);
+int w64_place(const Win64& w, void* stream);
+
 // Small FP64 LPs: one workgroup runs a launch sequence's attempts by itself
 // (k_one), with y and x' in its LDS. Rows of up to 32 entries (the short
 // class) take a lane each; their entries are stored again in slices of 64
@@ -381,6 +442,7 @@ struct LaunchCfg {
   const SegItem* seg_t;  // segmented long rows, finished after the windowed chunks
   const SegItem* seg_a;
   int nseg_t, nseg_a;
+  Win64 w64_t, w64_a;  // windowed rows of a set of one FP64 LP
   // a fixed set of one LP: its decision record comes with the launch
   // arguments, so the decision kernel skips reading the LP table
   int solo;
@@ -397,7 +459,7 @@ struct Kernels {
   static int init_products(const LaunchCfg& c, void* stream);
   static int primal(const LaunchCfg& c, void* stream, int force);
   static int dual(const LaunchCfg& c, void* stream, int force = 0);
-  // windowed chunks of each side (FP32 only; nothing to launch when the set has none)
+  // windowed chunks of each side (nothing to launch when the set has none)
   static int primal_win(const LaunchCfg& c, void* stream, int force);
   static int dual_win(const LaunchCfg& c, void* stream, int force = 0);
   // segmented long rows: adds each row's segment partials and runs its epilogue
@@ -522,6 +584,8 @@ template <typename V>
 int prep_finish(const PrepCfg& c, void* stream);
 // Sets the windowed kernels' LDS attribute (once per process); 0 on success.
 int window_kernels_ready();
+// And of the FP64 ones.
+int w64_kernels_ready();
 
 const char* device_error_string();
 
