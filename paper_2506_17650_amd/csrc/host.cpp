@@ -2393,14 +2393,11 @@ static int device_prepare(uint8_t* base, const SlotLayout& L, Prepared& P, int p
   int rc = 0;
   // Ruiz passes, the L2 pass, the Pock-Chambolle pass (Section 2), as on the host
   for (int it = 0; it < P.prep_ruiz && !rc; ++it)
-    rc = prep_stats(c, stream, false, 0, 0.0) | prep_stats(c, stream, true, 0, 0.0) |
-         prep_apply(c, stream);
+    rc = prep_stats(c, stream, 0) | prep_apply(c, stream);
   if (!rc && P.prep_l2)
-    rc = prep_stats(c, stream, false, 2, 0.0) | prep_stats(c, stream, true, 2, 0.0) |
-         prep_apply(c, stream);
+    rc = prep_stats(c, stream, 2) | prep_apply(c, stream);
   if (!rc && P.prep_beta >= 0.0)
-    rc = prep_stats(c, stream, false, 1, P.prep_beta) |
-         prep_stats(c, stream, true, 1, 2.0 - P.prep_beta) | prep_apply(c, stream);
+    rc = prep_stats(c, stream, 1, P.prep_beta, 2.0 - P.prep_beta) | prep_apply(c, stream);
   if (!rc) rc = prec == OPDHG_FP32 ? prep_finish<float>(c, stream) : prep_finish<double>(c, stream);
   // the constant step's eta0 from the power iteration (after the scalars,
   // whose eta0 it replaces)

@@ -3445,68 +3445,72 @@ int Kernels<V>::dual(const LaunchCfg& c, void* stream, int force) {
 // device-side preparation (FP64)
 // ---------------------------------------------------------------------------
 
-// The host's double-double accumulator, operation for operation (the
-// preparation on either side gives the same bits).
-struct SeqDD {
-  double hi = 0.0, lo = 0.0;
-  __device__ __forceinline__ void add(double x) {
-    const double s = hi + x;
-    const double bb = s - hi;
-    lo += (hi - (s - bb)) + (x - bb);
-    hi = s;
+// Row statistics of |a~_ij| = |a_ij| d_r,i d_c,j over the rows of A (sr) and of
+// A^T (sc, a row per column of A): eight lanes a row, a wave for the long ones
+// (the first rows in device order). Maxima and double-double sums do not depend
+// on the order. A pass over rows of 10 entries is a chain of loads per row, of
+// which a lane has one or two here: 13 us for both sides of LPs of 140k
+// entries (34 for two launches of a thread per row), 0.7 ms for a sum over 35
+// million with rows of 2140 (3.6 ms for A alone).
+constexpr int kPrepLanes = 8;
+template <int LANES>
+__device__ __forceinline__ void stat_row(const PrepCfg& a, bool tside, int r, int kind, double e) {
+  constexpr int U = 2;
+  const gptr<const int32_t> rp = gp(tside ? a.rp_t : a.rp_a);
+  const gptr<const int32_t> ci = gp(tside ? a.ci_t : a.ci_a);
+  const gptr<const double> raw = gp(tside ? a.raw_t : a.raw_a);
+  const gptr<const double> other = gp(tside ? (const double*)a.dr : (const double*)a.dc);
+  const double own = gp(tside ? a.dc : a.dr)[r];
+  const int e0 = rp[r], e1 = rp[r + 1];
+  double mx = 0.0;
+  DD acc = dd_zero();
+  for (int k = e0 + (int)(threadIdx.x & (LANES - 1)); k < e1; k += U * LANES) {
+    int c[U];
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int kk = min(k + u * LANES, e1 - 1);
+      c[u] = ci[kk];
+      v[u] = fabs(raw[kk]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const double o = other[c[u]];
+      const double x = tside ? (v[u] * o) * own : (v[u] * own) * o;
+      if (kind == 0) {
+        mx = mx < x ? x : mx;  // (the last entry again past the row's end)
+      } else if (k + u * LANES < e1) {
+        dd_add(acc, kind == 2 ? x * x : (e == 1.0 ? x : pow(x, e)));
+      }
+    }
   }
-  __device__ __forceinline__ void add_prod(double a, double b) {
-    const double p = a * b;
-    add(p);
-    lo += fma(a, b, -p);
+#pragma unroll
+  for (int off = LANES / 2; off > 0; off >>= 1) {
+    if (kind == 0) {
+      const double o = __shfl_xor(mx, off, 64);
+      mx = mx < o ? o : mx;
+    } else {
+      acc = dd_merge(acc, dd_shfl_xor(acc, off));
+    }
   }
-  __device__ __forceinline__ double value() const { return hi + lo; }
-};
+  if ((threadIdx.x & (LANES - 1)) == 0)
+    gp(tside ? a.sc : a.sr)[r] =
+        kind == 0 ? mx : (kind == 1 ? dd_value(acc) : sqrt(dd_value(acc)));
+}
 
-// Row statistics of |a~_ij| = |a_ij| d_r,i d_c,j over the rows of A
-// (tside 0) or of A^T (tside 1, a row per column of A), one thread per row,
-// entries in stored order.
-__global__ __launch_bounds__(kBlock) void k_prep_stats(PrepCfg a, int tside, int kind, double e) {
-  const int rows = tside ? a.n : a.m;
-  const int32_t* rp = tside ? a.rp_t : a.rp_a;
-  const int32_t* ci = tside ? a.ci_t : a.ci_a;
-  const double* raw = tside ? a.raw_t : a.raw_a;
-  double* out = tside ? a.sc : a.sr;
-  auto scaled = [&](int r, int k) {
-    const double v = fabs(raw[k]);
-    return tside ? (v * a.dr[ci[k]]) * a.dc[r] : (v * a.dr[r]) * a.dc[ci[k]];
-  };
-  int r_first = 0;
-  if (kind == 0) {
-    // maxima do not depend on the order: a wave per long row (the first
-    // rows in device order), then a thread per row for the rest
-    const int nlong = tside ? a.nlong_t : a.nlong_a;
-    const int lane = threadIdx.x & 63;
-    const int nw = gridDim.x * (kBlock / 64);
-    for (int r = (blockIdx.x * kBlock + threadIdx.x) >> 6; r < nlong; r += nw) {
-      double mx = 0.0;
-      for (int k = rp[r] + lane; k < rp[r + 1]; k += 64) {
-        const double x = scaled(r, k);
-        mx = mx < x ? x : mx;
-      }
-      for (int off = 32; off > 0; off >>= 1) {
-        const double o = __shfl_xor(mx, off, 64);
-        mx = mx < o ? o : mx;
-      }
-      if (lane == 0) out[r] = mx;
-    }
-    r_first = nlong;
+// ea, et: the exponents of kind 1 on the two sides.
+__global__ __launch_bounds__(kBlock) void k_prep_stats(PrepCfg a, int kind, double ea, double et) {
+  const int t0 = blockIdx.x * kBlock + threadIdx.x, nt = gridDim.x * kBlock;
+  const int nlong = a.nlong_a + a.nlong_t;
+  for (int q = t0 / 64; q < nlong; q += nt / 64) {
+    const bool tside = q >= a.nlong_a;
+    stat_row<64>(a, tside, tside ? q - a.nlong_a : q, kind, tside ? et : ea);
   }
-  for (int r = r_first + blockIdx.x * kBlock + threadIdx.x; r < rows; r += gridDim.x * kBlock) {
-    double mx = 0.0;
-    SeqDD acc;
-    for (int k = rp[r]; k < rp[r + 1]; ++k) {
-      const double x = scaled(r, k);
-      if (kind == 0) mx = mx < x ? x : mx;
-      else if (kind == 1) acc.add(e == 1.0 ? x : pow(x, e));
-      else acc.add(x * x);
-    }
-    out[r] = kind == 0 ? mx : (kind == 1 ? acc.value() : sqrt(acc.value()));
+  const int ra = a.m - a.nlong_a, rt = a.n - a.nlong_t;
+  for (int q = t0 / kPrepLanes; q < ra + rt; q += nt / kPrepLanes) {
+    const bool tside = q >= ra;
+    stat_row<kPrepLanes>(a, tside, tside ? a.nlong_t + q - ra : a.nlong_a + q, kind,
+                         tside ? et : ea);
   }
 }
 
@@ -3653,7 +3657,7 @@ __global__ __launch_bounds__(kBlock) void k_prep_apply(PrepCfg a) {
 
 // Rows of A to device order; each entry also to its A^T row's cursor. A
 // wave per row of more than 256 entries (the first rows in device order),
-// a thread per row for the rest.
+// eight lanes per row for the rest.
 __global__ __launch_bounds__(kBlock) void k_struct_rows(StructCfg a) {
   auto entry = [&](int i, int64_t k, int d) {
     const int j2 = a.inv_t[a.src_ci[k]];
@@ -3670,19 +3674,20 @@ __global__ __launch_bounds__(kBlock) void k_struct_rows(StructCfg a) {
     const int64_t s = a.src_rp[i], e = a.src_rp[i + 1];
     for (int64_t k = s + lane; k < e; k += 64) entry(i, k, a.rp_a[i2] + (int)(k - s));
   }
-  const int t0 = blockIdx.x * kBlock + threadIdx.x, nt = gridDim.x * kBlock;
-  for (int i2 = a.nlong_a + t0; i2 < a.m; i2 += nt) {
+  const int g0 = (blockIdx.x * kBlock + threadIdx.x) / kPrepLanes;
+  const int ng = gridDim.x * kBlock / kPrepLanes, l8 = threadIdx.x & (kPrepLanes - 1);
+  for (int i2 = a.nlong_a + g0; i2 < a.m; i2 += ng) {
     const int i = a.perm_a[i2];
     const int64_t s = a.src_rp[i], e = a.src_rp[i + 1];
     const int d0 = a.rp_a[i2];
-    for (int64_t k = s; k < e; ++k) entry(i, k, d0 + (int)(k - s));
+    for (int64_t k = s + l8; k < e; k += kPrepLanes) entry(i, k, d0 + (int)(k - s));
   }
 }
 
 // Each A^T row in ascending original row: an entry's place is its rank
 // among the row's original rows (distinct: A has no duplicate entry). A
 // wave per row of more than 32 entries (first in device order), with the
-// row's original rows in LDS; a thread per row for the rest.
+// row's original rows in LDS; eight lanes per row for the rest.
 __global__ __launch_bounds__(kBlock) void k_struct_cols(StructCfg a) {
   __shared__ int32_t s_rows[kBlock / 64][kStructMaxCol];
   auto place = [&](int s, int p, int ip, int rank) {
@@ -3714,9 +3719,10 @@ __global__ __launch_bounds__(kBlock) void k_struct_cols(StructCfg a) {
     __builtin_amdgcn_wave_barrier();
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
   }
-  for (int j2 = a.nmed_t + blockIdx.x * kBlock + threadIdx.x; j2 < a.n; j2 += gridDim.x * kBlock) {
+  const int ng = gridDim.x * kBlock / kPrepLanes, l8 = threadIdx.x & (kPrepLanes - 1);
+  for (int j2 = a.nmed_t + (blockIdx.x * kBlock + threadIdx.x) / kPrepLanes; j2 < a.n; j2 += ng) {
     const int s = a.rp_t[j2], e = a.rp_t[j2 + 1];
-    for (int p = s; p < e; ++p) {
+    for (int p = s + l8; p < e; p += kPrepLanes) {
       const int ip = a.tmp_i[p];
       int rank = 0;
       for (int q = s; q < e; ++q) rank += a.tmp_i[q] < ip ? 1 : 0;
@@ -3743,19 +3749,20 @@ __global__ __launch_bounds__(kBlock) void k_prep_values(PrepCfg a) {
     mx = mx < bits ? bits : mx;
   };
   auto put_t = [&](int r, int k) { vt[k] = (V)((a.raw_t[k] * a.dr[a.ci_t[k]]) * a.dc[r]); };
-  // a wave per long row (the first rows in device order), a thread per row
+  // a wave per long row (the first rows in device order), eight lanes per row
   // for the rest; every entry is computed on its own
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, l8 = threadIdx.x & (kPrepLanes - 1);
   const int w0 = (blockIdx.x * kBlock + threadIdx.x) >> 6, nw = gridDim.x * (kBlock / 64);
-  const int t0 = blockIdx.x * kBlock + threadIdx.x, nt = gridDim.x * kBlock;
+  const int g0 = (blockIdx.x * kBlock + threadIdx.x) / kPrepLanes;
+  const int ng = gridDim.x * (kBlock / kPrepLanes);
   for (int r = w0; r < a.nlong_a; r += nw)
     for (int k = a.rp_a[r] + lane; k < a.rp_a[r + 1]; k += 64) put_a(r, k);
-  for (int r = a.nlong_a + t0; r < a.m; r += nt)
-    for (int k = a.rp_a[r]; k < a.rp_a[r + 1]; ++k) put_a(r, k);
+  for (int r = a.nlong_a + g0; r < a.m; r += ng)
+    for (int k = a.rp_a[r] + l8; k < a.rp_a[r + 1]; k += kPrepLanes) put_a(r, k);
   for (int r = w0; r < a.nlong_t; r += nw)
     for (int k = a.rp_t[r] + lane; k < a.rp_t[r + 1]; k += 64) put_t(r, k);
-  for (int r = a.nlong_t + t0; r < a.n; r += nt)
-    for (int k = a.rp_t[r]; k < a.rp_t[r + 1]; ++k) put_t(r, k);
+  for (int r = a.nlong_t + g0; r < a.n; r += ng)
+    for (int k = a.rp_t[r] + l8; k < a.rp_t[r + 1]; k += kPrepLanes) put_t(r, k);
   atomicMax(&s_max, mx);
   __syncthreads();
   if (threadIdx.x == 0)
@@ -3819,12 +3826,18 @@ __global__ __launch_bounds__(kBlock) void k_prep_scalars(PrepCfg a) {
   DD p[2];
   p[0] = dd_zero();
   p[1] = dd_zero();
+  static_assert(kPrepGrid == kBlock, "a thread per workgroup's partials");
+  {
+    const gptr<const double> g = gp((const double*)a.scr) + 4 * threadIdx.x;
+    p[0] = DD{g[0], g[1]};
+    p[1] = DD{g[2], g[3]};
+  }
+  __shared__ DD s_norm[2];
+  const DD t = block_total<2, kBlock / 64, false>(p, s_red);
+  if (threadIdx.x < 2) s_norm[threadIdx.x] = t;
+  lds_barrier();
   if (threadIdx.x == 0) {
-    for (int g = 0; g < kPrepGrid; ++g) {
-      p[0] = dd_merge(p[0], DD{a.scr[4 * g + 0], a.scr[4 * g + 1]});
-      p[1] = dd_merge(p[1], DD{a.scr[4 * g + 2], a.scr[4 * g + 3]});
-    }
-    const double bsn = sqrt(dd_value(p[0])), csn = sqrt(dd_value(p[1]));
+    const double bsn = sqrt(dd_value(s_norm[0])), csn = sqrt(dd_value(s_norm[1]));
     const double amax = __longlong_as_double(
         (long long)*reinterpret_cast<const unsigned long long*>(a.scr + 4 * kPrepGrid));
     const double eta0 = amax > 0.0 ? 1.0 / amax : 1.0;
@@ -3834,7 +3847,6 @@ __global__ __launch_bounds__(kBlock) void k_prep_scalars(PrepCfg a) {
     a.scr[4 * kPrepGrid + 1] = eta0;
     a.scr[4 * kPrepGrid + 2] = om0;
   }
-  (void)s_red;
 }
 
 // The windowed kernels take more than the default 64 KiB of LDS; the
@@ -4044,19 +4056,25 @@ int launch_board(const LaunchCfg& c, void* stream, bool clear) {
   OPDHG_LAUNCH(k_board, c.launch_lp, c, clear ? 1 : 0);
 }
 
-int prep_stats(const PrepCfg& c, void* stream, bool tside, int kind, double e) {
-  const int rows = tside ? c.n : c.m;
-  const int grid = std::max(1, std::min(4096, (rows + kBlock - 1) / kBlock));
-  hipLaunchKernelGGL(k_prep_stats, dim3(grid), dim3(kBlock), 0, (hipStream_t)stream, c,
-                     tside ? 1 : 0, kind, e);
+static int prep_grid(const PrepCfg& c) {
+  const int64_t lanes = ((int64_t)c.m + c.n) * kPrepLanes;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(4096, (lanes + kBlock - 1) / kBlock));
+}
+
+int prep_stats(const PrepCfg& c, void* stream, int kind, double ea, double et) {
+  hipLaunchKernelGGL(k_prep_stats, dim3(prep_grid(c)), dim3(kBlock), 0, (hipStream_t)stream, c,
+                     kind, ea, et);
   return launched();
 }
 
 int struct_build(const StructCfg& c, void* stream) {
-  const int g1 = std::max(1, std::min(4096, (c.m + kBlock - 1) / kBlock));
+  auto grid = [](int64_t rows) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(4096, (rows * kPrepLanes + kBlock - 1) / kBlock));
+  };
+  const int g1 = grid(c.m);
   hipLaunchKernelGGL(k_struct_rows, dim3(g1), dim3(kBlock), 0, (hipStream_t)stream, c);
   if (launched()) return -1;
-  const int g2 = std::max(1, std::min(4096, (c.n + kBlock - 1) / kBlock));
+  const int g2 = grid(c.n);
   hipLaunchKernelGGL(k_struct_cols, dim3(g2), dim3(kBlock), 0, (hipStream_t)stream, c);
   return launched();
 }
@@ -4084,9 +4102,7 @@ int prep_apply(const PrepCfg& c, void* stream) {
 
 template <typename V>
 int prep_finish(const PrepCfg& c, void* stream) {
-  const int rows = std::max(c.m, c.n);
-  const int grid = std::max(1, std::min(4096, (rows + kBlock - 1) / kBlock));
-  hipLaunchKernelGGL(k_prep_values<V>, dim3(grid), dim3(kBlock), 0, (hipStream_t)stream, c);
+  hipLaunchKernelGGL(k_prep_values<V>, dim3(prep_grid(c)), dim3(kBlock), 0, (hipStream_t)stream, c);
   if (launched()) return -1;
   hipLaunchKernelGGL(k_prep_vectors<V>, dim3(kPrepGrid), dim3(kBlock), 0, (hipStream_t)stream, c);
   if (launched()) return -1;

@@ -576,8 +576,8 @@ int one_pack(const LpDev& lp, void* stream);
 // Sets k_one's LDS attribute (once per process); 0 on success.
 int one_kernel_ready();
 
-// kind 0: maxima of |a~|, 1: sums of |a~|^e, 2: L2 norms
-int prep_stats(const PrepCfg& c, void* stream, bool tside, int kind, double e);
+// of both sides; kind 0: maxima of |a~|, 1: sums of |a~|^ea and |a~|^et, 2: L2 norms
+int prep_stats(const PrepCfg& c, void* stream, int kind, double ea = 0.0, double et = 0.0);
 int prep_apply(const PrepCfg& c, void* stream);  // dr /= sqrt(sr), dc /= sqrt(sc)
 int power_norm(const PrepCfg& c, void* stream);  // the constant step's eta0 (power iteration)
 template <typename V>
