@@ -11,7 +11,10 @@
 // LDS, all loads of the tile in flight together; then each row is reduced
 // from LDS by a group of `lanes` threads and finished by a per-row epilogue
 // whose vector loads were issued before the stream. A row longer than
-// kTileCap is a tile of its own, reduced by the whole workgroup.
+// kTileCap is a tile of its own, reduced by the whole workgroup. Rows that
+// gather from a small part of the vector are taken by windowed kernels instead,
+// which stage that part in LDS (FP32: k_*_win; an FP64 LP alone: k_*_w64), and
+// all attempts of a small FP64 LP by one workgroup (k_one).
 //
 // The epilogues fuse the method's vector work into the sparse products and
 // accumulate FP64 partial sums per thread. The FP32 step kernels store one
@@ -2003,7 +2006,7 @@ __device__ __forceinline__ void win_chunk(const LaunchCfg& cfg, const WinItem* l
 // Segmented long rows: kSegLanes lanes per row. Lane l merges the row's
 // partials l, l + kSegLanes, ... in order, the lanes combine in a fixed
 // shuffle tree, and the row's first lane runs the row epilogue. The
-// partials come from windowed chunks (FP32) and from the pieces of rows
+// partials come from windowed chunks and from the pieces of rows
 // split in tiles (float in FP32 runs, double-double in FP64 runs).
 template <typename V, typename Step, typename Pre, int NV>
 __device__ __forceinline__ void seg_rows(const LaunchCfg& cfg, const SegItem* list, int nitems,
@@ -2327,8 +2330,8 @@ __global__ __launch_bounds__(kWinBlock) void k_dual_w64(LaunchCfg cfg, int force
   w64_chunk<false, DualStep<double>, DualPre<double>, 4>(cfg, cfg.w64_a, force);
 }
 
-// Planning of an FP64 side's windows, a workgroup per chunk (0.2 ms a side
-// at 31 million entries).
+// Planning of an FP64 side's windows, a workgroup per chunk (1.2 ms for the
+// A side of the 64 blocks, 0.5 for A^T, nearly all of it k_w64_place).
 // Exclusive sum of one value a thread over the workgroup; s_w: kWinWaves ints.
 __device__ __forceinline__ int block_scan(int v, int* s_w, int* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
