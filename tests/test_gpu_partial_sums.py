@@ -51,7 +51,8 @@ def _same(a, b):
 @pytest.mark.parametrize("tile,wg", [(64, 1), (64, 3), (64, 40), (256, 8), (16, 2), (0, 2048)])
 def test_chunking_changes_no_bit(P, solved, tile, wg):
     lps, ref = solved
-    p = lib_params(P, default_params(**OP), tile_nnz=tile, workgroups=wg)
+    p = lib_params(P, default_params(**OP), tile_nnz=tile, workgroups=wg,
+                   windows=P.OPDHG_WINDOWS_OFF)
     for lp, r in zip(lps, ref):
         _same(P.opdhg_solve(lp, p), r)
     for got, r in zip(P.opdhg_solve_batch(lps, p), ref):

@@ -2,7 +2,9 @@
 depend on the order): chunks of one slice of 64 rows up to several, a last
 chunk and a last slice that are not full, one to eight passes, a last bucket
 that ends early (odd and even widths, a single column of it), sides without
-short rows, rows without entries, long and medium rows beside the windows."""
+short rows, rows without entries, long and medium rows beside the windows:
+as segments, or in tiles where their columns do not ascend (blocks with
+columns of two classes); a band, where rows may be cut anywhere."""
 
 import numpy as np
 import pytest
@@ -33,7 +35,30 @@ def _empty_rows(lp, rows):
     return lp
 
 
+def _from_rows(seed, n, rows):
+    """A random LP's data around rows of the given columns."""
+    r = np.random.default_rng(seed)
+    lp = random_lp(seed, len(rows), n, degree=("fixed", 1))
+    lp.row_ptr = np.concatenate([[0], np.cumsum([len(c) for c in rows])]).astype(np.int64)
+    lp.col_idx = np.concatenate(rows).astype(np.int32)
+    lp.val = r.standard_normal(lp.col_idx.size)
+    return lp
+
+
+def _two_classes():
+    r = np.random.default_rng(11)
+    rows = [[] for _ in range(4 * 700)]
+    for j in range(4 * 1500):
+        b = j // 1500
+        for i in r.choice(700, 40 if j % 30 == 0 else 5, replace=False):
+            rows[b * 700 + i].append(j)
+    rows += [np.sort(r.choice(6000, 420, replace=False)) for _ in range(6)]
+    return _from_rows(11, 6000, rows)
+
+
 LPS = {
+    "two_classes": _two_classes,
+    "band": lambda: _from_rows(12, 9005, [np.arange(2 * i, 2 * i + 1 + i % 14) for i in range(4490)]),
     "block": lambda: block_angular_lp(3, blocks=9, block_rows=411, block_cols=1097, col_degree=6,
                                       link_rows=20, link_nnz_per_row=500),
     "block_3": lambda: block_angular_lp(9, blocks=3, block_rows=1200, block_cols=3001, col_degree=5,
