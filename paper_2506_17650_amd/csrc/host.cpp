@@ -2261,6 +2261,9 @@ int write_tables(uint8_t* dst, const std::vector<LpDev>& lps_in,
     segs(true, gt);
     segs(false, ga);
   }
+  for (const LpDev& d : lps)
+    if (std::max(d.nslot_t, d.nslot_st) > d.ntiles_t || std::max(d.nslot_a, d.nslot_sa) > d.ntiles_a)
+      return fail(OPDHG_ERR_DEVICE, "internal error: more partial sums than slots");
   cfg->nwin_t = (int)vt.size();
   cfg->nwin_a = (int)va.size();
   cfg->nseg_t = (int)gt.size();
@@ -2929,6 +2932,42 @@ static int cut_rows64(const std::vector<int2>& range, const int32_t* key, int64_
 
 constexpr int64_t kW64MinRows = 2048;
 
+// Gives a side's short rows to the windows w: the step kernels then take the
+// rows before them as segments (w.groups), or as tiles, the longest split in
+// pieces. Every tile, chunk and workgroup of segmented rows may store a partial
+// of its own: they must fit the slots that the side was laid out with, since
+// one past the last is the first of the next quantity's.
+bool take_windows64(Prepared& P, bool tside, const Win64& w, int64_t cap, int lanes,
+                    int64_t workgroups, size_t tables) {
+  WinPlan& W = tside ? P.win_t : P.win_a;
+  std::vector<Tile>& tiles = tside ? P.stiles_t : P.stiles_a;
+  auto slots = [&] { return tside ? P.part_stride_t() : P.part_stride_a(); };
+  const int64_t laid_out = slots();
+  const std::vector<Tile> old_tiles = tiles;
+  const WinPlan old = W;
+  tiles.clear();
+  if (w.groups) {
+    W = WinPlan();
+    W.nsegs = w.row0 * w.groups;
+    W.sptr.push_back(0);
+    for (int32_t r = 0; r < w.row0; ++r) {
+      W.srow.push_back(r);
+      for (int32_t g = 0; g < w.groups; ++g) W.sids.push_back(r * w.groups + g);
+      W.sptr.push_back((int32_t)W.sids.size());
+    }
+  } else {
+    const std::vector<int32_t>& rp = tside ? P.rp_t : P.rp_a;
+    if (w.row0 > 0) tiles = build_tiles(rp.data(), w.row0, cap, lanes);
+    split_long_tiles(tiles, W);
+  }
+  (tside ? P.w64_t : P.w64_a) = w;
+  if (slots() <= laid_out && tables_bytes({&P}, workgroups) <= tables) return true;
+  tiles = old_tiles;
+  W = old;
+  (tside ? P.w64_t : P.w64_a) = Win64{};
+  return false;
+}
+
 // Windows of the short rows of an uploaded FP64 LP (see Win64), for the
 // session's step kernels. The plan is made on the device, in the parts of the
 // slot that held the caller's arrays and the unscaled values, which nothing
@@ -2986,7 +3025,8 @@ static int plan_windows64(uint8_t* base, const SlotLayout& L, Prepared& P, const
     S.most = p->window_rows > 0 ? INT64_MAX : round;
     S.ncols = ncols;
     S.before = rp[lo];
-    // slots beside those of the tiles and segmented rows left
+    // slots beside those of the tiles and segmented rows left, before rows
+    // are split (take_windows64 counts what is there in the end)
     S.stride = (tside ? P.part_stride_t() : P.part_stride_a()) - lo -
                (lo + kSegRows - 1) / kSegRows;
     // values where the unscaled ones were; segments join the short rows' entries
@@ -3098,33 +3138,11 @@ static int plan_windows64(uint8_t* base, const SlotLayout& L, Prepared& P, const
     w.relstride = (int32_t)rel;
     w.rel = static_cast<uint16_t*>(take(2 * (size_t)(passes * rel)));
     if (!w.rel) continue;
-    // what the step kernels take besides: segmented rows, or tiles
-    WinPlan& W = tside ? P.win_t : P.win_a;
-    std::vector<Tile>& tiles = tside ? P.stiles_t : P.stiles_a;
-    const std::vector<Tile> old_tiles = tiles;
-    const WinPlan old = W;
-    tiles.clear();
-    if (w.groups) {
-      W = WinPlan();
-      W.nsegs = w.row0 * w.groups;
-      W.sptr.push_back(0);
-      for (int32_t r = 0; r < w.row0; ++r) {
-        W.srow.push_back(r);
-        for (int32_t g = 0; g < w.groups; ++g) W.sids.push_back(r * w.groups + g);
-        W.sptr.push_back((int32_t)W.sids.size());
-      }
-    } else {
-      if (w.row0 > 0) tiles = build_tiles(rp.data(), w.row0, cap, p->lanes);
-      split_long_tiles(tiles, W);
-    }
-    if (tables_bytes({&P}, grid_cap(p)) > tables) {  // no room for the lists
-      tiles = old_tiles;
-      W = old;
-      continue;
-    }
+    if (!take_windows64(P, tside, w, cap, p->lanes, grid_cap(p), tables)) continue;
     HIP_TRY(hipMemcpyAsync(const_cast<W64Chunk*>(w.chunk), S.chunk.data(), sizeof(W64Chunk) * nch,
                            hipMemcpyHostToDevice, stream));
     if (w.groups) {
+      const WinPlan& W = tside ? P.win_t : P.win_a;
       HIP_TRY(hipMemcpyAsync(const_cast<int32_t*>(w.srow), W.srow.data(), 4 * W.srow.size(),
                              hipMemcpyHostToDevice, stream));
       HIP_TRY(hipMemcpyAsync(const_cast<int32_t*>(w.sptr), W.sptr.data(), 4 * W.sptr.size(),
@@ -3133,7 +3151,6 @@ static int plan_windows64(uint8_t* base, const SlotLayout& L, Prepared& P, const
                              hipMemcpyHostToDevice, stream));
     }
     if (w64_place(w, stream)) return fail(OPDHG_ERR_DEVICE, device_error_string());
-    (tside ? P.w64_t : P.w64_a) = w;
   }
   HIP_TRY(hipStreamSynchronize(stream));  // the lists are still being copied
   return OPDHG_OK;

@@ -137,14 +137,18 @@ struct Prepared {
   bool one = false;
   Win64 w64_t{}, w64_a{};  // windowed rows of an FP64 session, once planned (plan_windows64)
   int one_threads = 0;
-  // partial slots per side: evaluation tiles, or step tiles plus windowed chunks
+  // partial slots per side: evaluation tiles, or step tiles plus windowed
+  // chunks (FP64's are planned after the layout, within its slots) and the
+  // workgroups of segmented rows
   int64_t part_stride_t() const {
     return (int64_t)std::max(tiles_t.size(),
-                             stiles_t.size() + win_t.chunks() + win_t.seg_items());
+                             stiles_t.size() + win_t.chunks() + win_t.seg_items() +
+                                 (size_t)w64_t.nch);
   }
   int64_t part_stride_a() const {
     return (int64_t)std::max(tiles_a.size(),
-                             stiles_a.size() + win_a.chunks() + win_a.seg_items());
+                             stiles_a.size() + win_a.chunks() + win_a.seg_items() +
+                                 (size_t)w64_a.nch);
   }
 };
 
@@ -203,6 +207,12 @@ size_t tables_bytes(const std::vector<const Prepared*>& preps, int64_t cap);
 size_t tables_bytes(int64_t nlps, int64_t nwork_t, int64_t nwork_a, int64_t cap);
 // The step tiles of an LP: its rows outside windowed chunks, tiled.
 void step_tiles(Prepared& P, int64_t cap, int lanes);
+// Gives a side's short rows of an FP64 LP to planned windows (plan_windows64)
+// and the rows before them to segments or tiles. False, with P as it was,
+// where that takes more partial slots than the side has or the launch tables
+// would need more than `tables` bytes.
+bool take_windows64(Prepared& P, bool tside, const Win64& w, int64_t cap, int lanes,
+                    int64_t workgroups, size_t tables);
 // Work list of one side for a set of LPs (tiles of LP 0, then LP 1, ...),
 // chunked over at most cap workgroups and padded to grid * chunk items;
 // fills each item's slot / last flags and each LP's slot count.
