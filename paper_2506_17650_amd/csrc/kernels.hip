@@ -4085,13 +4085,29 @@ int struct_build(const StructCfg& c, void* stream) {
 int power_norm(const PrepCfg& c, void* stream) {
   const int64_t lanes = (int64_t)c.m * kPwLanes;
   const int ga = (int)std::max<int64_t>(1, std::min<int64_t>(4096, (lanes + kBlock - 1) / kBlock));
-  for (int r = 0; r < c.power_iters; ++r) {
-    hipLaunchKernelGGL(k_power_av, dim3(ga), dim3(kBlock), 0, (hipStream_t)stream, c, r);
-    if (launched()) return -1;
-    hipLaunchKernelGGL(k_power_w, dim3(c.pw_grid), dim3(kBlock), 0, (hipStream_t)stream, c, r);
-    if (launched()) return -1;
-    hipLaunchKernelGGL(k_power_step, dim3(1), dim3(64), 0, (hipStream_t)stream, c, r);
-    if (launched()) return -1;
+  // the stopping flag is read after 8 rounds, 16 more, 32, and every 64 from
+  // there: a read costs as much as two rounds, the rounds after the stop
+  // three empty launches each (9 us)
+  int r = 0;
+  for (int block = 8; r < c.power_iters; block = std::min(2 * block, 64)) {
+    for (const int end = std::min(c.power_iters, r + block); r < end; ++r) {
+      hipLaunchKernelGGL(k_power_av, dim3(ga), dim3(kBlock), 0, (hipStream_t)stream, c, r);
+      if (launched()) return -1;
+      hipLaunchKernelGGL(k_power_w, dim3(c.pw_grid), dim3(kBlock), 0, (hipStream_t)stream, c, r);
+      if (launched()) return -1;
+      hipLaunchKernelGGL(k_power_step, dim3(1), dim3(64), 0, (hipStream_t)stream, c, r);
+      if (launched()) return -1;
+    }
+    if (r == c.power_iters) break;
+    double done = 0.0;
+    hipError_t e = hipMemcpyAsync(&done, c.scr + c.pw_at + 1, sizeof(done), hipMemcpyDeviceToHost,
+                                  (hipStream_t)stream);
+    if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
+    if (e != hipSuccess) {
+      g_last_device_error = e;
+      return -1;
+    }
+    if (done != 0.0) break;
   }
   hipLaunchKernelGGL(k_power_final, dim3(1), dim3(64), 0, (hipStream_t)stream, c);
   return launched();
