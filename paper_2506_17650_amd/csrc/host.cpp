@@ -1307,8 +1307,16 @@ static void plan_one(const opdhg_params* p, Prepared& P) {
   P.one_threads = 64 * (int)std::min<int64_t>(units, kOneThreads / 64);
 }
 
-// Rounds of the power iteration that are launched one by one at most.
+// Rounds of the power iteration that are launched one by one at most, and the
+// entries from which on it runs on the device. A round costs the device 9 us
+// of launches whatever the LP, the host 4 to 5 us per 1000 entries: creating a
+// session at 200 rounds with the device's norm and with the host's, 219
+// entries 2.0 and 0.7 ms, 1103 2.2 and 1.6, 1672 3.0 and 1.9, 2236 2.0 and 2.1,
+// 2741 2.2 and 1.8, 3315 2.6 and 4.6, 3868 3.0 and 5.2, 5518 3.1 and 7.0, 13288
+// 3.3 and 15.7. (One that converges in two rounds takes 1.36 and 1.31 ms at
+// 4000 entries.)
 constexpr int kPowerDevIters = 1000;
+constexpr int64_t kPowerDevNnz = 3072;
 
 int prepare(const opdhg_lp* lp, const opdhg_params* p, Prepared& out, bool structure_only) {
   out.m = lp->m;
@@ -1396,10 +1404,10 @@ int prepare(const opdhg_lp* lp, const opdhg_params* p, Prepared& out, bool struc
   if (!structure_only && !out.dprep) {
     rescale_with(lp, C, p->ruiz_iters, p->l2_rescale != 0, p->pc_beta, sval, out.dr, out.dc);
     // the constant step's norm: by kernels over the uploaded values, which
-    // are FP64 as here (13k entries and 200 rounds: 13 ms on the host, 2.7 ms
-    // there), or here
+    // are FP64 as here, or of small LPs here
     out.power_dev = p->step_rule == OPDHG_STEP_CONSTANT && p->prep == OPDHG_PREP_AUTO &&
-                    p->precision == OPDHG_FP64 && !out.host_power && p->power_iters <= kPowerDevIters;
+                    p->precision == OPDHG_FP64 && !out.host_power &&
+                    p->power_iters <= kPowerDevIters && nnz >= kPowerDevNnz;
     if (p->step_rule == OPDHG_STEP_CONSTANT && !out.power_dev)
       spec = spectral_norm_with(lp, C, sval, p->power_iters, p->power_tol);
   }

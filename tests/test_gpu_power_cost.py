@@ -1,7 +1,10 @@
 """What the constant step's norm costs at session creation: not much more
 than on the host, whichever side the automatic preparation takes, and the same
 bits. Best of several creations; the bounds are a few milliseconds where
-launches for nothing would take ten."""
+launches for nothing would take ten, and 0.7 where they would take 1.3. And
+the same bits from the fewest entries that the device takes (3072) on, in one
+row, in one column and at the ends of a group of 8 lanes and of a workgroup's
+32 rows, with limits around the rounds after which it looks for the end."""
 
 import time
 
@@ -49,3 +52,24 @@ def test_rounds_end_where_the_norm_has_converged(P):
     dev, host = _create(P, lp), _create(P, lp, prep=P.OPDHG_PREP_HOST)
     assert dev[1] == host[1]
     assert dev[0] < host[0] + 4.0, (dev, host)
+
+
+def test_small_lps_cost_no_more_than_on_the_host(P):
+    for m, n in ((20, 45), (200, 300)):
+        lp = random_lp((m, n), m, n, degree=("uniform", 3, 8), eq_frac=0.5)
+        dev, host = _create(P, lp), _create(P, lp, prep=P.OPDHG_PREP_HOST)
+        assert dev[1] == host[1]
+        assert dev[0] < host[0] + 0.7, (m, n, dev, host)
+
+
+@pytest.mark.parametrize("m,n,degree", [(1, 3072, 1), (7, 1025, 3), (8, 1031, 3), (9, 770, 4),
+                                        (500, 8, 400), (5000, 1, 3500), (200, 33, 100), (31, 257, 12)])
+def test_device_norm_from_its_fewest_entries_on(P, m, n, degree):
+    lp = random_lp((m, n), m, n, degree=("fixed", degree), eq_frac=0.5)
+    assert lp.val.size >= 3072
+    for rounds in (1, 8, 9, 24, 25, 200):
+        got = []
+        for prep in (P.OPDHG_PREP_AUTO, P.OPDHG_PREP_HOST):
+            with P.Session(lp, P.opdhg_vanilla_params(0.0, power_iters=rounds, prep=prep)) as s:
+                got.append(s.state()[4].eta)
+        assert got[0] == got[1], rounds
