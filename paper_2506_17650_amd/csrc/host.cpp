@@ -2733,6 +2733,19 @@ int run_group(Group& grp, const std::vector<Ctl*>& d_ctls, std::vector<Ctl>& h_c
   return OPDHG_OK;
 }
 
+int workspace_need(const opdhg_lp* lp, const opdhg_params* p, size_t* need, size_t* least) {
+  int rc = validate_lp(lp);
+  if (rc) return rc;
+  if ((rc = validate_params(p))) return rc;
+  if (!need) return fail(OPDHG_ERR_INVALID_ARGUMENT, "bytes is NULL");
+  Prepared P;
+  if ((rc = prepare(lp, p, P, true))) return rc;
+  const SlotLayout L = slot_layout(P, p->precision);
+  *need = L.total + tables_bytes({&P}, grid_cap(p));
+  *least = *need - (L.total - L.base);
+  return OPDHG_OK;
+}
+
 }  // namespace opdhg
 
 using namespace opdhg;
@@ -2785,15 +2798,8 @@ void opdhg_default_params(opdhg_params* p) {
 int opdhg_validate(const opdhg_lp* lp) { return validate_lp(lp); }
 
 int opdhg_workspace_bytes(const opdhg_lp* lp, const opdhg_params* p, size_t* bytes) {
-  int rc = validate_lp(lp);
-  if (rc) return rc;
-  if ((rc = validate_params(p))) return rc;
-  if (!bytes) return fail(OPDHG_ERR_INVALID_ARGUMENT, "bytes is NULL");
-  Prepared P;
-  if ((rc = prepare(lp, p, P, true))) return rc;
-  SlotLayout L = slot_layout(P, p->precision);
-  *bytes = L.total + tables_bytes({&P}, grid_cap(p));
-  return OPDHG_OK;
+  size_t least = 0;
+  return workspace_need(lp, p, bytes, &least);
 }
 
 int opdhg_rescale(const opdhg_lp* lp, const opdhg_params* p, double* scaled_val, double* d_row,

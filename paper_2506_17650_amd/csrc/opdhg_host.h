@@ -297,6 +297,10 @@ struct Group {
 int run_group(Group& grp, const std::vector<Ctl*>& d_ctls, std::vector<Ctl>& h_ctls,
               Ctl* pinned, int64_t k_target, double time_limit, double* elapsed);
 
+// Workspace bytes of an LP solved alone, and the least a session accepts: a
+// small FP64 LP solves without its packed entries too.
+int workspace_need(const opdhg_lp* lp, const opdhg_params* p, size_t* need, size_t* least);
+
 // Session set-up behind opdhg_session_create; direct: a launch group in
 // direct mode and pageable readback (nothing allocated on the device or
 // pinned). need_out (optional) receives the device bytes the LP needs.

@@ -464,29 +464,31 @@ void ServerImpl::fallback_loop() {
     }
     opdhg_params p64 = j->p;
     p64.precision = OPDHG_FP64;
-    // small LPs solve in one workgroup where the budget holds their packed
-    // entries too (windows are off for the shared sequence; FP64 results do
-    // not depend on it)
+    // small LPs solve in one workgroup where the arena has room for their
+    // packed entries too, now (windows are off for the shared sequence; FP64
+    // results do not depend on it)
     p64.windows = OPDHG_WINDOWS_AUTO;
     const opdhg_lp v = lp_view(*j);
-    size_t need = 0;
-    int rc = opdhg_workspace_bytes(&v, &p64, &need);
+    size_t need = 0, least = 0;
+    int rc = workspace_need(&v, &p64, &need, &least);
     need = align256(need);
-    if (!rc && need > budget) {
-      p64.windows = OPDHG_WINDOWS_OFF;
-      rc = opdhg_workspace_bytes(&v, &p64, &need);
-      need = align256(need);
-    }
+    least = align256(least);
     size_t off = 0;
     bool got = false;
     {
       std::unique_lock<std::mutex> lk(mu);
-      if (rc || need > budget) {
+      if (rc || least > budget) {
         finish_job(*j, OPDHG_OK, "");
         continue;
       }
-      fb_wait = need;
-      while (!stopping && !j->cancel && !(got = arena.alloc(need, &off)))
+      fb_wait = least;
+      auto take = [&] {
+        if (arena.alloc(need, &off)) return true;
+        if (!arena.alloc(least, &off)) return false;
+        need = least;
+        return true;
+      };
+      while (!stopping && !j->cancel && !(got = take()))
         cv_fb.wait_for(lk, std::chrono::duration<double>(std::max(cfg.poll_interval_s, 1e-4)));
       fb_wait = 0;
       cv_sched.notify_all();
