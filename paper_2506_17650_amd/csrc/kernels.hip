@@ -65,8 +65,10 @@
 #include <math.h>
 
 #include <algorithm>
+#include <initializer_list>
 #include <mutex>
 #include <type_traits>
+#include <vector>
 
 #include "crmath.h"
 #include "opdhg_internal.h"
@@ -3852,35 +3854,48 @@ __global__ __launch_bounds__(kBlock) void k_prep_scalars(PrepCfg a) {
   }
 }
 
-// The windowed kernels take more than the default 64 KiB of LDS; the
-// attribute is set once per process, before the first launch.
-static int win_attributes() {
-  static std::once_flag once;
-  static hipError_t err = hipSuccess;
-  std::call_once(once, [] {
-    const void* ks[] = {(const void*)k_primal_win, (const void*)k_dual_win,
-                        (const void*)k_prod_win<true, 0>, (const void*)k_prod_win<true, 1>,
-                        (const void*)k_prod_win<false, 0>};
-    for (const void* f : ks)
-      if (err == hipSuccess)
-        err = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWinLds);
-  });
-  if (err != hipSuccess) g_last_device_error = err;
-  return err == hipSuccess ? 0 : -1;
+// Some kernels take more than the default 64 KiB of LDS: the attribute
+// belongs to a function on one device and is set there once, before the
+// first launch (outside any capture: Group::init).
+class LdsAttribute {
+ public:
+  int set(std::initializer_list<const void*> kernels, size_t bytes) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    std::lock_guard<std::mutex> lock(mu_);
+    if (e == hipSuccess && std::find(done_.begin(), done_.end(), dev) != done_.end()) return 0;
+    for (const void* f : kernels)
+      if (e == hipSuccess)
+        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) {
+      g_last_device_error = e;
+      return -1;
+    }
+    done_.push_back(dev);
+    return 0;
+  }
+
+ private:
+  std::mutex mu_;
+  std::vector<int> done_;  // devices
+};
+
+int window_kernels_ready() {
+  static LdsAttribute lds;
+  return lds.set({(const void*)k_primal_win, (const void*)k_dual_win,
+                  (const void*)k_prod_win<true, 0>, (const void*)k_prod_win<true, 1>,
+                  (const void*)k_prod_win<false, 0>},
+                 kWinLds);
 }
 
-int window_kernels_ready() { return win_attributes(); }
-
 int w64_kernels_ready() {
-  static std::once_flag once;
-  static hipError_t err = hipSuccess;
-  std::call_once(once, [] {
-    for (const void* f : {(const void*)k_primal_w64, (const void*)k_dual_w64})
-      if (err == hipSuccess)
-        err = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kW64Lds);
-  });
-  if (err != hipSuccess) g_last_device_error = err;
-  return err == hipSuccess ? 0 : -1;
+  static LdsAttribute lds;
+  return lds.set({(const void*)k_primal_w64, (const void*)k_dual_w64}, kW64Lds);
+}
+
+int one_kernel_ready() {
+  static LdsAttribute lds;
+  return lds.set({(const void*)k_one}, kOneLdsMax);
 }
 
 int w64_keys(const Win64& w, int32_t* key, int2* range, void* stream) {
@@ -3914,7 +3929,7 @@ int Kernels<V>::primal_win(const LaunchCfg& c, void* stream, int force) {
     return launched();
   } else {
     if (c.nwin_t <= 0) return 0;
-    if (win_attributes()) return -1;
+    if (window_kernels_ready()) return -1;
     hipLaunchKernelGGL(k_primal_win, dim3(c.nwin_t), dim3(kWinBlock), kWinLds,
                        (hipStream_t)stream, c, force);
     return launched();
@@ -3929,7 +3944,7 @@ int Kernels<V>::dual_win(const LaunchCfg& c, void* stream, int force) {
     return launched();
   } else {
     if (c.nwin_a <= 0) return 0;
-    if (win_attributes()) return -1;
+    if (window_kernels_ready()) return -1;
     hipLaunchKernelGGL(k_dual_win, dim3(c.nwin_a), dim3(kWinBlock), kWinLds,
                        (hipStream_t)stream, c, force);
     return launched();
@@ -3952,17 +3967,6 @@ int Kernels<V>::decide(const LaunchCfg& c, void* stream) {
                      0, (hipStream_t)stream, c);
   return launched();
 }
-int one_kernel_ready() {
-  static std::once_flag once;
-  static hipError_t err = hipSuccess;
-  std::call_once(once, [] {
-    err = hipFuncSetAttribute((const void*)k_one, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)kOneLdsMax);
-  });
-  if (err != hipSuccess) g_last_device_error = err;
-  return err == hipSuccess ? 0 : -1;
-}
-
 template <typename V>
 int Kernels<V>::one(const LaunchCfg& c, void* stream, int attempts) {
   if constexpr (!std::is_same<V, double>::value) {
@@ -3995,7 +3999,7 @@ int Kernels<V>::eval_products(const LaunchCfg& c, void* stream) {
   if constexpr (!std::is_same<V, float>::value) {
     return -1;
   } else {
-    if (win_attributes()) return -1;
+    if (window_kernels_ready()) return -1;
     hipStream_t q = (hipStream_t)stream;
     // one vector at a time: its tiles and windowed chunks, then the
     // segments, whose partials both write

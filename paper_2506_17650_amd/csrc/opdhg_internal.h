@@ -574,7 +574,7 @@ int struct_build(const StructCfg& c, void* stream);
 
 // The packed entries of a small FP64 LP (see kOneThreads), from its CSR copies.
 int one_pack(const LpDev& lp, void* stream);
-// Sets k_one's LDS attribute (once per process); 0 on success.
+// Sets k_one's LDS attribute (once per device); 0 on success.
 int one_kernel_ready();
 
 // of both sides; kind 0: maxima of |a~|, 1: sums of |a~|^ea and |a~|^et, 2: L2 norms
@@ -583,7 +583,7 @@ int prep_apply(const PrepCfg& c, void* stream);  // dr /= sqrt(sr), dc /= sqrt(s
 int power_norm(const PrepCfg& c, void* stream);  // the constant step's eta0 (power iteration)
 template <typename V>
 int prep_finish(const PrepCfg& c, void* stream);
-// Sets the windowed kernels' LDS attribute (once per process); 0 on success.
+// Sets the windowed kernels' LDS attribute (once per device); 0 on success.
 int window_kernels_ready();
 // And of the FP64 ones.
 int w64_kernels_ready();
