@@ -138,9 +138,11 @@ __device__ __forceinline__ gptr<T> gp(T* p) {
 // The same address as constant memory: with a uniform pointer its loads are
 // scalar loads into scalar registers, several words each, where a vector
 // load of a uniform value takes a v_readfirstlane per word behind its wait.
-// Only for what no lane of the launch writes before it is read (launch
-// tables, LP records; control blocks, which a kernel reads before it writes
-// them). With the work items, records and control blocks of the step kernels
+// Only for what the launch does not write (launch tables, LP records), and for
+// fields of a control block that the launch writes but does not use any more
+// by then: the compiler may load a value again wherever it is used, so one
+// that is used after its field is written has to pass sgpr_own first
+// (k_decide). With the work items, records and control blocks of the step kernels
 // read this way an attempt takes 20.1 us in FP32 and 26.4 in FP64 on
 // 50k x 100k (23.1 and 29.6 with vector loads and the items staged in LDS
 // behind a barrier), 16.5 in FP64 on 15k x 10k (17.5).
@@ -1716,9 +1718,6 @@ struct DualStep {
   __device__ __forceinline__ void piece(int sid, const Acc<V>& a) const { seg_store(segp_, sid, a); }
 };
 
-// Chunking of a step kernel's tile list: fixed sets carry it in the launch
-// arguments (no dependent load before the work items); the server's
-// changing set reads the device-side counts.
 // Makes each value live in a scalar register at this point. Kernel
 // arguments read later behind branches would otherwise be loaded one
 // cache line at a time, each load waiting for the branch before it.
@@ -1731,6 +1730,20 @@ __device__ __forceinline__ void sgpr_ready(const T&... v) {
   (sgpr_ready1(v), ...);
 }
 
+// A value of its own from here on: not the memory it was loaded from, which
+// may be written now.
+template <typename T>
+__device__ __forceinline__ void sgpr_own1(T& v) {
+  asm volatile("" : "+s"(v));
+}
+template <typename... T>
+__device__ __forceinline__ void sgpr_own(T&... v) {
+  (sgpr_own1(v), ...);
+}
+
+// Chunking of a step kernel's tile list: fixed sets carry it in the launch
+// arguments (no dependent load before the work items); the server's
+// changing set reads the device-side counts.
 __device__ __forceinline__ SideChunks step_chunks(const LaunchCfg& cfg, bool tside) {
   const int fixed = cfg.step_fixed;
   const int g = tside ? cfg.sgrid_t : cfg.sgrid_a, ch = tside ? cfg.schunk_t : cfg.schunk_a;
@@ -2644,6 +2657,9 @@ __global__ __launch_bounds__(PLAIN ? kBlock : kDecBlock)
       in.attempts = g->attempts;
       in.retries = g->retries;
       in.cur = g->cur;
+      // the decision writes the same fields
+      sgpr_own(status, need, k_limit, ring_base, in.eta, in.omega, in.w, in.hp_norm, in.hd_norm,
+               in.k, in.t, in.attempts, in.retries, in.cur);
     };
     if constexpr (PLAIN) {
       sum_partials2<3, 4>(d.part_t, d.ntiles_t, d.ns_t, d.part_a, d.ntiles_a, d.ns_a, sv, s_red,
