@@ -397,6 +397,15 @@ int opdhg_session_state(opdhg_session* s, double* x, double* y, double* T, doubl
                         opdhg_state* st);
 /* Unscaled returned iterate and result of a finished (or paused) session. */
 int opdhg_session_result(opdhg_session* s, double* x_out, double* y_out, opdhg_result* res);
+/* Which kernels run the session's attempts, for checks and tuning: the
+ * windows that were planned can be fewer than OPDHG_WINDOWS_* asks for. */
+typedef struct opdhg_route {
+  int32_t one_workgroup;          /* 1: all attempts in one workgroup (small FP64 LPs) */
+  int32_t chunks_t, chunks_a;     /* windowed chunks over A^T rows and A rows (0: none) */
+  int32_t passes_t, passes_a;     /* the most windows a chunk takes one after another */
+  int32_t segments_t, segments_a; /* segments of long rows in those chunks */
+} opdhg_route;
+int opdhg_session_route(const opdhg_session* s, opdhg_route* route);
 /* Average device time of one launch of the primal kernel (CSR(A^T) SpMV
  * fused with the primal step) over reps launches, timed with HIP events on
  * the session's stream. The kernel only rewrites the candidate buffers, so

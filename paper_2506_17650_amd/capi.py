@@ -105,6 +105,11 @@ class opdhg_state(ctypes.Structure):
     ]
 
 
+class opdhg_route(ctypes.Structure):
+    _fields_ = [(f, c_i32) for f in ("one_workgroup", "chunks_t", "chunks_a", "passes_t",
+                                     "passes_a", "segments_t", "segments_a")]
+
+
 class opdhg_server_cfg(ctypes.Structure):
     _fields_ = [
         ("budget_bytes", c_sz), ("max_active", c_i32), ("attempts_per_replay", c_i32),
@@ -166,6 +171,7 @@ SIGNATURES = {
                                     _p(c_dbl), _p(opdhg_state)]),
     "opdhg_session_result": (c_i32, [ctypes.c_void_p, _p(c_dbl), _p(c_dbl),
                                      _p(opdhg_result)]),
+    "opdhg_session_route": (c_i32, [ctypes.c_void_p, _p(opdhg_route)]),
     "opdhg_session_time_primal_kernel": (c_i32, [ctypes.c_void_p, c_i32, _p(c_dbl)]),
     "opdhg_session_time_kernels": (c_i32, [ctypes.c_void_p, c_i32, _p(c_dbl), _p(c_dbl)]),
     "opdhg_session_destroy": (None, [ctypes.c_void_p]),
@@ -515,6 +521,12 @@ class Session:
         _check(load().opdhg_session_result(self._h, _dptr(x, c_dbl), _dptr(y, c_dbl),
                                            ctypes.byref(res)))
         return x, y[: self._a.m], res
+
+    def route(self) -> opdhg_route:
+        """Which kernels run the session's attempts."""
+        out = opdhg_route()
+        _check(load().opdhg_session_route(self._h, ctypes.byref(out)))
+        return out
 
     def time_primal_kernel(self, reps: int) -> float:
         out = c_dbl(0.0)

@@ -3150,6 +3150,7 @@ static int plan_windows64(uint8_t* base, const SlotLayout& L, Prepared& P, const
     if (total < 1 || total > P.nnz || passes * rel > INT32_MAX) continue;
     w.last = (int32_t)(total - 1);
     w.relstride = (int32_t)rel;
+    w.passes = (int32_t)passes;
     w.rel = static_cast<uint16_t*>(take(2 * (size_t)(passes * rel)));
     if (!w.rel) continue;
     if (!take_windows64(P, tside, w, cap, p->lanes, grid_cap(p), tables)) continue;
@@ -3383,6 +3384,28 @@ int opdhg_session_result(opdhg_session* s, double* x_out, double* y_out, opdhg_r
     unpermute(tmp.data(), S.P.perm_a, S.P.dr.data(), y_out);
   }
   if (res) fill_result(c, S.elapsed, res);
+  return OPDHG_OK;
+}
+
+int opdhg_session_route(const opdhg_session* s, opdhg_route* route) {
+  if (!s || !route) return fail(OPDHG_ERR_INVALID_ARGUMENT, "bad arguments");
+  const SessionImpl& S = s->impl;
+  *route = opdhg_route{};
+  route->one_workgroup = S.grp.cfg.one_threads > 0 ? 1 : 0;
+  auto side = [](const Win64& w, const WinPlan& W, int32_t& chunks, int32_t& passes,
+                 int32_t& segments) {
+    if (w.nch > 0) {  // FP64
+      chunks = w.nch;
+      passes = w.passes;
+      segments = w.row0 * w.groups;
+    } else if (W.chunks()) {
+      chunks = (int32_t)W.chunks();
+      passes = *std::max_element(W.npass.begin(), W.npass.end());
+      segments = W.nsegs_win;
+    }
+  };
+  side(S.P.w64_t, S.P.win_t, route->chunks_t, route->passes_t, route->segments_t);
+  side(S.P.w64_a, S.P.win_a, route->chunks_a, route->passes_a, route->segments_a);
   return OPDHG_OK;
 }
 

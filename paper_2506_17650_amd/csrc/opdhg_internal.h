@@ -233,6 +233,7 @@ struct Win64 {
   int32_t last;        // last entry
   int32_t slot0;       // partial slot of the first chunk
   int32_t groups;      // 0: no segments
+  int32_t passes;      // of a chunk at most
   void* segp;          // the segments as LpDev has them
   const int32_t *srow, *sptr, *sids;
 };

@@ -32,16 +32,20 @@ def _split_lp(seed, longs, shorts, k, n):
     return lp
 
 
-@pytest.mark.parametrize("longs,shorts,k,n,rows", [
-    (10, 2000, 4, 20000, 64), (10, 2000, 4, 20000, 256), (1, 3000, 18, 20011, 55),
-    (1, 3000, 18, 20011, 64), (2, 9000, 18, 30001, 0)])
-def test_windows_equal_tiles(P, longs, shorts, k, n, rows):
+# sides: those in windows
+@pytest.mark.parametrize("longs,shorts,k,n,rows,sides", [
+    (10, 2000, 4, 20000, 64, ""), (10, 2000, 4, 20000, 256, "TA"), (1, 3000, 18, 20011, 55, ""),
+    (1, 3000, 18, 20011, 64, "A"), (2, 9000, 18, 30001, 0, "TA")])
+def test_windows_equal_tiles(P, longs, shorts, k, n, rows, sides):
     lp = _split_lp((longs, rows), longs, shorts, k, n)
     kw = dict(prep=P.OPDHG_PREP_DEVICE, tol=0.0, lr=1e-2, phi=3)
     got = []
     for extra in (dict(windows=P.OPDHG_WINDOWS_ALWAYS, window_rows=rows),
                   dict(windows=P.OPDHG_WINDOWS_OFF)):
         with P.Session(lp, P.opdhg_default_params(**kw, **extra)) as s:
+            if not got:
+                r = s.route()
+                assert ("T" in sides) == (r.chunks_t > 0) and ("A" in sides) == (r.chunks_a > 0)
             s.run(150)
             got.append(s.state())
     for a, b in zip(got[0][:4], got[1][:4]):
