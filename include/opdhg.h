@@ -88,14 +88,20 @@ extern "C" {
 #define OPDHG_STEP_NORM_PRECOND 1 /* |dx|^2_{T^-1} and |dy|^2_{Sigma^-1}: the norms of the
                                      preconditioned step (eq. (6)); equal to PLAIN at T = Sigma = I */
 
-/* ---- windowed sparse products (FP32) ---- */
+/* ---- windowed sparse products ---- */
+/* FP64 windows are planned after the upload, in the slot's own memory, for an LP solved alone
+ * whose structure the device builds (prepared there, no column above 4096 entries) and that
+ * does not run in one workgroup; a side stays in tiles wherever its plan does not fit there
+ * (opdhg_session_route tells). Results do not depend on it in FP64. */
 #define OPDHG_WINDOWS_AUTO 0   /* a side whose rows give at least 128 windowed chunks uses them
-                                  (FP64: 256 chunks of 2048 rows) */
+                                  (FP64: 256 chunks of 2048 rows that stage at most 1.5 entries
+                                  for each that gathers from them) */
 #define OPDHG_WINDOWS_OFF 1    /* every row in tiles that gather from global memory; a small FP64
                                   LP too, whose attempts otherwise run in one workgroup (same
                                   results; without room for its packed entries in the workspace it
                                   runs in tiles as well) */
-#define OPDHG_WINDOWS_ALWAYS 2 /* every windowable chunk, however few (small LPs, checks) */
+#define OPDHG_WINDOWS_ALWAYS 2 /* every windowable chunk, however few (checks); a small FP64
+                                  LP still runs in one workgroup */
 
 /* ---- where the rescaling and the scaled data are computed ---- */
 #define OPDHG_PREP_AUTO 0   /* on the device for LPs of 2^20 nonzeros or more, else on the host;
@@ -415,7 +421,9 @@ int opdhg_session_time_primal_kernel(opdhg_session* s, int reps, double* avg_ms)
  * kernel (CSR(A) SpMV of the candidate x fused with the dual step), each
  * over reps back-to-back launches timed with HIP events on the session's
  * stream. Timing launches write only the candidate buffers (no
- * preconditioner update, no online gradient), so the state is unchanged. */
+ * preconditioner update, no online gradient), so the state is unchanged. For
+ * a session whose attempts run in one workgroup (opdhg_session_route) these
+ * are the tile kernels, which it does not run. */
 int opdhg_session_time_kernels(opdhg_session* s, int reps, double* primal_ms, double* dual_ms);
 void opdhg_session_destroy(opdhg_session* s);
 

@@ -1712,9 +1712,10 @@ Ctl initial_ctl(const Prepared& P) {
 }
 
 // Byte ranges of a slot that the host image fills and uploads: the whole
-// slot (but the packed entries of a small LP), or with the device-side structure everything but the CSR copies
-// and their values (built on the device) and the staging of the caller's
-// arrays (uploaded from them directly).
+// slot (but the packed entries of a small LP), or with the device-side
+// structure everything but the CSR copies and their values (built on the
+// device) and the staging of the caller's arrays (uploaded from them
+// directly).
 static std::vector<std::pair<size_t, size_t>> image_ranges(const SlotLayout& L, const Prepared& P) {
   if (!P.dstruct) return {{0, L.base}};
   return {{0, L.ci_a}, {L.rp_t, L.ci_t}, {L.vn[0], L.raw_a}, {L.raw_b, L.st_rp}};
@@ -1974,7 +1975,8 @@ int Group::launch_init() {
   return Kernels<double>::init_products(cfg, stream);
 }
 
-// A forced launch of a side, as in the captured sequence.
+// A forced launch of a side's step kernels (those of the captured sequence,
+// where k_one does not run the attempts).
 int Group::launch_primal_forced() { return launch_side(true, 1, stream); }
 
 int Group::launch_dual_forced() { return launch_side(false, 1, stream); }
@@ -2573,7 +2575,7 @@ constexpr size_t kPinFrom = 16 * kPinPiece;
 // the first read): not in direct mode, which allocates nothing, and not
 // below kPinFrom for x, y, T and Sigma together. There the runtime's own
 // copies and one thread are as fast (2.4 MB of 50k x 100k: 0.38 ms against
-// 0.50), and a first read would pay for the allocation (2 to 10 ms).
+// 0.50), and a first read pays for the allocation (0.3 to 0.7 ms).
 static bool pinned_staging(SessionImpl& S) {
   const size_t V = S.grp.prec == OPDHG_FP32 ? 4 : 8;
   if (S.direct || 2 * V * (size_t)(S.P.n + S.P.m) < kPinFrom) return false;

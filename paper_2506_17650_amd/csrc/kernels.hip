@@ -1078,10 +1078,9 @@ __device__ __forceinline__ T uni(T v) {
   }
 }
 
-// The control-block fields a step kernel reads, fetched together through
-// the global address space into scalar registers: every load is issued
-// before the first branch on any of them, so they cost one round trip
-// instead of one per branch.
+// The control-block fields a step kernel reads, fetched together into scalar
+// registers: every load is issued before the first branch on any of them, so
+// they cost one round trip instead of one per branch.
 struct CtlView {
   double eta, omega, g2, r2, hp_norm, hd_norm;
   int64_t k, k_limit;
@@ -2572,7 +2571,7 @@ __device__ __forceinline__ DecideLp decide_lp(const LpDev* rec) {
   d.part_a = L->part_a;
   d.ntiles_t = L->ntiles_t;
   d.ntiles_a = L->ntiles_a;
-  // slots of the step kernels (one per tile, then the windowed chunks)
+  // slots of the step kernels (see LpDev)
   d.ns_t = L->nslot_st;
   d.ns_a = L->nslot_sa;
   d.lr = L->s_lr;
@@ -3346,12 +3345,13 @@ __global__ __launch_bounds__(kDecBlock) void k_eval_decide(LaunchCfg cfg, int mi
   }
 }
 
-// Restart application or the final copy of the returned average. The
-// flags stay set until the next k_primal clears them, and restarting to the
-// average reads the sums it then clears, so this kernel runs exactly once
-// per evaluation step, right before attempt slots (every evaluation step of
-// a launch sequence, the guarded ones included, is followed by at least one
-// attempt slot before the next).
+// Restart application or the final copy of the returned average. Restarting
+// to the average reads the sums it then clears, so this kernel runs exactly
+// once per evaluation step, and the flags must be cleared before the next
+// one: by the primal kernel of the next attempt slot (k_primal, k_primal_win,
+// k_primal_w64) or by k_one, one of which follows every evaluation of a launch
+// sequence, or after a closing evaluation (Group::close), which no attempt
+// follows, by the board launch, for which clearing them is not optional.
 template <typename V>
 __global__ __launch_bounds__(kBlock) void k_apply(LaunchCfg cfg, int mid) {
   if (eval_step_skips(cfg, mid, false)) return;

@@ -249,6 +249,8 @@ int mid_eval_every(const opdhg_params* p, int64_t nlps);
 // (after a rejected attempt, say) is evaluated there and goes on within
 // mid_every slots, instead of waiting for the next sequence. A guarded step
 // in which no LP is due returns after one load per kernel (Counts::hint).
+// For a set of small FP64 LPs the attempts before a due evaluation are one
+// launch (k_one), with one guarded evaluation step and one launch after it.
 //
 // Direct mode (for callers that cannot let the library create HIP objects):
 // no captured graph, no streams or events of the library's own; each replay

@@ -2,9 +2,9 @@
 //
 // Device layout of one LP ("slot"): both CSR copies (A and A^T, int32 row
 // pointers and column indices, values in the compute precision V), the
-// iteration vectors in V, the rescaling diagonals in FP64, per-tile FP64
-// reduction partials, the tile tables, a control block (Ctl) and the
-// per-LP constants (DevParams). Everything sits in the caller's workspace.
+// iteration vectors in V, the rescaling diagonals in FP64, FP64 reduction
+// partials, the tile tables, a control block (Ctl) and the per-LP constants
+// (DevParams). Everything sits in the caller's workspace.
 //
 // Double buffering: x, y, A x, and the running sums of x and y have two
 // copies; Ctl::cur names the current one. An attempt writes the other copy,
@@ -17,7 +17,7 @@
 namespace opdhg {
 
 constexpr int kBlock = 256;        // threads per workgroup (4 wave64)
-constexpr int kPartStride = 32;    // doubles of reduction partials per tile (16 double-doubles)
+constexpr int kPartStride = 32;    // doubles of reduction partials per slot (16 double-doubles)
 constexpr int kPowTab = 8192;      // host-computed step-rule factors for the first attempts
 constexpr int kPowRing = 64;       // factors for the attempts of one launch sequence (at most
                                    // kPowRing attempts each)
@@ -496,8 +496,8 @@ constexpr int kClosing = -1;
 // Device-side preparation of one slot (FP64 arithmetic, results in V):
 // the rescaling passes over the two stored CSR copies in device order,
 // then the scaled values, vectors, windowed values and the first step size
-// and primal weight. Every row statistic follows the host's expression and
-// order (maxima; double-double sums added one entry at a time).
+// and primal weight. Every row statistic takes the host's expression in maxima
+// and double-double sums, which do not depend on the order.
 constexpr int kPrepGrid = 256;  // workgroups of the vector kernel (norm partials)
 struct PrepCfg {
   const int32_t* rp_a;

@@ -13,9 +13,11 @@
 // iterates are downloaded, unscaled and handed to poll / wait, and their
 // block returns to the arena.
 //
-// Each LP's arithmetic depends only on its own data: rows are reduced
-// inside one tile and every cross-tile sum is exact (double-double), so a
-// result does not depend on what else shares the launches.
+// Each LP's arithmetic depends only on its own data: rows are reduced inside
+// one tile, and every cross-tile sum is a double-double (FP64 steps, all
+// evaluations) or has one partial per tile added in the order of the LP's
+// own list (FP32 steps), so a result does not depend on what else shares the
+// launches.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
