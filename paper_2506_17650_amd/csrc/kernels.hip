@@ -2191,9 +2191,10 @@ __global__ __launch_bounds__(kWinBlock) void k_dual_win(LaunchCfg cfg, int force
 // bytes, 35 million a side on the block-angular LP of 64 blocks (1.92M x
 // 5.12M): 4.5 GB between L2 and L1, and neither other cache hints nor agent
 // scope made them smaller. From LDS they cost a bank access, and the rest is a
-// stream: A^T takes 189 us (290 in tiles; 680 MB, 3.6 TB/s), A 185 (310), an
-// attempt 396 (619). One workgroup of 16 waves owns the CU's LDS, so that
-// windows are as large and passes as few as they can be. Each row's entries lie
+// stream: A^T takes 189 us (290 in tiles; 680 MB by its arrays' sizes, not
+// counted, so 3.6 TB/s), A 185 (310), an attempt 396 (619). One workgroup of 16
+// waves owns the CU's LDS, so that windows are as large and passes as few as
+// they can be. Each row's entries lie
 // together, so a wave's loads hit a few lines between them and rows of any
 // length need no padding; the first four of the next slice are in flight while
 // a slice is summed (three or six, or loading the first epilogue before the
