@@ -2194,11 +2194,11 @@ __global__ __launch_bounds__(kWinBlock) void k_dual_win(LaunchCfg cfg, int force
 // stream: A^T takes 189 us (290 in tiles; 680 MB by its arrays' sizes, not
 // counted, so 3.6 TB/s), A 185 (310), an attempt 396 (619). One workgroup of 16
 // waves owns the CU's LDS, so that windows are as large and passes as few as
-// they can be. Each row's entries lie
-// together, so a wave's loads hit a few lines between them and rows of any
-// length need no padding; the first four of the next slice are in flight while
-// a slice is summed (three or six, or loading the first epilogue before the
-// passes, made no difference; half the rows a chunk: 432 us an attempt).
+// they can be. Each row's entries lie together, so a wave's loads hit a few
+// lines between them and rows of any length need no padding; the first four of
+// the next slice are in flight while a slice is summed (three or six, or loading
+// the first epilogue before the passes, made no difference; half the rows a
+// chunk: 432 us an attempt).
 template <bool tside, typename Step, typename Pre, int NV>
 __device__ __forceinline__ void w64_chunk(const LaunchCfg& cfg, const Win64& W, int force) {
   extern __shared__ double wlds64[];
