@@ -111,7 +111,7 @@ extern "C" {
 #define OPDHG_PREP_HOST 1   /* host threads (FP64) */
 #define OPDHG_PREP_DEVICE 2 /* device kernels (FP64), same results (with OPDHG_STEP_CONSTANT the
                                power iteration runs on the device too; in FP64 it does so under
-                               OPDHG_PREP_AUTO from 3072 nonzeros on) */
+                               OPDHG_PREP_AUTO from 2560 nonzeros on) */
 
 /* ---- restart scheme ---- */
 #define OPDHG_RESTART_ADAPTIVE 0 /* PDLP's KKT-based restarts, preconditioners kept (Section 3.2) */

@@ -1312,14 +1312,14 @@ static void plan_one(const opdhg_params* p, Prepared& P) {
 
 // Rounds of the power iteration that are launched one by one at most, and the
 // entries from which on it runs on the device. A round costs the device 9 us
-// of launches whatever the LP, the host 4 to 5 us per 1000 entries: creating a
-// session at 200 rounds with the device's norm and with the host's, 219
-// entries 2.0 and 0.7 ms, 1103 2.2 and 1.6, 1672 3.0 and 1.9, 2236 2.0 and 2.1,
-// 2741 2.2 and 1.8, 3315 2.6 and 4.6, 3868 3.0 and 5.2, 5518 3.1 and 7.0, 13288
-// 3.3 and 15.7. (One that converges in two rounds takes 1.36 and 1.31 ms at
-// 4000 entries.)
+// of launches whatever the LP, the host 5 us per 1000 entries, and both end
+// where the norm has converged. Creating a session with the norm from the
+// device and from the host: 219 entries 1.13 and 0.42 ms, 1103 1.91 and 1.03,
+// 1672 1.85 and 1.40, 2187 2.66 and 2.52, 2405 2.44 and 2.31, 2741 1.41 and 1.46,
+// 2806 1.70 and 1.80, 3315 2.4 and 3.6, 5518 2.4 and 5.9, 13288 4.2 and 13.9. (One
+// that converges in two rounds takes 1.29 and 1.22 ms at 4000 entries.)
 constexpr int kPowerDevIters = 1000;
-constexpr int64_t kPowerDevNnz = 3072;
+constexpr int64_t kPowerDevNnz = 2560;
 
 int prepare(const opdhg_lp* lp, const opdhg_params* p, Prepared& out, bool structure_only) {
   out.m = lp->m;
@@ -2364,7 +2364,7 @@ int write_tables(uint8_t* dst, const std::vector<LpDev>& lps_in,
 // diagonals (for unscaling results) and the first step size and primal
 // weight back to the host.
 static int device_prepare(uint8_t* base, const SlotLayout& L, Prepared& P, int prec,
-                          hipStream_t stream) {
+                          hipStream_t stream, void* pinned) {
   const LpDev d = slot_pointers(base, L, P);
   PrepCfg c{};
   c.rp_a = d.rp_a;
@@ -2405,6 +2405,7 @@ static int device_prepare(uint8_t* base, const SlotLayout& L, Prepared& P, int p
   c.power_tol = P.prep_power_tol;
   c.power_iters = P.prep_power_iters;
   c.pw_grid = kPrepGrid;
+  c.stop = static_cast<int32_t*>(pinned);
   c.pw_at = 4 * kPrepGrid + 3;
   int rc = 0;
   // Ruiz passes, the L2 pass, the Pock-Chambolle pass (Section 2), as on the host
@@ -2467,7 +2468,7 @@ static int device_structure(uint8_t* base, const SlotLayout& L, const Prepared& 
 // x and y that the first attempt overwrites, the norm's partials and scalars
 // (2 G + 5 doubles, G workgroups of 32 rows of A^T) to the A^T side's
 // partials, which hold 32 doubles for each of its tiles of at most 256 rows.
-static int power_upload(const LpDev& d, const Prepared& P, hipStream_t stream) {
+static int power_upload(const LpDev& d, const Prepared& P, hipStream_t stream, void* pinned) {
   PrepCfg c{};
   c.rp_a = d.rp_a;
   c.ci_a = d.ci_a;
@@ -2488,11 +2489,12 @@ static int power_upload(const LpDev& d, const Prepared& P, hipStream_t stream) {
   c.power_iters = P.prep_power_iters;
   c.pw_grid = std::max(1, std::min(kPrepGrid, (d.n + 31) / 32));
   c.pw_at = 2 * c.pw_grid + 2;
+  c.stop = static_cast<int32_t*>(pinned);
   return power_norm(c, stream);
 }
 
 int upload_slot(uint8_t* base, const SlotLayout& L, Prepared& P, int prec, hipStream_t stream,
-                SlotImage& img) {
+                SlotImage& img, void* pinned) {
   if (prec == OPDHG_FP32) slot_image<float>(L, P, img);
   else slot_image<double>(L, P, img);
   for (const auto& r : image_ranges(L, P))
@@ -2506,10 +2508,10 @@ int upload_slot(uint8_t* base, const SlotLayout& L, Prepared& P, int prec, hipSt
     if (rc) return rc;
   }
   if (P.dprep) {
-    int rc = device_prepare(base, L, P, prec, stream);
+    int rc = device_prepare(base, L, P, prec, stream, pinned);
     if (rc) return rc;
   }
-  if (P.power_dev && power_upload(slot_pointers(base, L, P), P, stream))
+  if (P.power_dev && power_upload(slot_pointers(base, L, P), P, stream, pinned))
     return fail(OPDHG_ERR_DEVICE, device_error_string());
   if (P.one && one_pack(slot_pointers(base, L, P), stream))
     return fail(OPDHG_ERR_DEVICE, device_error_string());
@@ -3193,6 +3195,24 @@ static void segments64(const Prepared& P, LpDev& d) {
   }
 }
 
+// Pinned control blocks of the host, freed once the stream's kernels, which may
+// write there during an upload, are done (unless released before).
+struct PinnedCtl {
+  Ctl* ptr = nullptr;
+  hipStream_t stream = nullptr;
+  int alloc(size_t count, hipStream_t s) {
+    stream = s;
+    HIP_TRY(hipHostMalloc((void**)&ptr, sizeof(Ctl) * count, hipHostMallocDefault));
+    return OPDHG_OK;
+  }
+  Ctl* release() { return std::exchange(ptr, nullptr); }
+  ~PinnedCtl() {
+    if (!ptr) return;
+    (void)hipStreamSynchronize(stream);
+    (void)hipHostFree(ptr);
+  }
+};
+
 static int session_from_prepared(opdhg_prepared& pr, void* d_workspace, size_t workspace_bytes,
                                  void* hip_stream, bool direct, opdhg_session** out) {
   if (!out) return fail(OPDHG_ERR_INVALID_ARGUMENT, "out is NULL");
@@ -3223,8 +3243,10 @@ static int session_from_prepared(opdhg_prepared& pr, void* d_workspace, size_t w
   S.grp.mid_every = mid_eval_every(p, 1);
   S.grp.tol = p->tol;
   S.grp.max_iter = p->max_iter;
+  PinnedCtl pinned;
+  if (!direct && (rc = pinned.alloc(1, S.grp.stream))) return rc;
   SlotImage img;
-  if ((rc = upload_slot(S.ws, S.L, S.P, p->precision, S.grp.stream, img))) return rc;
+  if ((rc = upload_slot(S.ws, S.L, S.P, p->precision, S.grp.stream, img, pinned.ptr))) return rc;
   if ((rc = plan_windows64(S.ws, S.L, S.P, p, S.grp.stream))) return rc;
   S.lpd = slot_pointers(S.ws, S.L, S.P);
   segments64(S.P, S.lpd);
@@ -3237,8 +3259,7 @@ static int session_from_prepared(opdhg_prepared& pr, void* d_workspace, size_t w
   if ((rc = S.grp.launch_init())) return fail(OPDHG_ERR_DEVICE, device_error_string());
   HIP_TRY(hipStreamSynchronize(S.grp.stream));
   if ((rc = S.grp.capture(std::max(1, p->eval_every)))) return rc;
-  if (direct) S.h_ctl = &S.h_ctl_local;
-  else HIP_TRY(hipHostMalloc((void**)&S.h_ctl, sizeof(Ctl), hipHostMallocDefault));
+  S.h_ctl = direct ? &S.h_ctl_local : pinned.release();
   *out = s.release();
   return OPDHG_OK;
 }
@@ -3620,6 +3641,11 @@ static int batch_solve(opdhg_batch& B, void* d_workspace, size_t workspace_bytes
   grp.tol = p->tol;
   grp.max_iter = p->max_iter;
   std::vector<LpDev> lpd(count);
+  PinnedCtl pin;
+  if (pin.alloc(count, grp.stream)) {
+    grp.release();
+    return fail(OPDHG_ERR_DEVICE, "pinned host allocation failed");
+  }
   {
     // The slots are filled and copied by several threads, each with its own
     // image and stream (default priority): one thread's copy overlaps the
@@ -3638,8 +3664,9 @@ static int batch_solve(opdhg_batch& B, void* d_workspace, size_t workspace_bytes
       }
       SlotImage im;
       for (int i = nx++; i < count; i = nx++) {
-        int r = upload_slot(ws + offs[i], L[i], P[i], p->precision, s, im);
-        if (!r && hipStreamSynchronize(s) != hipSuccess) r = fail(OPDHG_ERR_DEVICE, "upload failed");
+        int r = upload_slot(ws + offs[i], L[i], P[i], p->precision, s, im, pin.ptr + i);
+        // (also after a failure: the kernels write pinned memory)
+        if (hipStreamSynchronize(s) != hipSuccess && !r) r = fail(OPDHG_ERR_DEVICE, "upload failed");
         if (r) {
           urc[i] = r;
           msgs[i] = opdhg_last_error();
@@ -3678,16 +3705,11 @@ static int batch_solve(opdhg_batch& B, void* d_workspace, size_t workspace_bytes
     grp.release();
     return rc;
   }
-  Ctl* pinned = nullptr;
-  if (hipHostMalloc((void**)&pinned, sizeof(Ctl) * count, hipHostMallocDefault) != hipSuccess) {
-    grp.release();
-    return fail(OPDHG_ERR_DEVICE, "pinned host allocation failed");
-  }
   std::vector<Ctl*> ctls(count);
   for (int i = 0; i < count; ++i) ctls[i] = lpd[i].ctl;
   std::vector<Ctl> h(count);
   double elapsed = 0.0;
-  rc = run_group(grp, ctls, h, pinned, -1, p->time_limit_s, &elapsed);
+  rc = run_group(grp, ctls, h, pin.ptr, -1, p->time_limit_s, &elapsed);
   for (int i = 0; i < count && rc == 0; ++i) {
     const Ctl& c = h[i];
     if (x_out && x_out[i]) {
@@ -3704,7 +3726,6 @@ static int batch_solve(opdhg_batch& B, void* d_workspace, size_t workspace_bytes
     }
     fill_result(c, elapsed, &res[i]);
   }
-  (void)hipHostFree(pinned);
   grp.release();
   return rc;
 }

@@ -3641,15 +3641,19 @@ __global__ void k_power_step(PrepCfg a, int round) {
   const DD t = wave_totals<1>(v);
   if (threadIdx.x != 0) return;
   const double lam_new = sqrt(dd_value(t));
+  auto stop = [&]() {
+    a.scr[a.pw_at + 1] = 1.0;
+    if (a.stop) __hip_atomic_store(a.stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  };
   if (lam_new == 0.0) {
     a.scr[a.pw_at + 2] = 1.0;
-    a.scr[a.pw_at + 1] = 1.0;
+    stop();
     return;
   }
   const double lam = a.scr[a.pw_at];
   const bool done = fabs(lam_new - lam) <= a.power_tol * lam_new;
   a.scr[a.pw_at] = lam_new;
-  if (done) a.scr[a.pw_at + 1] = 1.0;
+  if (done) stop();
 }
 
 // eta0 = step_scale / |A~|_2 (step_scale when the norm is 0) into the
@@ -4106,29 +4110,35 @@ int struct_build(const StructCfg& c, void* stream) {
 int power_norm(const PrepCfg& c, void* stream) {
   const int64_t lanes = (int64_t)c.m * kPwLanes;
   const int ga = (int)std::max<int64_t>(1, std::min<int64_t>(4096, (lanes + kBlock - 1) / kBlock));
-  // the stopping flag is read after 8 rounds, 16 more, 32, and every 64 from
-  // there: a read costs as much as two rounds, the rounds after the stop
-  // three empty launches each (9 us)
-  int r = 0;
-  for (int block = 8; r < c.power_iters; block = std::min(2 * block, 64)) {
-    for (const int end = std::min(c.power_iters, r + block); r < end; ++r) {
-      hipLaunchKernelGGL(k_power_av, dim3(ga), dim3(kBlock), 0, (hipStream_t)stream, c, r);
-      if (launched()) return -1;
-      hipLaunchKernelGGL(k_power_w, dim3(c.pw_grid), dim3(kBlock), 0, (hipStream_t)stream, c, r);
-      if (launched()) return -1;
-      hipLaunchKernelGGL(k_power_step, dim3(1), dim3(64), 0, (hipStream_t)stream, c, r);
-      if (launched()) return -1;
+  // No rounds are launched once the iteration has stopped: each costs 9 us of
+  // empty launches. With a flag in pinned host memory (c.stop), which
+  // k_power_step sets, a look at it costs nothing and the launches run on
+  // meanwhile. Without one the device's flag is read back after 8 rounds, 16
+  // more, 32, and every 64 from there, at some 50 to 130 us a read.
+  int next = 8, more = 16;
+  if (c.stop) __atomic_store_n(c.stop, 0, __ATOMIC_RELAXED);
+  for (int r = 0; r < c.power_iters; ++r) {
+    if (c.stop) {
+      if (__atomic_load_n(c.stop, __ATOMIC_RELAXED)) break;
+    } else if (r == next) {
+      double done = 0.0;
+      hipError_t e = hipMemcpyAsync(&done, c.scr + c.pw_at + 1, sizeof(done),
+                                    hipMemcpyDeviceToHost, (hipStream_t)stream);
+      if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
+      if (e != hipSuccess) {
+        g_last_device_error = e;
+        return -1;
+      }
+      if (done != 0.0) break;
+      next += more;
+      more = std::min(2 * more, 64);
     }
-    if (r == c.power_iters) break;
-    double done = 0.0;
-    hipError_t e = hipMemcpyAsync(&done, c.scr + c.pw_at + 1, sizeof(done), hipMemcpyDeviceToHost,
-                                  (hipStream_t)stream);
-    if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
-    if (e != hipSuccess) {
-      g_last_device_error = e;
-      return -1;
-    }
-    if (done != 0.0) break;
+    hipLaunchKernelGGL(k_power_av, dim3(ga), dim3(kBlock), 0, (hipStream_t)stream, c, r);
+    if (launched()) return -1;
+    hipLaunchKernelGGL(k_power_w, dim3(c.pw_grid), dim3(kBlock), 0, (hipStream_t)stream, c, r);
+    if (launched()) return -1;
+    hipLaunchKernelGGL(k_power_step, dim3(1), dim3(64), 0, (hipStream_t)stream, c, r);
+    if (launched()) return -1;
   }
   hipLaunchKernelGGL(k_power_final, dim3(1), dim3(64), 0, (hipStream_t)stream, c);
   return launched();

@@ -188,9 +188,10 @@ SlotLayout slot_layout(const Prepared& P, int prec);
 LpDev slot_pointers(uint8_t* base, const SlotLayout& L, const Prepared& P);
 // Writes the slot's image; with device-side preparation also runs the
 // preparation kernels and fills P.dr, P.dc, P.eta0 and P.omega0 from the
-// device (synchronizes the stream then).
+// device (synchronizes the stream then). pinned (optional): four bytes of
+// pinned host memory that the kernels may write until they have finished.
 int upload_slot(uint8_t* base, const SlotLayout& L, Prepared& P, int prec, hipStream_t stream,
-                SlotImage& img);
+                SlotImage& img, void* pinned = nullptr);
 // Launch tables of a set of LPs at dst: LP table, both work lists (chunked
 // over at most cap workgroups), counts and the Ctl board. With capacity > 0,
 // OPDHG_ERR_OVER_BUDGET when they need more bytes. With fixed_launch the

@@ -539,6 +539,9 @@ struct PrepCfg {
   // its workgroups, whose norm partials start scr, and the place of its
   // scalars there (see k_power_av)
   int32_t pw_grid, pw_at, pad;
+  // pinned host memory, or null: set once the power iteration has stopped, for
+  // the host to launch no more of it (see power_norm)
+  int32_t* stop;
 };
 constexpr int kPrepScr = 4 * kPrepGrid + 6;
 // Device-side structure of one slot (the host keeps only the row and

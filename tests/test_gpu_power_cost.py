@@ -2,9 +2,10 @@
 than on the host, whichever side the automatic preparation takes, and the same
 bits. Best of several creations; the bounds are a few milliseconds where
 launches for nothing would take ten, and 0.7 where they would take 1.3. And
-the same bits from the fewest entries that the device takes (3072) on, in one
+the same bits from the fewest entries that the device takes (2560) on, in one
 row, in one column and at the ends of a group of 8 lanes and of a workgroup's
-32 rows, with limits around the rounds after which it looks for the end."""
+32 rows, with limits around the rounds after which it looks for the end, in
+sessions, packed sets and the allocation-free solve."""
 
 import time
 
@@ -62,14 +63,29 @@ def test_small_lps_cost_no_more_than_on_the_host(P):
         assert dev[0] < host[0] + 0.7, (m, n, dev, host)
 
 
-@pytest.mark.parametrize("m,n,degree", [(1, 3072, 1), (7, 1025, 3), (8, 1031, 3), (9, 770, 4),
-                                        (500, 8, 400), (5000, 1, 3500), (200, 33, 100), (31, 257, 12)])
+@pytest.mark.parametrize("m,n,degree", [(1, 2560, 1), (7, 861, 3), (8, 857, 3), (9, 650, 4),
+                                        (500, 8, 320), (5000, 1, 2600), (200, 33, 78), (31, 257, 10),
+                                        (31, 257, 12), (600, 1100, 6)])
 def test_device_norm_from_its_fewest_entries_on(P, m, n, degree):
     lp = random_lp((m, n), m, n, degree=("fixed", degree), eq_frac=0.5)
-    assert lp.val.size >= 3072
+    assert lp.val.size >= 2560
     for rounds in (1, 8, 9, 24, 25, 200):
         got = []
         for prep in (P.OPDHG_PREP_AUTO, P.OPDHG_PREP_HOST):
             with P.Session(lp, P.opdhg_vanilla_params(0.0, power_iters=rounds, prep=prep)) as s:
                 got.append(s.state()[4].eta)
         assert got[0] == got[1], rounds
+
+
+def test_packed_and_allocation_free_solves(P):
+    # the allocation-free solve has no pinned memory to see the end in
+    lps = [random_lp((3, k), 300, 500, degree=("uniform", 3, 8), eq_frac=0.5) for k in range(3)]
+    lps += [_permutation_lp(2000)]
+    for rounds in (1, 8, 9, 24, 25, 56, 57, 1000):
+        p = P.opdhg_vanilla_params(1e-2, tol=0.0, max_iter=20, power_iters=rounds)
+        solo = [P.opdhg_solve(lp, P.opdhg_vanilla_params(1e-2, tol=0.0, max_iter=20, power_iters=rounds,
+                                                         prep=P.OPDHG_PREP_HOST)) for lp in lps]
+        for got in (P.opdhg_solve_batch(lps, p), [P.opdhg_solve_noalloc(lp, p) for lp in lps]):
+            for a, b in zip(got, solo):
+                assert a[2].eta == b[2].eta, rounds
+                assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
